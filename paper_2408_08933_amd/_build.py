@@ -23,10 +23,10 @@ COMMON = [
 
 
 # Kernels whose correctness depends on issuing no vector-memory operation
-# beyond their own (the FP16 kNN counts its outstanding loads by hand): a
+# beyond their own (the FP16 kNN kernels count their outstanding loads by hand): a
 # register spill would add scratch traffic to those counts, so it fails the
 # build.
-NO_SCRATCH = {"knn.hip": ["k_knn16"]}
+NO_SCRATCH = {"knn.hip": ["k_knn16", "k_scan16"]}
 
 
 def _check_no_scratch(src: str, remarks: str) -> None:

@@ -247,109 +247,60 @@ void knn_scan_row(const float *q, const float *X, int64_t n, int32_t d, int32_t 
 }  // namespace
 
 // Exact k nearest base rows of every query row, in canonical (delta, id)
-// order.  The GPU proposes K candidates per row (first from FP16 rows, at
-// the FP16 matrix rate, when every value fits FP16's range; rows it cannot
-// certify then from FP32 rows with K doubling up to 256); the candidates are
-// rescored with the canonical FP64 distance and a row is kept when its
-// certificate shows no other base row can be among its k nearest.  Rows no
-// list of 256 certifies are scanned in full on the host.
+// order, to device memory.  The GPU proposes K candidates per row (first from
+// FP16 rows, at the FP16 matrix rate, when every value fits FP16's range; rows
+// it cannot certify then from FP32 rows with K doubling up to 256); the
+// candidates are rescored with the canonical FP64 distance and a row is kept
+// when its certificate shows no other base row can be among its k nearest.
+// Rows no list of 256 certifies are scanned in full on the host.
+//
+// The values the certificate needs (the largest row norm and element) come
+// from the pass that makes the FP16 rows, results stay on the device, and the
+// host sees the count of rows not certified; the base comes back to the host
+// only for the scan.  Before, both matrices were copied to the host for the
+// norms and the lists went through it: on 10k x 1M x 200 that was 215 of 270
+// ms.
 int knn_exact(const float *Qdev, int64_t nq, const float *Xdev, int64_t n, int32_t d, int32_t k, int32_t slack,
-              const float *Qhost, const float *Xhost, int threads, std::vector<uint32_t> *ids_out,
-              std::vector<double> *d_out, hipStream_t st) {
+              const float *Xhost, int threads, uint32_t *ids, float *dists, hipStream_t st) {
     threads = hw_threads(threads);
     if (slack <= 0) slack = std::max(16, k / 4);
-    ids_out->assign((size_t)nq * k, kNone);
-    if (d_out) d_out->assign((size_t)nq * k, INFINITY);
     g_knn_rows[0] = g_knn_rows[1] = g_knn_rows[2] = 0;
     const bool log = std::getenv("RG_LOG") != nullptr;
     const double u32 = std::ldexp(1.0, -24), u64 = std::ldexp(1.0, -53), u16 = std::ldexp(1.0, -11);
     const double g64 = (d + 1) * u64 / (1.0 - (d + 1) * u64);
-    std::vector<double> norm2((size_t)n);
-    std::vector<float> xabs((size_t)n), qabs((size_t)nq);  // largest |element| per row
-    par_rows(n, threads, [&](int64_t i) {
-        double s = 0.0;
-        float a = 0.f;
-        for (int j = 0; j < d; ++j) {
-            s += (double)Xhost[i * d + j] * (double)Xhost[i * d + j];
-            a = std::max(a, std::fabs(Xhost[i * d + j]));
-        }
-        norm2[i] = s;
-        xabs[i] = a;
-    });
-    par_rows(nq, threads, [&](int64_t i) {
-        float a = 0.f;
-        for (int j = 0; j < d; ++j) a = std::max(a, std::fabs(Qhost[i * d + j]));
-        qabs[i] = a;
-    });
-    const double xmax = std::sqrt(*std::max_element(norm2.begin(), norm2.end())) * (1.0 + 1e-12);
-    const float amax = std::max(*std::max_element(xabs.begin(), xabs.end()),
-                                nq ? *std::max_element(qabs.begin(), qabs.end()) : 0.f);
+    const int32_t dp = knn16_width(d);
+    const int32_t K16 = (int32_t)std::min<int64_t>(std::min<int64_t>(256, n), std::max(2 * k, k + 48));
+    const int32_t s16 = knn16_sample(n, K16);
 
-    std::vector<int64_t> rows((size_t)nq);
-    for (int64_t i = 0; i < nq; ++i) rows[i] = i;
+    // lists of rows still open (this pass's and the next one's) and their count
+    DevBuf lists, small;
+    int rc = lists.alloc(2 * sizeof(uint32_t) * (size_t)nq);
+    if (!rc) rc = small.alloc(2 * sizeof(PackStats) + 16);
+    if (rc) return rc;
+    uint32_t *open_rows = lists.as<uint32_t>(), *next_rows = open_rows + nq;
+    PackStats *st_q = small.as<PackStats>(), *st_x = st_q + 1;
+    uint32_t *n_fail = reinterpret_cast<uint32_t *>(st_x + 1);
+    int64_t m = nq;  // rows open; all of them in order while m == nq
+    bool all = true;
 
-    // One pass: candidates of the rows listed (kind 16 or 32, K per row),
-    // certification, results of the certified rows; `rows` keeps the others.
-    auto pass = [&](const float *qd, const void *cand_q, const void *cand_x, int32_t dp, bool f16, int32_t K,
-                     double gsum, double eta, double abs0) -> int {
-        const int64_t m = (int64_t)rows.size();
-        DevBuf cid, csc;
-        int rc = cid.alloc(sizeof(uint32_t) * (size_t)m * K);
-        if (!rc) rc = csc.alloc(sizeof(float) * (size_t)m * K);
-        if (rc) return rc;
-        rc = f16 ? launch_knn16_candidates(cand_q, m, cand_x, n, d, dp, K, cid.as<uint32_t>(), csc.as<float>(), st)
-                 : launch_knn_candidates(static_cast<const float *>(cand_q), m, d, static_cast<const float *>(cand_x),
-                                         n, d, d, K, cid.as<uint32_t>(), csc.as<float>(), st);
-        if (rc) return rc;
-        DevBuf oid, od, okb;
-        rc = oid.alloc(sizeof(uint32_t) * (size_t)m * k);
-        if (!rc && d_out) rc = od.alloc(sizeof(double) * (size_t)m * k);
-        if (!rc) rc = okb.alloc((size_t)m);
-        if (rc) return rc;
-        rc = launch_knn_certify(qd, m, d, Xdev, n, d, d, cid.as<uint32_t>(), csc.as<float>(), K, k, gsum, xmax, eta,
-                                abs0, oid.as<uint32_t>(), d_out ? od.as<double>() : nullptr, okb.as<uint8_t>(), st);
-        if (rc) return rc;
-        std::vector<uint32_t> hid((size_t)m * k);
-        std::vector<double> hd(d_out ? (size_t)m * k : 0);
-        std::vector<uint8_t> ok((size_t)m, 0);
-        RG_HIP(hipMemcpyAsync(hid.data(), oid.p, sizeof(uint32_t) * hid.size(), hipMemcpyDeviceToHost, st));
-        if (d_out) RG_HIP(hipMemcpyAsync(hd.data(), od.p, sizeof(double) * hd.size(), hipMemcpyDeviceToHost, st));
-        RG_HIP(hipMemcpyAsync(ok.data(), okb.p, ok.size(), hipMemcpyDeviceToHost, st));
+    // One pass: candidates of the open rows, certification, results of the
+    // certified rows; the others stay open.
+    double xmax = 0.0;
+    auto certify = [&](const float *qd, const uint32_t *cid, const float *csc, bool f16, int32_t K, double gsum,
+                       double eta, double abs0) -> int {
+        int r = launch_knn_certify(qd, m, d, Xdev, n, d, d, cid, csc, K, k, gsum, xmax, eta, abs0,
+                                   all ? nullptr : open_rows, ids, dists, next_rows, n_fail, st);
+        if (r) return r;
+        uint32_t nf = 0;
+        RG_HIP(hipMemcpyAsync(&nf, n_fail, 4, hipMemcpyDeviceToHost, st));
         RG_HIP(hipStreamSynchronize(st));
-        par_rows(m, threads, [&](int64_t i) {
-            if (!ok[i]) return;
-            const int64_t q = rows[i];
-            std::memcpy(&(*ids_out)[q * k], &hid[i * k], sizeof(uint32_t) * k);
-            if (d_out) std::memcpy(&(*d_out)[q * k], &hd[i * k], sizeof(double) * k);
-        });
-        std::vector<int64_t> fail;
-        for (int64_t i = 0; i < m; ++i)
-            if (!ok[i]) fail.push_back(rows[i]);
-        g_knn_rows[f16 ? 0 : 1] += m - (int64_t)fail.size();
+        g_knn_rows[f16 ? 0 : 1] += m - (int64_t)nf;
         if (log)
             std::fprintf(stderr, "[rg] knn %s candidates: %lld rows, K=%d, %lld not certified\n", f16 ? "FP16" : "FP32",
-                         (long long)m, K, (long long)fail.size());
-        rows.swap(fail);
-        return RG_OK;
-    };
-    // the query rows still uncertified, gathered contiguously on the device
-    std::vector<float> qsub;
-    DevBuf qbuf;
-    auto gather_rows = [&](const float **qd) -> int {
-        if ((int64_t)rows.size() == nq) {
-            *qd = Qdev;
-            return RG_OK;
-        }
-        qsub.resize(rows.size() * (size_t)d);
-        for (size_t i = 0; i < rows.size(); ++i) std::memcpy(&qsub[i * d], Qhost + rows[i] * d, sizeof(float) * d);
-        if (qbuf.p) {
-            (void)hipFree(qbuf.p);
-            qbuf.p = nullptr;
-        }
-        int rc = qbuf.alloc(sizeof(float) * qsub.size());
-        if (rc) return rc;
-        RG_HIP(hipMemcpyAsync(qbuf.p, qsub.data(), sizeof(float) * qsub.size(), hipMemcpyHostToDevice, st));
-        *qd = qbuf.as<float>();
+                         (long long)m, K, (long long)nf);
+        std::swap(open_rows, next_rows);
+        m = nf;
+        all = false;
         return RG_OK;
     };
 
@@ -361,40 +312,92 @@ int knn_exact(const float *Qdev, int64_t nq, const float *Xdev, int64_t n, int32
     //   (2 u16 + u16^2 + gacc (1 + u16)^2) sum|t_i x_i|
     //   + (1 + gacc) (1 + u16) eta0 (|t|_1 + |x|_1) + (1 + gacc) d eta0^2,
     // with sum|t_i x_i| <= |t| xmax and |v|_1 <= sqrt(d) |v|.
-    if (amax < 32768.f) {
-        const int32_t dp = knn16_width(d);
-        const int32_t K = (int32_t)std::min<int64_t>(std::min<int64_t>(256, n), std::max(2 * k, k + 48));
-        const double eta0 = std::ldexp(1.0, -25);
-        const double gacc = 2.0 * dp * u32 / (1.0 - 2.0 * dp * u32);
-        const double gsum = 2 * u16 + u16 * u16 + gacc * (1 + u16) * (1 + u16) + g64;
-        const double eta = (1 + gacc) * (1 + u16) * eta0 * std::sqrt((double)d);
-        const double abs0 = (1 + gacc) * d * eta0 * eta0;
-        DevBuf q16, x16;
-        int rc = q16.alloc(2 * (size_t)knn16_rows(nq) * dp);
-        if (!rc) rc = x16.alloc(2 * (size_t)knn16_rows(n) * dp);
-        if (!rc) rc = launch_to_f16(Qdev, nq, d, d, q16.p, knn16_rows(nq), dp, st);
-        if (!rc) rc = launch_to_f16(Xdev, n, d, d, x16.p, knn16_rows(n), dp, st);
-        if (!rc) rc = pass(Qdev, q16.p, x16.p, dp, true, K, gsum, eta, abs0);
+    {
+        const size_t hq = 2 * (size_t)knn16_rows(nq) * dp, hx = 2 * (size_t)knn16_rows(n) * dp;
+        const size_t hs = s16 > 0 ? 2 * (size_t)knn16_rows((n + s16 - 1) / s16) * dp : 0;
+        DevBuf half, cand;
+        rc = half.alloc(hq + hx + hs);
         if (rc) return rc;
+        char *q16 = half.as<char>(), *x16 = q16 + hq, *smp = s16 > 0 ? x16 + hx : nullptr;
+        rc = launch_pack16(Qdev, nq, d, d, q16, knn16_rows(nq), dp, nullptr, 0, st_q, st);
+        if (!rc) rc = launch_pack16(Xdev, n, d, d, x16, knn16_rows(n), dp, smp, s16, st_x, st);
+        if (rc) return rc;
+        PackStats h[2];
+        RG_HIP(hipMemcpyAsync(h, st_q, sizeof(h), hipMemcpyDeviceToHost, st));
+        RG_HIP(hipStreamSynchronize(st));
+        double norm2;
+        float aq, ax;
+        std::memcpy(&norm2, &h[1].norm2, 8);
+        std::memcpy(&aq, &h[0].amax, 4);
+        std::memcpy(&ax, &h[1].amax, 4);
+        // the sums of squares, in another order, may be off by d ulps
+        xmax = h[1].nan0 ? NAN : std::sqrt(norm2) * (1.0 + 1e-12 + d * u64);
+        if (std::max(aq, ax) < 32768.f) {
+            const double eta0 = std::ldexp(1.0, -25);
+            const double gacc = 2.0 * dp * u32 / (1.0 - 2.0 * dp * u32);
+            const double gsum = 2 * u16 + u16 * u16 + gacc * (1 + u16) * (1 + u16) + g64;
+            const double eta = (1 + gacc) * (1 + u16) * eta0 * std::sqrt((double)d);
+            const double abs0 = (1 + gacc) * d * eta0 * eta0;
+            rc = cand.alloc(8 * (size_t)nq * K16);
+            if (rc) return rc;
+            uint32_t *cid = cand.as<uint32_t>();
+            float *csc = reinterpret_cast<float *>(cid + (size_t)nq * K16);
+            rc = launch_knn16_candidates(q16, nq, x16, n, d, dp, smp, s16, K16, cid, csc, st);
+            if (!rc) rc = certify(Qdev, cid, csc, true, K16, gsum, eta, abs0);
+            if (rc) return rc;
+        }
     }
     // FP32 passes for what is left, K doubling
     const double g32 = (d + 1) * u32 / (1.0 - (d + 1) * u32);
     int32_t K = (int32_t)std::min<int64_t>(n, (int64_t)k + slack);
     if (K > 256) K = std::max(k, 256);
-    while (!rows.empty()) {
-        const float *qd = nullptr;
-        int rc = gather_rows(&qd);
-        if (!rc) rc = pass(qd, qd, Xdev, d, false, K, g32 + g64, 0.0, 0.0);
+    while (m > 0) {
+        DevBuf qbuf, cand;
+        const float *qd = Qdev;
+        if (!all) {
+            rc = qbuf.alloc(sizeof(float) * (size_t)m * d);
+            if (!rc) rc = launch_gather_rows(Qdev, open_rows, m, d, qbuf.as<float>(), st);
+            if (rc) return rc;
+            qd = qbuf.as<float>();
+        }
+        rc = cand.alloc(8 * (size_t)m * K);
         if (rc) return rc;
-        if (rows.empty() || K >= 256 || K >= n) break;
+        uint32_t *cid = cand.as<uint32_t>();
+        float *csc = reinterpret_cast<float *>(cid + (size_t)m * K);
+        rc = launch_knn_candidates(qd, m, d, Xdev, n, d, d, K, cid, csc, st);
+        if (!rc) rc = certify(qd, cid, csc, false, K, g32 + g64, 0.0, 0.0);
+        if (rc) return rc;
+        if (m == 0 || K >= 256 || K >= n) break;
         K = (int32_t)std::min<int64_t>(std::min<int64_t>(256, n), 2 * (int64_t)K);
     }
+    if (m == 0) return RG_OK;
     // the rest by a full canonical scan on the host
-    if (log && !rows.empty())
-        std::fprintf(stderr, "[rg] knn: %lld rows scanned on the host\n", (long long)rows.size());
-    for (int64_t q : rows)
-        knn_scan_row(Qhost + q * d, Xhost, n, d, k, threads, &(*ids_out)[q * k], d_out ? &(*d_out)[q * k] : nullptr);
-    g_knn_rows[2] = (int64_t)rows.size();
+    if (log) std::fprintf(stderr, "[rg] knn: %lld rows scanned on the host\n", (long long)m);
+    std::vector<float> xh, q((size_t)d), hd((size_t)k);
+    if (!Xhost) {
+        rc = copy_to_host(Xdev, n * d, xh, st);
+        if (rc) return rc;
+        Xhost = xh.data();
+    }
+    std::vector<uint32_t> rows((size_t)m), hid((size_t)k);
+    std::vector<double> dd((size_t)k);
+    if (!all) {
+        RG_HIP(hipMemcpyAsync(rows.data(), open_rows, sizeof(uint32_t) * (size_t)m, hipMemcpyDeviceToHost, st));
+        RG_HIP(hipStreamSynchronize(st));
+    } else {
+        for (int64_t i = 0; i < m; ++i) rows[i] = (uint32_t)i;
+    }
+    for (uint32_t r : rows) {
+        rc = copy_to_host(Qdev + (int64_t)r * d, d, q, st);
+        if (rc) return rc;
+        knn_scan_row(q.data(), Xhost, n, d, k, threads, hid.data(), dd.data());
+        for (int j = 0; j < k; ++j) hd[j] = (float)dd[j];
+        RG_HIP(hipMemcpyAsync(ids + (int64_t)r * k, hid.data(), sizeof(uint32_t) * k, hipMemcpyHostToDevice, st));
+        if (dists)
+            RG_HIP(hipMemcpyAsync(dists + (int64_t)r * k, hd.data(), sizeof(float) * k, hipMemcpyHostToDevice, st));
+        RG_HIP(hipStreamSynchronize(st));
+    }
+    g_knn_rows[2] = m;
     return RG_OK;
 }
 
@@ -424,28 +427,26 @@ int rg_knn_candidates_f16(const float *queries, int64_t nq, const float *base, i
     }
     if (nq == 0) return RG_OK;
     hipStream_t st = (hipStream_t)stream;
-    std::vector<float> qh, xh;
-    int rc = copy_to_host(queries, nq * d, qh, st);
-    if (!rc) rc = copy_to_host(base, n * d, xh, st);
-    if (rc) return rc;
-    for (float v : qh)
-        if (!(std::fabs(v) < 32768.f)) {
-            set_error("rg_knn_candidates_f16: a query value is out of the FP16 range used (|v| < 2^15)");
-            return RG_EINVAL;
-        }
-    for (float v : xh)
-        if (!(std::fabs(v) < 32768.f)) {
-            set_error("rg_knn_candidates_f16: a base value is out of the FP16 range used (|v| < 2^15)");
-            return RG_EINVAL;
-        }
-    const int32_t dp = knn16_width(d);
-    DevBuf q16, x16;
-    rc = q16.alloc(2 * (size_t)knn16_rows(nq) * dp);
+    const int32_t dp = knn16_width(d), s = knn16_sample(n, K);
+    DevBuf q16, x16, smp, stats;
+    int rc = q16.alloc(2 * (size_t)knn16_rows(nq) * dp);
     if (!rc) rc = x16.alloc(2 * (size_t)knn16_rows(n) * dp);
-    if (!rc) rc = launch_to_f16(queries, nq, d, d, q16.p, knn16_rows(nq), dp, st);
-    if (!rc) rc = launch_to_f16(base, n, d, d, x16.p, knn16_rows(n), dp, st);
-    if (!rc) rc = launch_knn16_candidates(q16.p, nq, x16.p, n, d, dp, K, ids, scores, st);
-    return rc;
+    if (!rc && s > 0) rc = smp.alloc(2 * (size_t)knn16_rows((n + s - 1) / s) * dp);
+    if (!rc) rc = stats.alloc(2 * sizeof(PackStats));
+    if (!rc)
+        rc = launch_pack16(queries, nq, d, d, q16.p, knn16_rows(nq), dp, nullptr, 0, stats.as<PackStats>(), st);
+    if (!rc) rc = launch_pack16(base, n, d, d, x16.p, knn16_rows(n), dp, smp.p, s, stats.as<PackStats>() + 1, st);
+    if (rc) return rc;
+    PackStats h[2];
+    RG_HIP(hipMemcpyAsync(h, stats.p, sizeof(h), hipMemcpyDeviceToHost, st));
+    RG_HIP(hipStreamSynchronize(st));
+    for (int i = 0; i < 2; ++i)
+        if (h[i].bad) {
+            set_error(std::string("rg_knn_candidates_f16: a ") + (i == 0 ? "query" : "base") +
+                      " value is out of the FP16 range used (|v| < 2^15)");
+            return RG_EINVAL;
+        }
+    return launch_knn16_candidates(q16.p, nq, x16.p, n, d, dp, smp.p, s, K, ids, scores, st);
 }
 
 int rg_knn_last_stats(int64_t *rows_f16, int64_t *rows_f32, int64_t *rows_host) {
@@ -464,20 +465,7 @@ int rg_knn(const float *queries, int64_t nq, const float *base, int64_t n, int32
     }
     if (nq == 0) return RG_OK;
     hipStream_t st = (hipStream_t)stream;
-    std::vector<float> qh, xh;
-    int rc = copy_to_host(queries, nq * d, qh, st);
-    if (!rc) rc = copy_to_host(base, n * d, xh, st);
-    if (rc) return rc;
-    std::vector<uint32_t> hid;
-    std::vector<double> hd;
-    rc = knn_exact(queries, nq, base, n, d, k, 0, qh.data(), xh.data(), 0, &hid, &hd, st);
-    if (rc) return rc;
-    std::vector<float> hdf(hd.size());
-    for (size_t i = 0; i < hd.size(); ++i) hdf[i] = (float)hd[i];
-    RG_HIP(hipMemcpyAsync(ids, hid.data(), sizeof(uint32_t) * hid.size(), hipMemcpyHostToDevice, st));
-    RG_HIP(hipMemcpyAsync(dists, hdf.data(), sizeof(float) * hdf.size(), hipMemcpyHostToDevice, st));
-    RG_HIP(hipStreamSynchronize(st));
-    return RG_OK;
+    return knn_exact(queries, nq, base, n, d, k, 0, nullptr, 0, ids, dists, st);
 }
 
 int rg_build(const float *base, int64_t n, int32_t d, const float *train, int64_t nt, int32_t Nq, int32_t M,
@@ -502,19 +490,22 @@ int rg_build(const float *base, int64_t n, int32_t d, const float *train, int64_
     const auto t0 = std::chrono::steady_clock::now();
     std::vector<float> xh, th;
     int rc = copy_to_host(base, n * d, xh, st);
-    if (!rc) rc = copy_to_host(train, nt * d, th, st);
+    if (!rc && o.keep_stages) rc = copy_to_host(train, nt * d, th, st);
     if (rc) return rc;
-    std::vector<uint32_t> knn;
+    std::vector<uint32_t> knn((size_t)nt * Nq);
     if (std::getenv("RG_LOG")) std::fprintf(stderr, "[rg] build: n=%lld d=%d nt=%lld Nq=%d M=%d L=%d\n", (long long)n, d, (long long)nt, Nq, M, L);
-    rc = knn_exact(train, nt, base, n, d, Nq, o.knn_slack, th.data(), xh.data(), threads, &knn, nullptr, st);
-    if (rc) return rc;
+    {
+        DevBuf ids;
+        rc = ids.alloc(sizeof(uint32_t) * knn.size());
+        if (!rc)
+            rc = knn_exact(train, nt, base, n, d, Nq, o.knn_slack, xh.data(), threads, ids.as<uint32_t>(), nullptr, st);
+        if (rc) return rc;
+        RG_HIP(hipMemcpyAsync(knn.data(), ids.p, sizeof(uint32_t) * knn.size(), hipMemcpyDeviceToHost, st));
+        RG_HIP(hipStreamSynchronize(st));
+    }
     if (std::getenv("RG_LOG"))
         std::fprintf(stderr, "[rg] kNN preprocessing done in %.2f s\n",
                      std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count());
-    if (!o.keep_stages) {
-        th.clear();
-        th.shrink_to_fit();
-    }
     const auto t1 = std::chrono::steady_clock::now();
     rg_index *ix = new rg_index();
     ix->n = n;

@@ -130,19 +130,33 @@ int launch_read_stream(const void *src, int64_t bytes, void *sink, int blocks, h
 int launch_mfma_probe(int kind, int iters, void *sink, int blocks, hipStream_t stream, double *flop);
 
 // The same from FP16 rows (round to nearest even): Q16 and X16 hold
-// knn16_rows(rows) rows of knn16_width(d) halves, zero padded.
+// knn16_rows(rows) rows of knn16_width(d) halves, zero padded and packed (see
+// knn.hip).  S16: every s-th base row, packed the same way (s =
+// knn16_sample(n, K); 0: no sample).
 int64_t knn16_rows(int64_t rows);
 int32_t knn16_width(int32_t d);
-int launch_to_f16(const float *src, int64_t rows, int32_t d, int64_t ld, void *dst, int64_t rows_pad, int32_t dp,
-                  hipStream_t stream);
+int32_t knn16_sample(int64_t n, int32_t K);
+struct PackStats {
+    unsigned long long norm2;  // bits of the largest squared row norm (FP64; NaN norms passed over)
+    uint32_t amax;             // bits of the largest |element| (FP32; NaN passed over)
+    uint32_t bad;              // some element is not below 2^15 in magnitude
+    uint32_t nan0;             // row 0's norm is a NaN
+    uint32_t pad;
+};
+int launch_pack16(const float *src, int64_t rows, int32_t d, int64_t ld, void *dst, int64_t rows_pad, int32_t dp,
+                  void *dst_s, int32_t s, PackStats *st, hipStream_t stream);
 int launch_knn16_candidates(const void *Q16, int64_t nq, const void *X16, int64_t n, int32_t d, int32_t dp,
-                            int32_t K, uint32_t *ids, float *scores, hipStream_t stream);
+                            const void *S16, int32_t s, int32_t K, uint32_t *ids, float *scores, hipStream_t stream);
 // Canonical FP64 rescoring, sort and certification of m rows of K
-// candidates (see knn.hip); ok[i] = 1 where row i's k results are exact.
+// candidates (see knn.hip).  Row i's k results go to row map[i] (null: i) of
+// the outputs when they are exact, else map[i] is appended to fail (*n_fail
+// counts from zero).
 // A candidate score errs by at most gsum |t| xmax + eta (|t| + xmax) + abs0.
 int launch_knn_certify(const float *Q, int64_t m, int64_t ldq, const float *X, int64_t n, int64_t ldx, int32_t d,
                        const uint32_t *cid, const float *csc, int32_t K, int32_t k, double gsum, double xmax,
-                       double eta, double abs0, uint32_t *out_id, double *out_d, uint8_t *ok, hipStream_t stream);
+                       double eta, double abs0, const uint32_t *map, uint32_t *out_id, float *out_d, uint32_t *fail,
+                       uint32_t *n_fail, hipStream_t stream);
+int launch_gather_rows(const float *src, const uint32_t *list, int64_t m, int32_t d, float *dst, hipStream_t stream);
 
 // quant.hip
 int launch_pad_rows(const float *src, int64_t n, int32_t d, float *dst, int32_t pitch,
@@ -276,10 +290,10 @@ int launch_canon_search(const float *X, int32_t d, int32_t pitch, const uint32_t
 // canonical FP64 distance helpers (host)
 double canon_dist(const float *a, const float *b, int32_t d);
 
-// exact kNN = GPU candidates + host certification (api.cpp)
-int knn_exact(const float *Qdev, int64_t nq, const float *Xdev, int64_t n, int32_t d, int32_t k,
-              int32_t slack, const float *Qhost, const float *Xhost, int threads,
-              std::vector<uint32_t> *ids_out, std::vector<double> *d_out, hipStream_t stream);
+// exact kNN on the device (api.cpp); ids (nq x k) and dists (or null) are
+// device memory.  Xhost: a host copy of the base, or null (made if needed).
+int knn_exact(const float *Qdev, int64_t nq, const float *Xdev, int64_t n, int32_t d, int32_t k, int32_t slack,
+              const float *Xhost, int threads, uint32_t *ids, float *dists, hipStream_t stream);
 
 int hw_threads(int requested);
 
