@@ -258,9 +258,11 @@ int rg_index_set_storage(rg_index *idx, int32_t storage, void *stream);
  * stay below 5% of a query's expected row bytes (40 L_eff rows of 4d
  * bytes) or the graph is held as CSR (rows over 128 ids);
  * otherwise, and for BF16 / FP8, a visited table in LDS that forgets and
- * rescores (the results are the same; evals counts the rescoring): the
- * largest of 2^10, 2^9 and 2^8 entries that lets the most workgroups share
- * a CU (2^8 only while it holds twice a row batch).
+ * rescores (the results are the same; evals counts the rescoring): 4, 2 or 1
+ * KB of it, the largest that keeps the most wavefronts at work (1 KB only
+ * while twice a row batch is at most 256 ids).  For n up to 2^24 (4 KB: 2^25;
+ * 1 KB: 2^23) and rows of at most 64 ids it holds 16-bit entries in sets of
+ * four that drop their oldest; otherwise node ids, cleared at half load.
  * Asynchronous on stream.
  * Errors: RG_EINVAL, RG_EDEVICE.
  */
@@ -337,10 +339,10 @@ int rg_search_noalloc(const rg_index *idx, const float *queries, int64_t nq, int
                       uint32_t *ids, float *dists, uint32_t *hops, uint32_t *evals, void *stream);
 
 /*
- * rg_search_hashbits -- rg_search with the LDS visited table fixed at
- * 2^hash_bits entries (8..15, and at least twice the ELL row width).  The
- * table only bounds work (a cleared table makes nodes be scored again), so
- * results are identical for every size; tests use it to show that.
+ * rg_search_hashbits -- rg_search with the LDS visited table fixed at 4 *
+ * 2^hash_bits bytes (8..15, and at least twice the ELL row width in 4-byte
+ * entries).  The table only bounds work (a forgotten node is scored again),
+ * so results are identical for every size; tests use it to show that.
  */
 int rg_search_hashbits(const rg_index *idx, const float *queries, int64_t nq, int32_t k, int32_t L,
                        uint32_t *ids, float *dists, uint32_t *hops, uint32_t *evals, int32_t hash_bits,
@@ -403,8 +405,8 @@ typedef struct {
     int64_t hbm_pool_bytes;   /* bound on slot state bytes; 0 => no bound beyond max_slots */
     int32_t hops_per_step;    /* expansions per slot per step; 0 => 32 */
     int32_t max_L;            /* largest L_eff accepted (<= 512); 0 => 512 */
-    int32_t hash_bits;        /* visited table of 2^hash_bits ids per slot (8..13, and at least
-                                 twice the candidate batch); it bounds work, not results;
+    int32_t hash_bits;        /* visited table of 4 * 2^hash_bits bytes per slot (8..13, and
+                                 2^hash_bits at least twice the candidate batch); it bounds work, not results;
                                  0 => 9 */
 } rg_server_limits;
 

@@ -10,6 +10,9 @@ CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libroargraph.so")
 SOURCES = ["beam.hip", "knn.hip", "quant.hip", "canon.hip", "peaks.hip", "api.cpp", "host_build.cpp", "serve.cpp"]
+# sources compiled in parts, with these flags (see beam.hip)
+VARIANTS = {"beam.hip": [[]] + [[f"-DRG_BEAM_STORAGE={st}", f"-DRG_BEAM_PART={part}"] for st in (0, 1, 2)
+                                for part in (0, 1, 2)]}
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 COMMON = [
@@ -41,12 +44,21 @@ def _check_no_scratch(src: str, remarks: str) -> None:
                     raise RuntimeError(f"{src}: {kern} spills to scratch ({size} bytes per lane)")
 
 
-def _compile(src: str) -> str:
+def units() -> list[tuple[str, list[str], str]]:
+    """(source, extra flags, object file) of every compilation, the longest first."""
+    u = []
+    for src in SOURCES:
+        for i, flags in enumerate(VARIANTS.get(src, [[]])):
+            u.append((src, flags, os.path.join(OBJ, f"{src}.{i}.o" if i else f"{src}.o")))
+    return sorted(u, key=lambda x: not x[1])
+
+
+def _compile(unit: tuple[str, list[str], str]) -> str:
+    src, flags, obj = unit
     path = os.path.join(CSRC, src)
-    obj = os.path.join(OBJ, src + ".o")
     lang = ["-x", "hip"] if src.endswith(".hip") else []
     extra = ["-Rpass-analysis=kernel-resource-usage"] if src in NO_SCRATCH else []
-    cmd = [HIPCC, *COMMON, *lang, *extra, "-c", path, "-o", obj]
+    cmd = [HIPCC, *COMMON, *lang, *extra, *flags, "-c", path, "-o", obj]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError(f"compile failed: {' '.join(cmd)}\n{r.stdout}\n{r.stderr}")
@@ -57,9 +69,10 @@ def _compile(src: str) -> str:
 def build(jobs: int | None = None) -> str:
     """Compile every source (always) and link the shared library."""
     os.makedirs(OBJ, exist_ok=True)
-    jobs = jobs or min(len(SOURCES), os.cpu_count() or 4)
+    todo = units()
+    jobs = jobs or min(len(todo), os.cpu_count() or 4)
     with cf.ThreadPoolExecutor(max_workers=jobs) as ex:
-        objs = list(ex.map(_compile, SOURCES))
+        objs = list(ex.map(_compile, todo))
     tmp = LIB + ".tmp"
     cmd = [HIPCC, "-shared", "-fPIC", "--offload-arch=gfx950", "-o", tmp, *objs, "-lpthread"]
     r = subprocess.run(cmd, capture_output=True, text=True)

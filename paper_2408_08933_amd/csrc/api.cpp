@@ -132,29 +132,53 @@ int upload_adj(rg_index *ix, hipStream_t st) {
     return RG_OK;
 }
 
-// Visited table of the LDS-table search: the largest of 2^10, 2^9 and 2^8
-// ids that lets the most workgroups share a CU (2^8 only while it holds
-// twice a row batch, as rg_search_hashbits requires).  The table only
-// bounds work; a smaller one forgets and rescores a little more.  Measured
-// per 10k queries: on 10M x 200 at L = 417, E4M3 rows 14.1 -> 11.6 ms and
-// BF16 18.3 -> 17.8 ms with 2^9 (16 -> 20 workgroups per CU) for 0.8% more
-// rows scored; on 8M x 512 at L = 803, E4M3 80.5 -> 66.5 ms and BF16 70.2
-// -> 65.7 ms with 2^8 (13 -> 15) for 0.7% more.  FP32 rows on 10M x 200 are
-// held to 16 workgroups per CU by registers and keep 2^10.
-int table_bits(SearchArgs a) {
+}  // namespace
+
+// The visited table of the LDS-table search at 4 << hash_bits bytes: sets of
+// 16-bit entries, or ids where an entry would need more bits (n > 2^(15 +
+// hash_bits)) or an expansion more than one turn (rows over 64 ids, CSR).
+void set_table(SearchArgs &a, int hash_bits) {
+    int bits = 1;
+    while (bits < 31 && (a.n_rows - 1) >> bits) ++bits;
+    a.hash_bits = hash_bits;
+    a.id_bits = std::max(bits, hash_bits - 1);
+    a.sets = !a.adj_off && a.ell <= 64 && a.id_bits - (hash_bits - 1) <= 16;
+}
+
+namespace {
+
+// The size: the largest of 4, 2 and 1 KB that keeps the most wavefronts per
+// SIMD at work, as far as there are queries for them.  A smaller table scores
+// more rows (about 7% from one size to the next), fewer wavefronts wait
+// longer for each: per row, E4M3 d = 200 L = 409 takes 0.69 / 0.80 / 1.00 (us
+// x 1e-3) at 20 / 16 / 11 workgroups per CU, BF16 d = 128 0.54 / 0.67 at 24 /
+// 16, and counts between two multiples of 4 run like the lower one (a SIMD
+// more or less).  The LDS is handed out in 1,280-byte pieces, which the
+// occupancy query leaves out.  BF16 rows of 768 bytes and more wait for
+// bandwidth instead (d = 512: 1.54 / 1.61 / 1.55 at 20 / 18 / 14) and take the
+// largest table.
+int choose_table(SearchArgs &a, int cus) {
     const int width = a.adj_off ? kMaxEll : a.ell;  // ids inserted per batch
+    const int64_t want = (a.nq + cus - 1) / std::max(1, cus);
     int best = 10, occ = -1;
     for (int hb = 10; hb >= 8; --hb) {
         if ((1 << hb) < 2 * width + 2) break;
         int o = 0;
-        a.hash_bits = hb;
-        if (table_search_occupancy(a, &o)) return best;
+        set_table(a, hb);
+        const int rc = table_search_occupancy(a, &o);
+        if (rc) return rc;
+        const int piece = 1280, lds = (int)search_lds_bytes(a.Leff, a.qpad, hb, a.cand);
+        o = std::min(o, (160 << 10) / ((lds + piece - 1) / piece * piece));
+        if (o >= 4) o &= ~3;
+        o = (int)std::min<int64_t>(o, want);
         if (o > occ) {
             occ = o;
             best = hb;
         }
+        if (hb == 10 && a.storage == RG_STORE_BF16 && a.d >= 384 && o >= 12) break;
     }
-    return best;
+    set_table(a, best);
+    return RG_OK;
 }
 
 // Search parameters common to every search entry point.
@@ -182,6 +206,7 @@ SearchArgs search_args(const rg_index *ix, const float *queries, int64_t nq, int
     a.Leff = std::max(k, L);
     a.cand = cand_capacity(ix->ell, ix->d_adj_off != nullptr);
     a.hash_bits = 0;
+    a.n_rows = ix->n;
     a.entry = ix->entry;
     a.storage = ix->storage;
     return a;
@@ -959,13 +984,14 @@ int rg_search(const rg_index *ix, const float *queries, int64_t nq, int32_t k, i
     if (nq == 0) return RG_OK;
     hipStream_t st = (hipStream_t)stream;
     SearchArgs a = search_args(ix, queries, nq, k, L, ids, dists, hops, evals);
+    int cus = 0;
+    RG_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, ix->device));
     if (ix->storage != RG_STORE_FP32) {
         // BF16 / FP8 rows: the search waits on memory latency, not bandwidth;
         // a small LDS visited table (no device atomics) is faster even though
-        // it forgets and rescores some rows (same results), the more so when
-        // it is small enough to let more workgroups share a CU
-        a.hash_bits = table_bits(a);
-        return launch_search(a, st);
+        // it forgets and rescores some rows (same results)
+        const int rc = choose_table(a, cus);
+        return rc ? rc : launch_search(a, st);
     }
     // FP32 rows, bandwidth bound.  The persistent kernel's exact visited
     // bitmap costs about n/8 bytes per query (the clear, then the lines its
@@ -978,15 +1004,14 @@ int rg_search(const rg_index *ix, const float *queries, int64_t nq, int32_t k, i
     // always for CSR graphs, whose wide rows would overflow the table at
     // every expansion.
     if (!ix->d_adj_off && (double)ix->n / 8.0 > 0.05 * 40.0 * std::max(L, k) * 4.0 * ix->d) {
-        a.hash_bits = table_bits(a);
-        return launch_search(a, st);
+        const int rc = choose_table(a, cus);
+        return rc ? rc : launch_search(a, st);
     }
     // persistent grid: as many resident workgroups as the chip holds, each
     // with its own visited bitmap (bounded to 8 GiB in total)
-    int per_cu = 0, cus = 0;
+    int per_cu = 0;
     int rc = search_occupancy(a, &per_cu);
     if (rc) return rc;
-    RG_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, ix->device));
     a.bm_words = ((ix->n + 31) / 32 + 63) / 64 * 64;
     int64_t grid = (int64_t)std::max(1, per_cu) * std::max(1, cus);
     grid = std::min<int64_t>(grid, nq);
@@ -1068,7 +1093,7 @@ int rg_search_hashbits(const rg_index *ix, const float *queries, int64_t nq, int
         return RG_EINVAL;
     }
     SearchArgs a = search_args(ix, queries, nq, k, L, ids, dists, hops, evals);
-    a.hash_bits = hash_bits;
+    set_table(a, hash_bits);
     return launch_search(a, (hipStream_t)stream);
 }
 

@@ -4,11 +4,12 @@
 // Per query, in LDS:
 //   * the queue: the best L_eff (delta, id) pairs seen, sorted ascending, the
 //     id's top bit marking "expanded";
-//   * an open-addressing visited table of node ids.  When it passes half
-//     load it is cleared; a node seen again is then scored again and dropped
-//     at the merge if it is already queued.  Because the queue's last key
-//     only decreases once the queue is full, a forgotten node that was
-//     rejected or evicted is rejected again, so clearing changes only the
+//   * a visited table that forgets: sets of 16-bit entries that drop their
+//     oldest, or an open-addressing table of node ids that is cleared when it
+//     passes half load.  A forgotten node seen again is scored again and
+//     dropped at the merge if it is already queued.  Because the queue's last
+//     key only decreases once the queue is full, a forgotten node that was
+//     rejected or evicted is rejected again, so forgetting changes only the
 //     work done, never the result;
 //   * the candidate batch of the current expansion.
 // Per expansion: pick the first unexpanded queue entry, read its adjacency
@@ -32,11 +33,29 @@
 #include <climits>
 #include <mutex>
 
+// The build compiles this file in parts, side by side: per storage form
+// (RG_BEAM_STORAGE = RG_STORE_*) the search with a visited table of ids
+// (RG_BEAM_PART 0) or of 16-bit entries (1) and the other kernels (2), and
+// once without them the dispatch and the rest.
 namespace rg {
+
+// the launches of one storage form
+template <int ST>
+struct BeamOps {
+    static int search_ids(const SearchArgs &a, hipStream_t s);   // visited table of ids
+    static int search_sets(const SearchArgs &a, hipStream_t s);  // visited table of 16-bit entries
+    static int ids_occupancy(const SearchArgs &a);
+    static int sets_occupancy(const SearchArgs &a);
+    static int persistent(const SearchArgs &a, hipStream_t s);
+    static int persistent_occupancy(const SearchArgs &a);
+    static int serve_step(const SlotArgs &a, hipStream_t s);
+    static int serve_occupancy(const SlotArgs &a);
+};
+
+#ifdef RG_BEAM_STORAGE
 namespace {
 
 constexpr uint32_t kEmpty = 0xFFFFFFFFu;
-constexpr int kCand = 128;  // largest candidate batch (the widest ELL row, a CSR chunk)
 
 struct Lds {
     float *qs;      // the query, zero padded to the row pitch
@@ -61,6 +80,7 @@ __device__ __forceinline__ Lds carve(unsigned char *p, int Leff, int pitch, int 
     s.sd = reinterpret_cast<float *>(s.ci + cand);
     s.si = reinterpret_cast<uint32_t *>(s.sd + cand);
     s.slb = reinterpret_cast<int32_t *>(s.si + cand);
+    // 8-byte aligned: qpad and cand are even and L_eff counts twice
     s.htab = reinterpret_cast<uint32_t *>(s.slb + cand);
     return s;
 }
@@ -71,15 +91,7 @@ typedef float f32x2 __attribute__((ext_vector_type(2)));
 // Storage formats: 16-byte chunks of EPC elements.
 template <int ST>
 struct Fmt {
-    static constexpr int EPC = 4;
-};
-template <>
-struct Fmt<RG_STORE_BF16> {
-    static constexpr int EPC = 8;
-};
-template <>
-struct Fmt<RG_STORE_FP8E4M3> {
-    static constexpr int EPC = 16;
+    static constexpr int EPC = ST == RG_STORE_FP32 ? 4 : ST == RG_STORE_BF16 ? 8 : 16;
 };
 
 // Lane shape per dimension class (d <= 64, 128, 224, 256, 512, 1024) and
@@ -102,7 +114,7 @@ constexpr int shape_r(int st, int cls) { return st == RG_STORE_FP8E4M3 && cls <=
 // can reach, so bytes past d meet a zero).
 __device__ __forceinline__ void load_query(const float *q, int d, int qpad, float *qs) {
     for (int i = lane_id(); i < qpad; i += 64) qs[i] = i < d ? q[i] : 0.f;
-    __syncthreads();
+    wave_sync();
 }
 
 // Chunks of a stored row the search reads: the d elements, and for E4M3 rows
@@ -264,6 +276,7 @@ __device__ __forceinline__ uint32_t hslot(uint32_t u, int hb) { return (u * 2654
 struct VisitLds {
     uint32_t *htab;
     int hb, H, hcount;
+    __device__ __forceinline__ VisitLds(uint32_t *t, int hash_bits, int) : htab(t), hb(hash_bits), H(1 << hb), hcount(0) {}
     __device__ __forceinline__ void clear() {
         for (int i = lane_id(); i < H; i += 64) htab[i] = kEmpty;
         hcount = 0;
@@ -274,7 +287,7 @@ struct VisitLds {
     __device__ __forceinline__ void begin_hop(int ell) {
         if (hcount + ell > (H >> 1)) {
             clear();
-            __syncthreads();
+            wave_sync();
         }
     }
     __device__ __forceinline__ bool insert(uint32_t u) {
@@ -289,6 +302,67 @@ struct VisitLds {
         return false;
     }
     __device__ __forceinline__ void added(int k) { hcount += k; }
+    // what a resumed search needs beside the table's words
+    __device__ __forceinline__ int count() const { return hcount; }
+    __device__ __forceinline__ void restore(int c) { hcount = c; }
+};
+
+// Visited set kept in LDS that forgets one node at a time: 2^set_bits sets of
+// four 16-bit entries, the newest first; a new node pushes its set's oldest
+// one out.  A node's bits are spread by an odd multiplier (a bijection of the
+// id_bits-bit numbers); the product's top set_bits bits name the set and the
+// rest, which must fit 16 bits, is the entry, so an entry is one node and no
+// other.  Half the bytes of an id per node, and never cleared: at any time it
+// holds the last 4 * 2^set_bits nodes (up to uneven sets), where a table
+// cleared at half load holds a quarter of its ids on average.  Rows scored
+// per query, 10k queries a launch: 2M x 512 E4M3 at L = 409 26,160 -> 20,400
+// (2 KB; 16,560 distinct) and 40.0 -> 34.1 ms, 500k x 200 BF16 at L = 805,
+// 3,001 queries, 44,310 -> 33,200 (26,890) and 11.1 -> 8.8 ms, 700k x 100
+// FP32 at L = 32, 4,096 queries, 2,190 -> 1,713 (1,704) and 0.83 -> 0.69 ms.
+//
+// Lanes of one expansion that meet in a set take turns: each turn one lane's
+// compare-and-swap succeeds and the others look at the set again, so a node
+// that stands twice in an adjacency row is taken once.  That needs the row in
+// one turn (at most 64 ids).  The entry 0xFFFF marks a free place; the one
+// node per set that would have it (16-bit entries only) is never remembered,
+// and copies of it within a row are told apart by a vote.
+struct VisitSets {
+    unsigned long long *tab;
+    int set_bits, rest_bits;
+    uint32_t idmask;
+    __device__ __forceinline__ VisitSets(uint32_t *t, int hash_bits, int id_bits)
+        : tab(reinterpret_cast<unsigned long long *>(t)), set_bits(hash_bits - 1), rest_bits(id_bits - hash_bits + 1),
+          idmask(id_bits >= 32 ? 0xFFFFFFFFu : (1u << id_bits) - 1u) {}
+    __device__ __forceinline__ void clear() {
+        for (int i = lane_id(); i < (1 << set_bits); i += 64) tab[i] = ~0ull;
+    }
+    __device__ __forceinline__ void mark_entry(uint32_t u) { (void)insert(u); }
+    __device__ __forceinline__ void begin_hop(int) {}
+    __device__ __forceinline__ void added(int) {}
+    __device__ __forceinline__ int count() const { return 0; }
+    __device__ __forceinline__ void restore(int) {}
+    __device__ __forceinline__ bool insert(uint32_t u) {
+        const uint32_t h = (u * 2654435761u) & idmask;
+        const uint32_t rest = h & ((1u << rest_bits) - 1u), twice = rest * 0x10001u;
+        unsigned long long *p = tab + (h >> rest_bits);
+        bool fresh = true;
+        for (uint64_t m = ballot64(rest == 0xFFFFu); m; m &= m - 1) {
+            const int src = (int)__builtin_ctzll(m);
+            // readlane: the lanes after src compare with it, whichever are active
+            const uint32_t first = (uint32_t)__builtin_amdgcn_readlane((int)u, src);
+            if (u == first && lane_id() > src) fresh = false;
+        }
+        if (rest == 0xFFFFu) return fresh;
+        unsigned long long old = *p;
+        for (;;) {
+            // a 16-bit half of a word is zero iff the node is there
+            const uint32_t a = (uint32_t)old ^ twice, b = (uint32_t)(old >> 32) ^ twice;
+            if ((((a - 0x10001u) & ~a) | ((b - 0x10001u) & ~b)) & 0x80008000u) return false;
+            const unsigned long long got = atomicCAS(p, old, (old << 16) | rest);
+            if (got == old) return true;
+            old = got;
+        }
+    }
 };
 
 // Exact visited set: one bit per base node in device memory, owned by the
@@ -338,7 +412,7 @@ __device__ __forceinline__ void run_search(const SearchArgs &a, const Lds &s, VI
         }
         ptr = sel;
         const uint32_t v = s.qi[sel];
-        __syncthreads();
+        wave_sync();
         if (lane == 0) s.qi[sel] = v | kExpanded;
         ++hops;
         // ELL row (width ell), or a CSR row of any length taken a.cand ids
@@ -368,16 +442,16 @@ __device__ __forceinline__ void run_search(const SearchArgs &a, const Lds &s, VI
             }
             vis.added(nnew);
             evals += (uint32_t)nnew;
-            __syncthreads();
+            wave_sync();
             if (nnew == 0) continue;
             score_batch<ST, G, NCH, R>(a, s.qs, nch, s.ci, 0xFFFFFFFFu, s.cd, nnew);
-            __syncthreads();
+            wave_sync();
             const QueueLds<float> ql{s.qd, s.qi, s.cd, s.ci, s.sd, s.si, s.slb};
             if (nnew <= 64)
                 merge_batch<1, float, QR>(ql, nnew, Leff, qn, ptr);
             else
                 merge_batch<2, float, QR>(ql, nnew, Leff, qn, ptr);
-            __syncthreads();
+            wave_sync();
         }
     }
 }
@@ -394,7 +468,7 @@ __device__ __forceinline__ void init_state(const SearchArgs &a, const Lds &s, VI
     dot_rows<ST, G, NCH, 1>(a, u, s.qs, row_chunk_count<ST>(a.d), acc, sc);
     acc[0] = group_sum<G>(acc[0]);
     if constexpr (ST == RG_STORE_FP8E4M3) sc[0] = group_sum<G>(sc[0]);
-    __syncthreads();
+    wave_sync();
     if (lane == 0) {
         s.qd[0] = finish_delta<ST>(acc[0], sc[0]);
         s.qi[0] = a.entry;
@@ -405,7 +479,7 @@ __device__ __forceinline__ void init_state(const SearchArgs &a, const Lds &s, VI
     ptr = 0;
     hops = 0;
     evals = 1;
-    __syncthreads();
+    wave_sync();
 }
 
 // Rescore the final queue (at most 64 * QR entries) against FP32 rows and
@@ -414,7 +488,7 @@ template <int CLS, int QR>
 __device__ __forceinline__ void rerank_queue(const SearchArgs &a, const Lds &s, int qn) {
     constexpr int G = shape_g(RG_STORE_FP32, CLS), NCH = shape_nch(RG_STORE_FP32, CLS);
     score_batch<RG_STORE_FP32, G, NCH, 2>(a, s.qs, (a.d + 3) >> 2, s.qi, ~kExpanded, s.qd, qn);
-    __syncthreads();
+    wave_sync();
     constexpr int E = QR;
     const int lane = lane_id();
     float k[E];
@@ -426,7 +500,7 @@ __device__ __forceinline__ void rerank_queue(const SearchArgs &a, const Lds &s, 
         id[e] = i < qn ? (s.qi[i] & ~kExpanded) : kNone;
     }
     wave_sort<E>(k, id);
-    __syncthreads();
+    wave_sync();
 #pragma unroll
     for (int e = 0; e < E; ++e) {
         const int i = lane * E + e;
@@ -435,7 +509,7 @@ __device__ __forceinline__ void rerank_queue(const SearchArgs &a, const Lds &s, 
             s.qi[i] = id[e];
         }
     }
-    __syncthreads();
+    wave_sync();
 }
 
 // The k results: the first k entries of the final queue that are not
@@ -491,13 +565,14 @@ __device__ __forceinline__ void write_result(const SearchArgs &a, const Lds &s, 
 // QR = queue capacity / 64: kMaxL / 64, or kMaxSearchL / 64 for L_eff above
 // kMaxL, where twice the queue entries per lane in the merge and the rerank
 // take four resident wavefronts per SIMD for every storage form.
-template <int ST, int CLS, int QR>
+// VIS: VisitSets, or VisitLds (rg_search_hashbits, wide rows, huge bases).
+template <int ST, int CLS, int QR, class VIS>
 __global__ __launch_bounds__(64)
 __attribute__((amdgpu_waves_per_eu(ST == RG_STORE_FP32 || QR > kMaxL / 64 ? 4 : 5))) void k_search(SearchArgs a) {
     extern __shared__ __align__(16) unsigned char smem[];
     const int64_t q = blockIdx.x;
     const Lds s = carve(smem, a.Leff, a.qpad, a.cand);
-    VisitLds vis{s.htab, a.hash_bits, 1 << a.hash_bits, 0};
+    VIS vis(s.htab, a.hash_bits, a.id_bits);
     load_query(a.queries + q * a.d, a.d, a.qpad, s.qs);
     int qn, ptr;
     uint32_t hops, evals;
@@ -534,7 +609,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
         run_search<ST, CLS, QR>(a, s, vis, qn, ptr, hops, evals, INT_MAX, done);
         if constexpr (ST != RG_STORE_FP32) rerank_queue<CLS, QR>(a, s, qn);
         write_result(a, s, q, qn, hops, evals);
-        __syncthreads();
+        wave_sync();
     }
 }
 
@@ -544,7 +619,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
 // Slot state word 0: 0 = admitted, not started; > 0 = queue length of a
 // search in progress; -1 = finished (its record written; the slot is
 // skipped until the host admits a new request into it).
-template <int ST, int CLS>
+template <int ST, int CLS, class VIS>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5))) void k_serve_step(SlotArgs sa) {
     extern __shared__ __align__(16) unsigned char smem[];
     const int slot = sa.active[blockIdx.x];
@@ -562,13 +637,13 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5))) void k_
     uint32_t *gh = sa.slot_hash + ((size_t)slot << a.hash_bits);
     int qn, ptr;
     uint32_t hops, evals;
-    VisitLds vis{s.htab, a.hash_bits, H, 0};
+    VIS vis(s.htab, a.hash_bits, a.id_bits);
     if (st[0] == 0) {
         init_state<ST, CLS>(a, s, vis, qn, ptr, hops, evals);
     } else {
         qn = st[0];
         ptr = st[1];
-        vis.hcount = st[2];
+        vis.restore(st[2]);
         hops = (uint32_t)st[3];
         evals = (uint32_t)st[4];
         for (int i = lane; i < qn; i += 64) {
@@ -576,7 +651,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5))) void k_
             s.qi[i] = gqi[i];
         }
         for (int i = lane; i < H; i += 64) s.htab[i] = gh[i];
-        __syncthreads();
+        wave_sync();
     }
     bool done;
     run_search<ST, CLS, kMaxL / 64>(a, s, vis, qn, ptr, hops, evals, sa.hops_budget, done);
@@ -603,43 +678,27 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5))) void k_
         if (lane == 0) {
             st[0] = qn;
             st[1] = ptr;
-            st[2] = vis.hcount;
+            st[2] = vis.count();
             st[3] = (int32_t)hops;
             st[4] = (int32_t)evals;
         }
     }
 }
 
-__global__ __launch_bounds__(64) void k_serve_admit(int32_t n, const int32_t *slots, const float *q,
-                                                   const int32_t *k, const int32_t *L, int32_t d, float *slot_q,
-                                                   int32_t *slot_k, int32_t *slot_L, int32_t *slot_state) {
-    const int i = blockIdx.x;
-    const int s = slots[i];
-    for (int j = threadIdx.x; j < d; j += 64) slot_q[(size_t)s * d + j] = q[(size_t)i * d + j];
-    if (threadIdx.x < 8) slot_state[(size_t)s * 8 + threadIdx.x] = 0;
-    if (threadIdx.x == 0) {
-        slot_k[s] = k[i];
-        slot_L[s] = L[i];
-    }
-}
-
 // The kernels for a queue of L_eff entries: kMaxL or fewer, or up to kMaxSearchL.
-template <int ST, int CLS>
+template <int ST, int CLS, class VIS>
 void (*table_kernel(int Leff))(SearchArgs) {
-    return Leff > kMaxL ? k_search<ST, CLS, kMaxSearchL / 64> : k_search<ST, CLS, kMaxL / 64>;
+    return Leff > kMaxL ? k_search<ST, CLS, kMaxSearchL / 64, VIS> : k_search<ST, CLS, kMaxL / 64, VIS>;
 }
 template <int ST, int CLS>
 void (*persistent_kernel(int Leff))(SearchArgs) {
     return Leff > kMaxL ? k_search_persistent<ST, CLS, kMaxSearchL / 64> : k_search_persistent<ST, CLS, kMaxL / 64>;
 }
 
-template <int ST, int CLS>
-int launch_one(const SearchArgs &a, hipStream_t stream) {
+template <int ST, int CLS, class VIS>
+int launch_table(const SearchArgs &a, hipStream_t stream) {
     const size_t lds = search_lds_bytes(a.Leff, a.qpad, a.hash_bits, a.cand);
-    if (a.Leff > kMaxL)
-        hipLaunchKernelGGL((k_search<ST, CLS, kMaxSearchL / 64>), dim3((unsigned)a.nq), dim3(64), lds, stream, a);
-    else
-        hipLaunchKernelGGL((k_search<ST, CLS, kMaxL / 64>), dim3((unsigned)a.nq), dim3(64), lds, stream, a);
+    hipLaunchKernelGGL((table_kernel<ST, CLS, VIS>(a.Leff)), dim3((unsigned)a.nq), dim3(64), lds, stream, a);
     RG_HIP(hipGetLastError());
     return RG_OK;
 }
@@ -665,9 +724,14 @@ int occupancy_of(int Leff, int pitch, int cand, int *blocks_per_cu) {
 }
 
 template <int ST, int CLS>
+void (*step_kernel(const SearchArgs &a))(SlotArgs) {
+    return a.sets ? k_serve_step<ST, CLS, VisitSets> : k_serve_step<ST, CLS, VisitLds>;
+}
+
+template <int ST, int CLS>
 int launch_step(const SlotArgs &sa, hipStream_t stream) {
     const size_t lds = search_lds_bytes(kMaxL, sa.s.qpad, sa.s.hash_bits, sa.s.cand);
-    hipLaunchKernelGGL((k_serve_step<ST, CLS>), dim3((unsigned)sa.n_active), dim3(64), lds, stream, sa);
+    hipLaunchKernelGGL((step_kernel<ST, CLS>(sa.s)), dim3((unsigned)sa.n_active), dim3(64), lds, stream, sa);
     RG_HIP(hipGetLastError());
     return RG_OK;
 }
@@ -685,21 +749,24 @@ int dispatch_dim(int d, const Arg &a, hipStream_t stream) {
     return RG_EINVAL;
 }
 
-template <int ST, int CLS>
-struct SearchLaunch {
-    static int run(const SearchArgs &a, hipStream_t s) { return launch_one<ST, CLS>(a, s); }
+template <class VIS>
+struct Table {
+    template <int ST, int CLS>
+    struct Launch {
+        static int run(const SearchArgs &a, hipStream_t s) { return launch_table<ST, CLS, VIS>(a, s); }
+    };
+    template <int ST, int CLS>
+    struct Occ {
+        static int run(const SearchArgs &a, hipStream_t) {
+            const size_t lds = search_lds_bytes(a.Leff, a.qpad, a.hash_bits, a.cand);
+            RG_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(a.occ_out, table_kernel<ST, CLS, VIS>(a.Leff), 64, lds));
+            return RG_OK;
+        }
+    };
 };
 template <int ST, int CLS>
 struct PersistentLaunch {
     static int run(const SearchArgs &a, hipStream_t s) { return launch_persistent<ST, CLS>(a, s); }
-};
-template <int ST, int CLS>
-struct TableOcc {
-    static int run(const SearchArgs &a, hipStream_t) {
-        const size_t lds = search_lds_bytes(a.Leff, a.qpad, a.hash_bits, a.cand);
-        RG_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(a.occ_out, table_kernel<ST, CLS>(a.Leff), 64, lds));
-        return RG_OK;
-    }
 };
 template <int ST, int CLS>
 struct OccLaunch {
@@ -715,10 +782,79 @@ template <int ST, int CLS>
 struct StepOcc {
     static int run(const SlotArgs &a, hipStream_t) {
         const size_t lds = search_lds_bytes(kMaxL, a.s.qpad, a.s.hash_bits, a.s.cand);
-        RG_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(a.s.occ_out, k_serve_step<ST, CLS>, 64, lds));
+        RG_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(a.s.occ_out, step_kernel<ST, CLS>(a.s), 64, lds));
         return RG_OK;
     }
 };
+
+}  // namespace
+
+constexpr int kST = RG_BEAM_STORAGE;
+#if RG_BEAM_PART == 0
+template <>
+int BeamOps<kST>::search_ids(const SearchArgs &a, hipStream_t s) {
+    return dispatch_dim<Table<VisitLds>::Launch, kST>(a.d, a, s);
+}
+template <>
+int BeamOps<kST>::ids_occupancy(const SearchArgs &a) {
+    return dispatch_dim<Table<VisitLds>::Occ, kST>(a.d, a, nullptr);
+}
+#elif RG_BEAM_PART == 1
+template <>
+int BeamOps<kST>::search_sets(const SearchArgs &a, hipStream_t s) {
+    return dispatch_dim<Table<VisitSets>::Launch, kST>(a.d, a, s);
+}
+template <>
+int BeamOps<kST>::sets_occupancy(const SearchArgs &a) {
+    return dispatch_dim<Table<VisitSets>::Occ, kST>(a.d, a, nullptr);
+}
+#else
+template <>
+int BeamOps<kST>::persistent(const SearchArgs &a, hipStream_t s) {
+    return dispatch_dim<PersistentLaunch, kST>(a.d, a, s);
+}
+template <>
+int BeamOps<kST>::persistent_occupancy(const SearchArgs &a) {
+    return dispatch_dim<OccLaunch, kST>(a.d, a, nullptr);
+}
+template <>
+int BeamOps<kST>::serve_step(const SlotArgs &a, hipStream_t s) {
+    return dispatch_dim<StepLaunch, kST>(a.s.d, a, s);
+}
+template <>
+int BeamOps<kST>::serve_occupancy(const SlotArgs &a) {
+    return dispatch_dim<StepOcc, kST>(a.s.d, a, nullptr);
+}
+#endif
+
+#else  // !RG_BEAM_STORAGE
+namespace {
+
+constexpr int kCand = 128;  // largest candidate batch (the widest ELL row, a CSR chunk)
+
+__global__ __launch_bounds__(64) void k_serve_admit(int32_t n, const int32_t *slots, const float *q,
+                                                   const int32_t *k, const int32_t *L, int32_t d, float *slot_q,
+                                                   int32_t *slot_k, int32_t *slot_L, int32_t *slot_state) {
+    const int i = blockIdx.x;
+    const int s = slots[i];
+    for (int j = threadIdx.x; j < d; j += 64) slot_q[(size_t)s * d + j] = q[(size_t)i * d + j];
+    if (threadIdx.x < 8) slot_state[(size_t)s * 8 + threadIdx.x] = 0;
+    if (threadIdx.x == 0) {
+        slot_k[s] = k[i];
+        slot_L[s] = L[i];
+    }
+}
+
+// f(BeamOps of the storage form)
+template <class F>
+int with_storage(int storage, const char *who, F &&f) {
+    switch (storage) {
+    case RG_STORE_FP32: return f(BeamOps<RG_STORE_FP32>());
+    case RG_STORE_BF16: return f(BeamOps<RG_STORE_BF16>());
+    case RG_STORE_FP8E4M3: return f(BeamOps<RG_STORE_FP8E4M3>());
+    default: set_error(std::string(who) + ": unknown storage"); return RG_EINVAL;
+    }
+}
 
 }  // namespace
 
@@ -728,53 +864,26 @@ size_t search_lds_bytes(int Leff, int pitch, int hash_bits, int cand) {
 
 int cand_capacity(int ell, bool csr) { return csr || ell > 64 ? kCand : 64; }
 
-int default_hash_bits(int Leff) {
-    // table of about 16 entries per queue slot, 2^11 .. 2^13
-    int hb = 11;
-    while (hb < 13 && (1 << hb) < 16 * Leff) ++hb;
-    return hb;
-}
-
 int launch_search(const SearchArgs &a, hipStream_t stream) {
     if (a.nq == 0) return RG_OK;
-    switch (a.storage) {
-    case RG_STORE_FP32: return dispatch_dim<SearchLaunch, RG_STORE_FP32>(a.d, a, stream);
-    case RG_STORE_BF16: return dispatch_dim<SearchLaunch, RG_STORE_BF16>(a.d, a, stream);
-    case RG_STORE_FP8E4M3: return dispatch_dim<SearchLaunch, RG_STORE_FP8E4M3>(a.d, a, stream);
-    default: set_error("search: unknown storage"); return RG_EINVAL;
-    }
+    return with_storage(a.storage, "search", [&](auto ops) { return a.sets ? ops.search_sets(a, stream) : ops.search_ids(a, stream); });
 }
 
 int launch_search_persistent(const SearchArgs &a, hipStream_t stream) {
     if (a.nq == 0) return RG_OK;
-    switch (a.storage) {
-    case RG_STORE_FP32: return dispatch_dim<PersistentLaunch, RG_STORE_FP32>(a.d, a, stream);
-    case RG_STORE_BF16: return dispatch_dim<PersistentLaunch, RG_STORE_BF16>(a.d, a, stream);
-    case RG_STORE_FP8E4M3: return dispatch_dim<PersistentLaunch, RG_STORE_FP8E4M3>(a.d, a, stream);
-    default: set_error("search: unknown storage"); return RG_EINVAL;
-    }
+    return with_storage(a.storage, "search", [&](auto ops) { return ops.persistent(a, stream); });
 }
 
 int search_occupancy(const SearchArgs &a, int *blocks_per_cu) {
     SearchArgs b = a;
     b.occ_out = blocks_per_cu;
-    switch (a.storage) {
-    case RG_STORE_FP32: return dispatch_dim<OccLaunch, RG_STORE_FP32>(a.d, b, nullptr);
-    case RG_STORE_BF16: return dispatch_dim<OccLaunch, RG_STORE_BF16>(a.d, b, nullptr);
-    case RG_STORE_FP8E4M3: return dispatch_dim<OccLaunch, RG_STORE_FP8E4M3>(a.d, b, nullptr);
-    default: set_error("search: unknown storage"); return RG_EINVAL;
-    }
+    return with_storage(a.storage, "search", [&](auto ops) { return ops.persistent_occupancy(b); });
 }
 
 int table_search_occupancy(const SearchArgs &a, int *blocks_per_cu) {
     SearchArgs b = a;
     b.occ_out = blocks_per_cu;
-    switch (a.storage) {
-    case RG_STORE_FP32: return dispatch_dim<TableOcc, RG_STORE_FP32>(a.d, b, nullptr);
-    case RG_STORE_BF16: return dispatch_dim<TableOcc, RG_STORE_BF16>(a.d, b, nullptr);
-    case RG_STORE_FP8E4M3: return dispatch_dim<TableOcc, RG_STORE_FP8E4M3>(a.d, b, nullptr);
-    default: set_error("search: unknown storage"); return RG_EINVAL;
-    }
+    return with_storage(a.storage, "search", [&](auto ops) { return b.sets ? ops.sets_occupancy(b) : ops.ids_occupancy(b); });
 }
 
 int launch_serve_admit(int32_t n, const int32_t *slots, const float *q, const int32_t *k, const int32_t *L,
@@ -789,23 +898,13 @@ int launch_serve_admit(int32_t n, const int32_t *slots, const float *q, const in
 
 int launch_serve_step(const SlotArgs &sa, hipStream_t stream) {
     if (sa.n_active == 0) return RG_OK;
-    switch (sa.s.storage) {
-    case RG_STORE_FP32: return dispatch_dim<StepLaunch, RG_STORE_FP32>(sa.s.d, sa, stream);
-    case RG_STORE_BF16: return dispatch_dim<StepLaunch, RG_STORE_BF16>(sa.s.d, sa, stream);
-    case RG_STORE_FP8E4M3: return dispatch_dim<StepLaunch, RG_STORE_FP8E4M3>(sa.s.d, sa, stream);
-    default: set_error("serve: unknown storage"); return RG_EINVAL;
-    }
+    return with_storage(sa.s.storage, "serve", [&](auto ops) { return ops.serve_step(sa, stream); });
 }
 
 int serve_step_occupancy(const SlotArgs &a, int *blocks_per_cu) {
     SlotArgs b = a;
     b.s.occ_out = blocks_per_cu;
-    switch (a.s.storage) {
-    case RG_STORE_FP32: return dispatch_dim<StepOcc, RG_STORE_FP32>(a.s.d, b, nullptr);
-    case RG_STORE_BF16: return dispatch_dim<StepOcc, RG_STORE_BF16>(a.s.d, b, nullptr);
-    case RG_STORE_FP8E4M3: return dispatch_dim<StepOcc, RG_STORE_FP8E4M3>(a.s.d, b, nullptr);
-    default: set_error("serve: unknown storage"); return RG_EINVAL;
-    }
+    return with_storage(a.s.storage, "serve", [&](auto ops) { return ops.serve_occupancy(b); });
 }
 
 // ---------------------------------------------------------------------------
@@ -859,5 +958,7 @@ int launch_zero_words(uint32_t *p, int n, hipStream_t stream) {
     RG_HIP(hipGetLastError());
     return RG_OK;
 }
+
+#endif  // RG_BEAM_STORAGE
 
 }  // namespace rg

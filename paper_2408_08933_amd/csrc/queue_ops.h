@@ -1,6 +1,6 @@
 // Sorted-queue merge shared by the search kernels (FP32 keys) and the
 // construction-time canonical search (FP64 keys).  One wavefront owns the
-// queue; all arrays live in LDS.
+// queue; all arrays live in LDS, so wave_sync orders its steps.
 #pragma once
 
 #include <climits>
@@ -86,22 +86,22 @@ __device__ __forceinline__ void merge_batch(const QueueLds<K> &s, int cnt, int L
         if (total == 0) return;
         if (total <= kRankByCount) {
             // survivor order = number of survivors that precede it
-            __syncthreads();
+            wave_sync();
             if (sv) {
                 s.sd[lanes_below(m)] = kc;
                 s.si[lanes_below(m)] = ic;
             }
-            __syncthreads();
+            wave_sync();
             int rank = 0;
             if (sv)
                 for (int t = 0; t < total; ++t) rank += kless(s.sd[t], s.si[t], kc, ic) ? 1 : 0;
-            __syncthreads();
+            wave_sync();
             if (sv) {
                 s.sd[rank] = kc;
                 s.si[rank] = ic;
                 s.slb[rank] = lbc;
             }
-            __syncthreads();
+            wave_sync();
             sorted = true;
         }
     } else if (full) {  // nothing to do unless some candidate beats the last entry
@@ -141,7 +141,7 @@ __device__ __forceinline__ void merge_batch(const QueueLds<K> &s, int cnt, int L
         }
         total = __shfl(incl, 63);
         int w = incl - mine;
-        __syncthreads();
+        wave_sync();
 #pragma unroll
         for (int e = 0; e < E; ++e) {
             if (sv[e]) {
@@ -151,7 +151,7 @@ __device__ __forceinline__ void merge_batch(const QueueLds<K> &s, int cnt, int L
                 ++w;
             }
         }
-        __syncthreads();
+        wave_sync();
         if (total == 0) return;
     }
     const int lbmin = s.slb[0];
@@ -183,7 +183,7 @@ __device__ __forceinline__ void merge_batch(const QueueLds<K> &s, int cnt, int L
             pp[r] = s.slb[t] + t;
         }
     }
-    __syncthreads();
+    wave_sync();
 #pragma unroll
     for (int r = 0; r < R; ++r)
         if (mp[r] < Leff) {
@@ -198,7 +198,7 @@ __device__ __forceinline__ void merge_batch(const QueueLds<K> &s, int cnt, int L
         }
     qn = min(Leff, qn + total);
     ptr = min(ptr, lbmin);
-    __syncthreads();
+    wave_sync();
 }
 
 

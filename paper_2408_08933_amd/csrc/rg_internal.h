@@ -43,12 +43,14 @@ struct SearchArgs {
     float *out_d;               // nq x k
     uint32_t *out_hops;         // nq or null
     uint32_t *out_evals;        // nq or null
-    int64_t nq;
+    int64_t nq, n_rows;         // queries; nodes of the graph
     int32_t d, pitch, pitch8, ell;
     int32_t qpad;               // floats of the query kept in LDS (zero padded): every element a chunk reaches
     int32_t k, Leff;
     int32_t cand;               // candidate-batch capacity (64 or 128; cand_capacity)
-    int32_t hash_bits;
+    int32_t hash_bits;          // LDS visited table of 4 << hash_bits bytes
+    int32_t sets;               // nonzero: 2^(hash_bits - 1) sets of four 16-bit entries, else 2^hash_bits ids
+    int32_t id_bits;            // bits of the largest node id (sets)
     uint32_t entry;
     int32_t storage;            // RG_STORE_*
     // persistent variant: visited bitmaps (grid x bm_words) and the work counter
@@ -69,7 +71,7 @@ int noalloc_scratch(int device, uint32_t **out);
 int launch_zero_words(uint32_t *p, int n, hipStream_t stream);
 int launch_search_persistent(const SearchArgs &a, hipStream_t stream);
 int search_occupancy(const SearchArgs &a, int *blocks_per_cu);
-// workgroups of the LDS-table search (k_search) one CU holds with a.hash_bits
+// workgroups of the LDS-table search (k_search) one CU holds with a.hash_bits and a.sets
 int table_search_occupancy(const SearchArgs &a, int *blocks_per_cu);
 size_t search_lds_bytes(int Leff, int pitch, int hash_bits, int cand);
 int cand_capacity(int ell, bool csr);  // candidate-batch capacity for a graph layout
@@ -84,7 +86,8 @@ inline int32_t fp8_pitch(int32_t d) { return (fp8_row_bytes(d) + 127) & ~127; }
 inline int32_t query_pad(int32_t d, int32_t pitch, int32_t storage) {
     return storage == RG_STORE_FP8E4M3 ? std::max(pitch, fp8_row_bytes(d)) : pitch;
 }
-int default_hash_bits(int Leff);
+// the visited table of 4 << hash_bits bytes of LDS for this graph (api.cpp)
+void set_table(SearchArgs &a, int hash_bits);
 
 // Serving step: same per-query arithmetic as launch_search, resumable.
 struct SlotArgs {

@@ -133,7 +133,8 @@ bool rg_server::launch(StepBuf &b, int32_t n_adm_now, int32_t n_active) {
     sa.s.qpad = query_pad(d, ix->pitch, ix->storage);
     sa.s.ell = ix->ell;
     sa.s.cand = cand_capacity(ix->ell, ix->d_adj_off != nullptr);
-    sa.s.hash_bits = hash_bits;
+    sa.s.n_rows = ix->n;
+    set_table(sa.s, hash_bits);
     sa.s.entry = ix->entry;
     sa.s.storage = ix->storage;
     sa.active = b.d_active;
@@ -293,7 +294,10 @@ int rg_server_create(const rg_index *ix, const rg_server_limits *lim, rg_server 
         sa.s.d = ix->d;
         sa.s.qpad = query_pad(ix->d, ix->pitch, ix->storage);
         sa.s.cand = cand_capacity(ix->ell, ix->d_adj_off != nullptr);
-        sa.s.hash_bits = l.hash_bits;
+        sa.s.ell = ix->ell;
+        sa.s.adj_off = ix->d_adj_off;
+        sa.s.n_rows = ix->n;
+        set_table(sa.s, l.hash_bits);
         sa.s.storage = ix->storage;
         int per_cu = 0, cus = 0;
         (void)hipSetDevice(ix->device);

@@ -12,6 +12,15 @@ __device__ __forceinline__ int lane_id() { return threadIdx.x & 63; }
 
 __device__ __forceinline__ uint64_t ballot64(bool p) { return __ballot(p); }
 
+// Orders a wavefront's LDS accesses across its lanes.  The LDS serves one
+// wavefront's operations in order, so this only keeps the compiler from
+// moving them; a workgroup barrier, even where a workgroup is one wavefront,
+// also waits for every outstanding load and store.
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
 // number of set bits of m below this lane
 __device__ __forceinline__ int lanes_below(uint64_t m) {
     return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0));

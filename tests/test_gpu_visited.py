@@ -1,0 +1,71 @@
+"""The forgetting visited tables of the search against the exact bitmap, on the GPU: the results never depend on
+what a table remembers."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+rg = pytest.importorskip("paper_2408_08933_amd")
+
+
+@pytest.fixture(scope="module")
+def dev():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    rg.lib()
+    return torch.device("cuda:0")
+
+
+def exact(ix, Q, k, L):
+    nq = Q.shape[0]
+    ids = torch.empty((nq, k), dtype=torch.int32, device=Q.device)
+    ds = torch.empty((nq, k), device=Q.device)
+    ev = torch.empty(nq, dtype=torch.int32, device=Q.device)
+    hops = torch.empty(nq, dtype=torch.int32, device=Q.device)
+    rg.rg_search_noalloc_into(ix, Q, k, L, ids, ds, hops, ev)
+    return ids, ds, hops, ev
+
+
+def graph(n, deg, seed, special=None):
+    """Rows of deg random ids, some of them twice in a row, the first rows holding the special ids twice each."""
+    rng = np.random.default_rng(seed)
+    nb = rng.integers(0, n, size=(n, deg), dtype=np.int64)
+    nb[:, 0] = (np.arange(n) + 1) % n
+    nb[::3, deg // 2] = nb[::3, 1]          # a copy far from its first place
+    nb[::5, 2] = nb[::5, 1]                 # and next to it
+    if special is not None:
+        s = np.resize(special, (64, deg // 2))
+        nb[:64, :deg // 2] = s
+        nb[:64, deg // 2:deg // 2 * 2] = s
+    return np.arange(n + 1, dtype=np.int64) * deg, nb.astype(np.uint32).reshape(-1)
+
+
+# n: 16-bit entries with room to spare, entries of exactly 16 bits at 2^8
+# (where one entry per set is the mark of a free place), and more than 16 bits
+# at 2^8 (a table of ids); deg: a full 64-id turn, and rows of several turns
+@pytest.mark.parametrize("n,deg", [(3000, 16), (3000, 64), (3000, 90), ((1 << 22) + 77, 16), ((1 << 23) + 5, 8)])
+@pytest.mark.parametrize("storage", ["fp32", "fp8"])
+def test_tables_return_the_exact_results(dev, n, deg, storage):
+    print(f"visited tables n={n} deg={deg} {storage}", flush=True)
+    g = torch.Generator().manual_seed(n + deg)
+    X = torch.randn(n, 8, generator=g)
+    bits = max(1, (n - 1).bit_length())
+    u = np.arange(n, dtype=np.uint64)
+    h = (u * np.uint64(2654435761)) & np.uint64((1 << bits) - 1)
+    marked = u[(h & np.uint64(0xFFFF)) == np.uint64(0xFFFF)]
+    off, idx = graph(n, deg, n + deg, marked if len(marked) else None)
+    Q = torch.randn(40, 8, generator=g).to(dev)
+    ix = rg.rg_index_from_csr(X.to(dev), off, idx, 3)
+    if storage == "fp8":
+        rg.rg_index_set_storage(ix, rg.RG_STORE_FP8E4M3)
+    for k, L in ((10, 20), (50, 200)):
+        ids, ds, hops, ev = exact(ix, Q, k, L)
+        for hb in (8, 9, 11, None):
+            if hb == 8 and deg > 64:
+                continue
+            a = rg.rg_search(ix, Q, k, L, stats=True, hash_bits=hb)
+            torch.cuda.synchronize()
+            assert torch.equal(a[0], ids) and torch.equal(a[1], ds) and torch.equal(a[2], hops), (k, L, hb)
+            assert (a[3] >= ev).all()
+        assert all(len(set(r.tolist())) == k for r in ids)   # no node twice
