@@ -254,7 +254,9 @@ int rg_index_set_storage(rg_index *idx, int32_t storage, void *stream);
  * a neighbour enters the queue if the queue is not full or it beats the last
  * entry.  With reduced-precision storage the final L_eff queue is rescored
  * against the FP32 rows and the best k are returned.  FP32 storage keeps an
- * exact visited bitmap per resident query in device memory while n/8 bytes
+ * exact visited set per query (a bitmap in device memory or, for small bases,
+ * in LDS; for few queries a table in LDS that overflows into one) while n/8
+ * bytes
  * stay below 5% of a query's expected row bytes (40 L_eff rows of 4d
  * bytes) or the graph is held as CSR (rows over 128 ids);
  * otherwise, and for BF16 / FP8, a visited table in LDS that forgets and

@@ -12,7 +12,7 @@ LIB = os.path.join(HERE, "libroargraph.so")
 SOURCES = ["beam.hip", "knn.hip", "quant.hip", "canon.hip", "peaks.hip", "api.cpp", "host_build.cpp", "serve.cpp"]
 # sources compiled in parts, with these flags (see beam.hip)
 VARIANTS = {"beam.hip": [[]] + [[f"-DRG_BEAM_STORAGE={st}", f"-DRG_BEAM_PART={part}"] for st in (0, 1, 2)
-                                for part in (0, 1, 2)]}
+                                for part in (0, 1, 2, 3)]}
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 COMMON = [

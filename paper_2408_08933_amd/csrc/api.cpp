@@ -986,33 +986,74 @@ int rg_search(const rg_index *ix, const float *queries, int64_t nq, int32_t k, i
     SearchArgs a = search_args(ix, queries, nq, k, L, ids, dists, hops, evals);
     int cus = 0;
     RG_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, ix->device));
-    if (ix->storage != RG_STORE_FP32) {
+    // FP32 rows keep an exact visited bitmap (about n/8 bytes per query: the
+    // clear, then the lines its atomics dirty) while that stays below 5% of a
+    // query's expected row bytes (about 40 L_eff rows of 4d bytes, as measured
+    // on built indexes: the graph's mean degree says little, the expanded
+    // nodes being its dense part), and always for CSR graphs, whose wide rows
+    // would overflow a table at every expansion.  Measured: the bitmap is
+    // faster at 1M x 200 (L = 183) and 8M x 512 (L = 500), the table at 10M x
+    // 200 (L = 439, by 28%).
+    const bool exact = ix->storage == RG_STORE_FP32 &&
+                       (ix->d_adj_off || (double)ix->n / 8.0 <= 0.05 * 40.0 * std::max(L, k) * 4.0 * ix->d);
+    a.bm_words = ((ix->n + 31) / 32 + 63) / 64 * 64;
+    int rc = RG_OK;
+    // Few queries: 8 wavefronts per query while that is one workgroup per CU
+    // (two wavefronts per SIMD with this kernel's registers), 4 up to two
+    // workgroups, 2 up to four where the visited set is small.  Beyond, and
+    // at two wavefronts with queues over 512 entries or an exact set (which
+    // would overflow in the LDS left for it), one wavefront per query is
+    // faster.  Measured, us, one wavefront / several: FP32 300k x 200 L = 100
+    // 1 query 808 / 530, 256 1,330 / 950, 512 1,390 / 1,140, (768 1,470 /
+    // 1,520); BF16 200k x 512 L = 200 1 query 1,840 / 1,280, 512 2,660 / 2,060,
+    // 1,024 3,150 / 2,770; E4M3 500k x 512 L = 409 1,024 queries 9,000 / 6,200;
+    // BF16 500k x 200 L = 805 512 queries 7,600 / 7,200, (768 7,540 / 9,330).
+    set_table(a, 10);
+    const int64_t most = (exact || a.Leff > kMaxL ? 2 : 4) * (int64_t)cus;
+    if (!a.adj_off && a.ell <= 64 && (exact || a.sets) && nq <= most) {
+        a.grid = nq <= cus ? 8 : nq <= 2 * (int64_t)cus ? 4 : 2;
+        a.prep = 2;
+        void *ws = nullptr;
+        if (exact) {
+            // room for twice the expected nodes, as LDS allows
+            a.sets = 0;
+            a.hash_bits = 11;
+            while (a.hash_bits < (a.grid == 8 ? 15 : 14) && (1 << a.hash_bits) < 80 * a.Leff) ++a.hash_bits;
+            if (ix->n + 64 * (kMaxWide + 1) > (3ll << a.hash_bits) / 4) {
+                if (hipMallocAsync(&ws, (size_t)nq * a.bm_words * 4, st) != hipSuccess) {
+                    set_error("rg_search: out of device memory for visited bitmaps");
+                    return RG_ENOMEM;
+                }
+                a.bitmap = static_cast<uint32_t *>(ws);
+            }
+        }
+        rc = launch_search_wide(a, st);
+        if (ws && hipFreeAsync(ws, st) != hipSuccess && !rc) {
+            set_error("rg_search: device call failed");
+            rc = RG_EDEVICE;
+        }
+        return rc;
+    }
+    if (!exact) {
         // BF16 / FP8 rows: the search waits on memory latency, not bandwidth;
         // a small LDS visited table (no device atomics) is faster even though
         // it forgets and rescores some rows (same results)
-        const int rc = choose_table(a, cus);
+        rc = choose_table(a, cus);
         return rc ? rc : launch_search(a, st);
     }
-    // FP32 rows, bandwidth bound.  The persistent kernel's exact visited
-    // bitmap costs about n/8 bytes per query (the clear, then the lines its
-    // atomics dirty); the LDS table costs the rows it forgets and rescores.
-    // Measured: the bitmap is faster at 1M x 200 (L = 183) and 8M x 512
-    // (L = 500), the table at 10M x 200 (L = 439, by 28%).  The bitmap is
-    // used while n/8 stays below 5% of a query's expected row bytes (about
-    // 40 L_eff rows of 4d bytes, as measured on these indexes: the graph's
-    // mean degree says little, the expanded nodes being its dense part), and
-    // always for CSR graphs, whose wide rows would overflow the table at
-    // every expansion.
-    if (!ix->d_adj_off && (double)ix->n / 8.0 > 0.05 * 40.0 * std::max(L, k) * 4.0 * ix->d) {
-        const int rc = choose_table(a, cus);
-        return rc ? rc : launch_search(a, st);
+    if (!a.adj_off && ix->n <= 32 << 10) {
+        // a small base: its bitmap fits in 4 KB of LDS, without the atomics'
+        // way to device memory and back at every expansion (10k x 64, 1,000
+        // queries, L = 50: 431 -> 360 us)
+        a.hash_bits = 6;
+        while ((32ll << a.hash_bits) < ix->n) ++a.hash_bits;
+        return launch_search_bits(a, st);
     }
     // persistent grid: as many resident workgroups as the chip holds, each
     // with its own visited bitmap (bounded to 8 GiB in total)
     int per_cu = 0;
-    int rc = search_occupancy(a, &per_cu);
+    rc = search_occupancy(a, &per_cu);
     if (rc) return rc;
-    a.bm_words = ((ix->n + 31) / 32 + 63) / 64 * 64;
     int64_t grid = (int64_t)std::max(1, per_cu) * std::max(1, cus);
     grid = std::min<int64_t>(grid, nq);
     grid = std::min<int64_t>(grid, std::max<int64_t>(1, (8ll << 30) / (a.bm_words * 4)));

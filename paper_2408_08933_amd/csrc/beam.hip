@@ -35,8 +35,9 @@
 
 // The build compiles this file in parts, side by side: per storage form
 // (RG_BEAM_STORAGE = RG_STORE_*) the search with a visited table of ids
-// (RG_BEAM_PART 0) or of 16-bit entries (1) and the other kernels (2), and
-// once without them the dispatch and the rest.
+// (RG_BEAM_PART 0) or of 16-bit entries (1), the persistent search and the
+// serving step (2) and the search of few queries (3), and once without them
+// the dispatch and the rest.
 namespace rg {
 
 // the launches of one storage form
@@ -44,8 +45,10 @@ template <int ST>
 struct BeamOps {
     static int search_ids(const SearchArgs &a, hipStream_t s);   // visited table of ids
     static int search_sets(const SearchArgs &a, hipStream_t s);  // visited table of 16-bit entries
+    static int search_bits(const SearchArgs &a, hipStream_t s);  // one bit per node (FP32 rows)
     static int ids_occupancy(const SearchArgs &a);
     static int sets_occupancy(const SearchArgs &a);
+    static int wide(const SearchArgs &a, hipStream_t s);         // several wavefronts per query
     static int persistent(const SearchArgs &a, hipStream_t s);
     static int persistent_occupancy(const SearchArgs &a);
     static int serve_step(const SlotArgs &a, hipStream_t s);
@@ -341,6 +344,16 @@ struct VisitSets {
     __device__ __forceinline__ void added(int) {}
     __device__ __forceinline__ int count() const { return 0; }
     __device__ __forceinline__ void restore(int) {}
+    // whether one of a set's four entries is rest (twice = rest * 0x10001): a
+    // 16-bit half of the difference is zero
+    static __device__ __forceinline__ bool among(unsigned long long set, uint32_t twice) {
+        const uint32_t a = (uint32_t)set ^ twice, b = (uint32_t)(set >> 32) ^ twice;
+        return ((((a - 0x10001u) & ~a) | ((b - 0x10001u) & ~b)) & 0x80008000u) != 0u;
+    }
+    __device__ __forceinline__ bool holds(uint32_t u) const {
+        const uint32_t h = (u * 2654435761u) & idmask, rest = h & ((1u << rest_bits) - 1u);
+        return rest != 0xFFFFu && among(tab[h >> rest_bits], rest * 0x10001u);
+    }
     __device__ __forceinline__ bool insert(uint32_t u) {
         const uint32_t h = (u * 2654435761u) & idmask;
         const uint32_t rest = h & ((1u << rest_bits) - 1u), twice = rest * 0x10001u;
@@ -355,14 +368,30 @@ struct VisitSets {
         if (rest == 0xFFFFu) return fresh;
         unsigned long long old = *p;
         for (;;) {
-            // a 16-bit half of a word is zero iff the node is there
-            const uint32_t a = (uint32_t)old ^ twice, b = (uint32_t)(old >> 32) ^ twice;
-            if ((((a - 0x10001u) & ~a) | ((b - 0x10001u) & ~b)) & 0x80008000u) return false;
+            if (among(old, twice)) return false;
             const unsigned long long got = atomicCAS(p, old, (old << 16) | rest);
             if (got == old) return true;
             old = got;
         }
     }
+};
+
+// Exact visited set of a small base: one bit per node in LDS, 32 per
+// word of the table.
+struct VisitBits {
+    uint32_t *bits;
+    int words;
+    __device__ __forceinline__ VisitBits(uint32_t *t, int hash_bits, int) : bits(t), words(1 << hash_bits) {}
+    __device__ __forceinline__ void clear() {
+        for (int i = lane_id(); i < words; i += 64) bits[i] = 0u;
+    }
+    __device__ __forceinline__ void mark_entry(uint32_t u) { (void)insert(u); }
+    __device__ __forceinline__ void begin_hop(int) {}
+    __device__ __forceinline__ bool insert(uint32_t u) {
+        const uint32_t bit = 1u << (u & 31u);
+        return (atomicOr(&bits[u >> 5], bit) & bit) == 0u;
+    }
+    __device__ __forceinline__ void added(int) {}
 };
 
 // Exact visited set: one bit per base node in device memory, owned by the
@@ -685,6 +714,457 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5))) void k_
     }
 }
 
+// ---------------------------------------------------------------------------
+// Few queries: several wavefronts per query.
+//
+// With fewer queries than the chip holds wavefronts an expansion is a chain
+// of waits (the adjacency row, the visited set, two or three rounds of rows,
+// the merge: 7 us on FP32 d = 200, 13 us on BF16 d = 512), and the rest of
+// the chip idles.  Here a workgroup runs one query, in rounds of three parts:
+//   * prepare, all wavefronts, P to each of the first W unexpanded queue
+//     entries that are not prepared yet: read the adjacency row and score the
+//     neighbours that are not visited;
+//   * commit, wavefront 0: while the first unexpanded entry is a prepared one,
+//     mark it expanded and merge what was scored.  It stops at an entry that
+//     is not prepared (a merge brought a closer one); what was prepared stays
+//     until it is committed or its place is needed;
+//   * visit, the last wavefront, while the others wait for their adjacency
+//     rows: mark the committed entries' neighbours visited, in commit order,
+//     and count the new ones.
+// The results are the sequential search's: distances do not depend on when
+// they are computed, expansions are committed in its order, and a node that
+// is scored although a commit in between has visited it is dropped at the
+// merge (it is queued, or it was rejected or evicted against a last key that
+// has only decreased since).  Rows prepared and never committed are extra
+// work; the counts are those of the visits, which happen as they would in
+// sequence.
+//
+// The visited set is VisitSets, or VisitSpill: exact, node ids in a large LDS
+// table that is written out to the query's bitmap in device memory when it is
+// three quarters full.  What has been prepared is then dropped, so that every
+// later preparation sees all that was written out.
+// ---------------------------------------------------------------------------
+struct VisitSpill {
+    static constexpr bool kExact [[maybe_unused]] = true;
+    uint32_t *htab, *bm;
+    int hb;
+    __device__ __forceinline__ VisitSpill(uint32_t *t, const SearchArgs &a, int64_t q)
+        : htab(t), bm(a.bitmap ? a.bitmap + q * a.bm_words : nullptr), hb(a.hash_bits) {}
+    __device__ __forceinline__ bool seen(uint32_t u, bool spilled) const {
+        const uint32_t hmask = (1u << hb) - 1u;
+        for (uint32_t h = hslot(u, hb);; h = (h + 1u) & hmask) {  // a quarter of the table is free
+            const uint32_t x = htab[h];
+            if (x == u) return true;
+            if (x == kEmpty) break;
+        }
+        return spilled && ((__hip_atomic_load(&bm[u >> 5], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >> (u & 31u)) & 1u);
+    }
+    __device__ __forceinline__ bool insert(uint32_t u) {
+        const uint32_t hmask = (1u << hb) - 1u;
+        for (uint32_t h = hslot(u, hb);; h = (h + 1u) & hmask) {
+            const uint32_t old = atomicCAS(&htab[h], kEmpty, u);
+            if (old == kEmpty) return true;
+            if (old == u) return false;
+        }
+    }
+    // whether count ids and one row more may fill the table too far
+    __device__ __forceinline__ bool full(int count) const { return count + 64 > (3 << hb) / 4; }
+    // all threads; the table's ids move to the bitmap (cleared the first time)
+    __device__ __forceinline__ void spill(int64_t words, bool first) {
+        if (first) {
+            uint4 *b4 = reinterpret_cast<uint4 *>(bm);
+            for (int64_t i = threadIdx.x; i < (words >> 2); i += blockDim.x) b4[i] = make_uint4(0u, 0u, 0u, 0u);
+            __threadfence();
+            __syncthreads();
+        }
+        for (int i = threadIdx.x; i < (1 << hb); i += blockDim.x) {
+            const uint32_t u = htab[i];
+            if (u != kEmpty) atomicOr(&bm[u >> 5], 1u << (u & 31u));
+            htab[i] = kEmpty;
+        }
+        __threadfence();
+    }
+};
+
+struct VisitSetsWide : VisitSets {
+    static constexpr bool kExact [[maybe_unused]] = false;
+    __device__ __forceinline__ VisitSetsWide(uint32_t *t, const SearchArgs &a, int64_t)
+        : VisitSets(t, a.hash_bits, a.id_bits) {}
+    __device__ __forceinline__ bool seen(uint32_t u, bool) const { return holds(u); }
+    __device__ __forceinline__ bool full(int) const { return false; }
+    __device__ __forceinline__ void spill(int64_t, bool) {}
+};
+
+// Merge one candidate per lane (cand: it takes part) into the sorted queue of
+// up to 64 * QR entries: the result of merge_batch, in fewer dependent steps
+// (one wavefront has its SIMD to itself here and each LDS round trip and each
+// ballot counts).  The entries that move count the candidates ahead of them in
+// registers.  A candidate's place comes from counting the entries ahead of it
+// where they are two per lane (3.2k cycles a merge at L = 100 against 4.4k
+// with the search), else from a 4-ary search (6.2k against 7.1k at L = 200,
+// 8.5k against 17k at L = 805).  A candidate that is queued, or that stands
+// earlier in the batch, is dropped.
+template <int QR>
+__device__ __forceinline__ void merge_lanes(float *qd, uint32_t *qi, int Leff, int &qn, int &ptr, float kc, uint32_t ic,
+                                            bool cand) {
+    constexpr bool kCount = QR <= 2;
+    const int lane = lane_id();
+    bool sv = cand;
+    if (qn == Leff) sv = cand && kless(kc, ic, qd[Leff - 1], qi[Leff - 1] & ~kExpanded);
+    uint64_t all = ballot64(sv);
+    if (all == 0) return;
+    int sh[QR];  // candidates ahead of entry 64 r + lane
+    float k[QR];
+    uint32_t v[QR];
+#pragma unroll
+    for (int r = 0; r < QR; ++r) sh[r] = 0;
+    int lb = 0;  // queue entries ahead of this candidate
+    if constexpr (kCount) {
+#pragma unroll
+        for (int r = 0; r < QR; ++r) {
+            const int i = r * 64 + lane;
+            k[r] = __builtin_inff();
+            v[r] = kNone;
+            if (i < qn) {
+                k[r] = qd[i];
+                v[r] = qi[i];
+            }
+        }
+    } else {
+        if (sv) {
+            // at most 1,023: a full queue of 1,024 has an entry behind every survivor
+            for (int st = qn >= 256 ? 256 : qn >= 64 ? 64 : qn >= 16 ? 16 : qn >= 4 ? 4 : 1; st > 0; st >>= 2) {
+                int c = 0;
+#pragma unroll
+                for (int j = 1; j <= 3; ++j) {
+                    const int i = lb + j * st - 1;
+                    if (i < qn) c += kless(qd[i], qi[i] & ~kExpanded, kc, ic) ? 1 : 0;
+                }
+                lb += c * st;
+            }
+            if (lb < qn && (qi[lb] & ~kExpanded) == ic) sv = false;  // queued already
+        }
+        all = ballot64(sv);
+        if (all == 0) return;
+    }
+    int ahead = 0, total = 0, lbmin = INT_MAX;
+    for (uint64_t m = all; m; m &= m - 1) {
+        const int src = (int)__builtin_ctzll(m);
+        const float ks = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(kc), src));
+        const uint32_t is = (uint32_t)__builtin_amdgcn_readlane((int)ic, src);
+        uint64_t drop = ballot64(sv && ic == is && lane < src);
+        int ls = 0;
+        if constexpr (kCount) {
+            bool less[QR];
+#pragma unroll
+            for (int r = 0; r < QR; ++r) {
+                const uint32_t id = v[r] & ~kExpanded;
+                less[r] = kless(k[r], id, ks, is);
+                ls += (int)__popcll(ballot64(less[r]));
+                drop |= ballot64(id == is);
+            }
+            if (drop) {
+                if (lane == src) sv = false;
+                continue;
+            }
+#pragma unroll
+            for (int r = 0; r < QR; ++r) sh[r] += less[r] ? 0 : 1;
+            if (lane == src) lb = ls;
+        } else {
+            if (drop) {
+                if (lane == src) sv = false;
+                continue;
+            }
+            ls = __builtin_amdgcn_readlane(lb, src);
+#pragma unroll
+            for (int r = 0; r < QR; ++r) sh[r] += r * 64 + lane >= ls ? 1 : 0;
+        }
+        ahead += kless(ks, is, kc, ic) ? 1 : 0;
+        lbmin = min(lbmin, ls);
+        ++total;
+    }
+    if (total == 0) return;
+    if constexpr (!kCount) {
+#pragma unroll
+        for (int r = 0; r < QR; ++r)
+            if (r * 64 + 63 >= lbmin && r * 64 + lane < qn) {
+                k[r] = qd[r * 64 + lane];
+                v[r] = qi[r * 64 + lane];
+            }
+    }
+    wave_sync();
+#pragma unroll
+    for (int r = 0; r < QR; ++r)
+        if (r * 64 + 63 >= lbmin) {
+            const int i = r * 64 + lane, p = i + sh[r];
+            if (i < qn && sh[r] > 0 && p < Leff) {
+                qd[p] = k[r];
+                qi[p] = v[r];
+            }
+        }
+    if (sv && lb + ahead < Leff) {
+        qd[lb + ahead] = kc;
+        qi[lb + ahead] = ic;
+    }
+    qn = min(Leff, qn + total);
+    ptr = min(ptr, lbmin);
+    wave_sync();
+}
+
+constexpr int kWide = kMaxWide;  // most wavefronts per query
+enum { kRun = 0, kDone = 1, kSpill = 2 };
+struct alignas(16) WideLds {
+    uint32_t id[kWide][64];  // a preparation: the adjacency row,
+    float cd[kWide][64];     // the distances of what was scored, in row order,
+    uint64_t mask[kWide];    // and which of the row that is
+    uint32_t ci[kWide][64];
+    uint32_t node[kWide], next[kWide], tgt[kWide];
+    int done[kWide];         // preparations committed in the last round, in order
+    int n_done, state, qn, count;
+    uint32_t hops, evals;
+    int pad[2];
+};
+// rows in flight per group: 32 chunks per lane, 4 to 8 rows
+constexpr int wide_r(int nch) { return nch >= 8 ? 4 : nch * 8 <= 32 ? 8 : 32 / nch; }
+
+template <int ST, int CLS, int QR, class VIS>
+__global__ __launch_bounds__(64 * kWide) __attribute__((amdgpu_waves_per_eu(2))) void k_search_wide(SearchArgs a) {
+    constexpr int G = shape_g(ST, CLS), NCH = shape_nch(ST, CLS), R = wide_r(NCH);
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int tid = threadIdx.x, nthr = blockDim.x, w = tid >> 6, lane = lane_id();
+    // P wavefronts per preparation, W preparations at a time
+    const int P = a.prep, W = (nthr >> 6) / P, slot_w = w / P, part = w % P;
+    const int64_t q = blockIdx.x;
+    const int Leff = a.Leff, nch = row_chunk_count<ST>(a.d);
+    WideLds &s = *reinterpret_cast<WideLds *>(smem);
+    float *qs = reinterpret_cast<float *>(smem + sizeof(WideLds));
+    float *qd = qs + a.qpad;
+    uint32_t *qi = reinterpret_cast<uint32_t *>(qd + Leff);
+    uint32_t *htab = qi + Leff;
+    VIS vis(htab, a, q);
+
+    for (int i = tid; i < a.qpad; i += nthr) qs[i] = i < a.d ? a.queries[q * a.d + i] : 0.f;
+    for (int i = tid; i < (1 << a.hash_bits); i += nthr) htab[i] = kEmpty;
+    // no queue place ever holds anything but a node
+    for (int i = tid; i < Leff; i += nthr) {
+        qd[i] = __builtin_inff();
+        qi[i] = a.entry | kExpanded;
+    }
+    if (tid < kWide) s.node[tid] = kNone;
+    if (tid == 0) {
+        s.n_done = 0;
+        s.count = 1;
+    }
+    __syncthreads();
+
+    // state of wavefront 0
+    int qn = 1, ptr = 0;
+    uint32_t hops = 0;
+    // of the last wavefront
+    const bool last = w == (nthr >> 6) - 1;
+    int count = 1;
+    uint32_t evals = 1;
+    bool spilled = false;
+    // the first W unexpanded entries that are not prepared, one to each
+    // preparation that is not among them (wavefront 0)
+    auto plan = [&]() {
+        int nt = 0;
+        for (int b = ptr; b < qn && nt < W; b += 64) {
+            const int i = b + lane;
+            const uint32_t x = i < qn ? qi[i] : kExpanded;
+            const bool un = !(x & kExpanded);
+            const uint64_t m = ballot64(un);
+            const int k = nt + lanes_below(m);
+            if (un && k < W) s.tgt[k] = x;
+            nt += (int)__popcll(m);
+        }
+        nt = min(nt, W);
+        wave_sync();
+        const uint32_t tv = lane < nt ? s.tgt[lane] : kNone, sv = lane < W ? s.node[lane] : kNone;
+        bool have = false, keep = false;
+        for (int i = 0; i < W; ++i) {
+            const uint32_t si = (uint32_t)__builtin_amdgcn_readlane((int)sv, i);
+            const uint32_t ti = (uint32_t)__builtin_amdgcn_readlane((int)tv, i);
+            have |= tv == si;
+            keep |= sv == ti && ti != kNone;
+        }
+        const uint64_t need = ballot64(lane < nt && !have), fre = ballot64(lane < W && !keep);
+        wave_sync();
+        if ((need >> lane) & 1u) s.tgt[lanes_below(need)] = tv;
+        wave_sync();
+        if (lane < W) {
+            const int r = lanes_below(fre);
+            s.next[lane] = ((fre >> lane) & 1u) && r < (int)__popcll(need) ? s.tgt[r] : kNone;
+        }
+        if (lane == 0) s.state = kRun;
+    };
+
+    if (w == 0) {
+        const uint32_t u[1] = {lane < G ? a.entry : kNone};
+        float acc[1], sc[1];
+        dot_rows<ST, G, NCH, 1>(a, u, qs, nch, acc, sc);
+        acc[0] = group_sum<G>(acc[0]);
+        if constexpr (ST == RG_STORE_FP8E4M3) sc[0] = group_sum<G>(sc[0]);
+        if (lane == 0) {
+            qd[0] = finish_delta<ST>(acc[0], sc[0]);
+            qi[0] = a.entry;
+            (void)vis.insert(a.entry);
+        }
+        wave_sync();
+        plan();
+    }
+    for (;;) {
+        __syncthreads();
+        const int state = s.state;
+        const uint32_t mine = state == kRun ? s.next[slot_w] : kNone;
+        uint32_t u = kNone;
+        if (mine != kNone && lane < a.ell) u = a.adj[(int64_t)mine * a.ell + lane];
+        if (last) {
+            const int nd = s.n_done;
+            for (int i = 0; i < nd; ++i) {
+                const int c = s.done[i];
+                const uint32_t x = s.id[c][lane];
+                // exact: what was not scored is visited; sets: it may be forgotten
+                bool fresh = false;
+                if (x != kNone && (!VIS::kExact || ((s.mask[c] >> lane) & 1u))) fresh = vis.insert(x);
+                const int nf = (int)__popcll(ballot64(fresh));
+                evals += (uint32_t)nf;
+                count += nf;
+            }
+            if (lane == 0) {
+                s.count = count;
+                s.evals = evals;
+            }
+        }
+        __syncthreads();
+        if (state == kDone) break;
+        if (state == kSpill) {
+            vis.spill(a.bm_words, !spilled);
+            spilled = true;
+            count = 0;
+            if (tid < kWide) s.node[tid] = kNone;
+            __syncthreads();
+            if (w == 0) {
+                if (lane == 0) {
+                    s.n_done = 0;
+                    s.count = 0;
+                }
+                plan();
+            }
+            continue;
+        }
+        if (mine != kNone) {
+            const bool fresh = u != kNone && !vis.seen(u, spilled);
+            const uint64_t m = ballot64(fresh);
+            const int cnt = (int)__popcll(m), r0 = cnt * part / P, r1 = cnt * (part + 1) / P;
+            if (fresh) s.ci[w][lanes_below(m)] = u;
+            wave_sync();
+            score_batch<ST, G, NCH, R>(a, qs, nch, s.ci[w] + r0, 0xFFFFFFFFu, s.cd[slot_w] + r0, r1 - r0);
+            if (part == 0) {
+                s.id[slot_w][lane] = u;
+                if (lane == 0) {
+                    s.mask[slot_w] = m;
+                    s.node[slot_w] = mine;
+                }
+            }
+        }
+        __syncthreads();
+        if (w != 0) continue;
+        // at most W commits (each uses a preparation up), so done[] holds them
+        int nd = 0, seen = s.count;
+        for (;;) {
+            int sel = -1;
+            for (int b = ptr; b < qn; b += 64) {
+                const int i = b + lane;
+                const uint64_t m = ballot64(i < qn && !(qi[i] & kExpanded));
+                if (m) {
+                    sel = b + (int)__builtin_ctzll(m);
+                    break;
+                }
+            }
+            if (sel < 0) {
+                if (lane == 0) {
+                    s.state = kDone;
+                    s.qn = qn;
+                    s.hops = hops;
+                }
+                break;
+            }
+            ptr = sel;
+            const uint32_t v = qi[sel];
+            const uint64_t at = ballot64(lane < W && s.node[lane & (kWide - 1)] == v);
+            if (at == 0) {
+                plan();
+                break;
+            }
+            if (vis.full(seen)) {
+                if (lane == 0) s.state = kSpill;
+                break;
+            }
+            const int slot = (int)__builtin_ctzll(at);
+            const uint64_t m = s.mask[slot];
+            const uint32_t x = s.id[slot][lane];
+            const bool scored = (m >> lane) & 1u;
+            const float kc = scored ? s.cd[slot][lanes_below(m)] : __builtin_inff();
+            wave_sync();
+            if (lane == 0) {
+                qi[sel] = v | kExpanded;
+                s.node[slot] = kNone;
+                s.done[nd] = slot;
+            }
+            wave_sync();
+            ++nd;
+            ++hops;
+            seen += (int)__popcll(m);
+            merge_lanes<QR>(qd, qi, Leff, qn, ptr, kc, x, scored);
+        }
+        if (lane == 0) s.n_done = nd;
+    }
+    const int n = s.qn;
+    if constexpr (ST != RG_STORE_FP32) {
+        // the final queue by its FP32 distances: every wavefront rescores a
+        // part, then every entry's place is the number of entries before it
+        constexpr int G32 = shape_g(RG_STORE_FP32, CLS), N32 = shape_nch(RG_STORE_FP32, CLS);
+        const int nw = nthr >> 6, per = (n + nw - 1) / nw, r0 = min(n, w * per), r1 = min(n, r0 + per);
+        score_batch<RG_STORE_FP32, G32, N32, 4>(a, qs, (a.d + 3) >> 2, qi + r0, ~kExpanded, qd + r0, r1 - r0);
+        __syncthreads();
+        constexpr int E = QR / 2;  // entries per thread, two wavefronts at least
+        float k[E];
+        uint32_t id[E];
+        int rank[E];
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            const int i = e * nthr + tid;
+            k[e] = i < n ? qd[i] : 0.f;
+            id[e] = i < n ? qi[i] & ~kExpanded : 0u;
+            rank[e] = 0;
+        }
+        for (int j = 0; j < n; ++j) {
+            const float kj = qd[j];
+            const uint32_t ij = qi[j] & ~kExpanded;
+#pragma unroll
+            for (int e = 0; e < E; ++e)
+                if (e * nthr < n) rank[e] += kless(kj, ij, k[e], id[e]) ? 1 : 0;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            const int i = e * nthr + tid;
+            if (i < n) {
+                qd[rank[e]] = k[e];
+                qi[rank[e]] = id[e];
+            }
+        }
+        __syncthreads();
+    }
+    if (w == 0) {
+        Lds out{};
+        out.qd = qd;
+        out.qi = qi;
+        write_result(a, out, q, n, s.hops, s.evals);
+    }
+}
+
 // The kernels for a queue of L_eff entries: kMaxL or fewer, or up to kMaxSearchL.
 template <int ST, int CLS, class VIS>
 void (*table_kernel(int Leff))(SearchArgs) {
@@ -727,6 +1207,30 @@ template <int ST, int CLS>
 void (*step_kernel(const SearchArgs &a))(SlotArgs) {
     return a.sets ? k_serve_step<ST, CLS, VisitSets> : k_serve_step<ST, CLS, VisitLds>;
 }
+
+template <int ST, int CLS, int QR>
+void (*wide_kernel(bool sets))(SearchArgs) {
+    if constexpr (ST == RG_STORE_FP32) {
+        if (!sets) return k_search_wide<ST, CLS, QR, VisitSpill>;
+    }
+    return k_search_wide<ST, CLS, QR, VisitSetsWide>;
+}
+
+template <int ST, int CLS>
+struct WideLaunch {
+    static int run(const SearchArgs &a, hipStream_t stream) {
+        const size_t lds = sizeof(WideLds) + (size_t)a.qpad * 4 + (size_t)a.Leff * 8 + ((size_t)4 << a.hash_bits);
+        auto k = a.Leff <= 128     ? wide_kernel<ST, CLS, 2>(a.sets)
+                 : a.Leff <= kMaxL ? wide_kernel<ST, CLS, kMaxL / 64>(a.sets)
+                                   : wide_kernel<ST, CLS, kMaxSearchL / 64>(a.sets);
+        if (lds > (64u << 10))
+            RG_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                       (int)lds));
+        hipLaunchKernelGGL(k, dim3((unsigned)a.nq), dim3(64 * (unsigned)a.grid), lds, stream, a);
+        RG_HIP(hipGetLastError());
+        return RG_OK;
+    }
+};
 
 template <int ST, int CLS>
 int launch_step(const SlotArgs &sa, hipStream_t stream) {
@@ -795,6 +1299,12 @@ template <>
 int BeamOps<kST>::search_ids(const SearchArgs &a, hipStream_t s) {
     return dispatch_dim<Table<VisitLds>::Launch, kST>(a.d, a, s);
 }
+#if RG_BEAM_STORAGE == 0
+template <>
+int BeamOps<kST>::search_bits(const SearchArgs &a, hipStream_t s) {
+    return dispatch_dim<Table<VisitBits>::Launch, kST>(a.d, a, s);
+}
+#endif
 template <>
 int BeamOps<kST>::ids_occupancy(const SearchArgs &a) {
     return dispatch_dim<Table<VisitLds>::Occ, kST>(a.d, a, nullptr);
@@ -807,6 +1317,11 @@ int BeamOps<kST>::search_sets(const SearchArgs &a, hipStream_t s) {
 template <>
 int BeamOps<kST>::sets_occupancy(const SearchArgs &a) {
     return dispatch_dim<Table<VisitSets>::Occ, kST>(a.d, a, nullptr);
+}
+#elif RG_BEAM_PART == 3
+template <>
+int BeamOps<kST>::wide(const SearchArgs &a, hipStream_t s) {
+    return dispatch_dim<WideLaunch, kST>(a.d, a, s);
 }
 #else
 template <>
@@ -867,6 +1382,26 @@ int cand_capacity(int ell, bool csr) { return csr || ell > 64 ? kCand : 64; }
 int launch_search(const SearchArgs &a, hipStream_t stream) {
     if (a.nq == 0) return RG_OK;
     return with_storage(a.storage, "search", [&](auto ops) { return a.sets ? ops.search_sets(a, stream) : ops.search_ids(a, stream); });
+}
+
+int launch_search_bits(const SearchArgs &a, hipStream_t stream) {
+    if (a.nq == 0) return RG_OK;
+    if (a.storage != RG_STORE_FP32 || a.n_rows > (32ll << a.hash_bits)) {
+        set_error("search: bad arguments for the visited bits in LDS");
+        return RG_EINTERNAL;
+    }
+    return BeamOps<RG_STORE_FP32>::search_bits(a, stream);
+}
+
+int launch_search_wide(const SearchArgs &a, hipStream_t stream) {
+    if (a.nq == 0) return RG_OK;
+    if (a.adj_off || a.ell > 64 || a.Leff > kMaxSearchL || a.grid < 2 || a.grid > kMaxWide ||
+        a.prep < 1 || a.grid % a.prep != 0 ||
+        (!a.sets && (a.storage != RG_STORE_FP32 || (!a.bitmap && a.n_rows + 64 * (kMaxWide + 1) > (3ll << a.hash_bits) / 4)))) {
+        set_error("search: bad arguments for several wavefronts per query");
+        return RG_EINTERNAL;
+    }
+    return with_storage(a.storage, "search", [&](auto ops) { return ops.wide(a, stream); });
 }
 
 int launch_search_persistent(const SearchArgs &a, hipStream_t stream) {

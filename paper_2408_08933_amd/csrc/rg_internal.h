@@ -58,6 +58,7 @@ struct SearchArgs {
     int64_t bm_words;
     uint32_t *work;
     int32_t grid;
+    int32_t prep;               // wavefronts per preparation (launch_search_wide)
     int *occ_out;
 };
 
@@ -70,6 +71,15 @@ constexpr int kMaxDevices = 64;
 int noalloc_scratch(int device, uint32_t **out);
 int launch_zero_words(uint32_t *p, int n, hipStream_t stream);
 int launch_search_persistent(const SearchArgs &a, hipStream_t stream);
+// FP32 rows, one query per workgroup, an exact visited bitmap of 4 <<
+// a.hash_bits bytes in LDS
+int launch_search_bits(const SearchArgs &a, hipStream_t stream);
+// a.grid wavefronts (2 .. kMaxWide) per query; ELL rows of at most 64 ids.
+// a.sets: the visited table of set_table; else an exact one of 2^hash_bits
+// ids that overflows into the bitmaps (one per query; null where
+// n nodes and kMaxWide + 1 rows of 64 fill less than 3/4 of the table)
+constexpr int kMaxWide = 8;
+int launch_search_wide(const SearchArgs &a, hipStream_t stream);
 int search_occupancy(const SearchArgs &a, int *blocks_per_cu);
 // workgroups of the LDS-table search (k_search) one CU holds with a.hash_bits and a.sets
 int table_search_occupancy(const SearchArgs &a, int *blocks_per_cu);

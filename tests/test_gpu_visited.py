@@ -69,3 +69,27 @@ def test_tables_return_the_exact_results(dev, n, deg, storage):
             assert torch.equal(a[0], ids) and torch.equal(a[1], ds) and torch.equal(a[2], hops), (k, L, hb)
             assert (a[3] >= ev).all()
         assert all(len(set(r.tolist())) == k for r in ids)   # no node twice
+
+
+# nq: the limits of 8, 4 and 2 wavefronts per query, and one past them; L: the
+# limits of 2, 8 and 16 queue entries per lane; n = 60000 visits more nodes at
+# L = 1024 than the exact table in LDS holds, so it overflows into the bitmap
+# (several times at 4 wavefronts), n = 3000 keeps its bitmap in LDS past 512
+# queries.  Rows hold copies.
+@pytest.mark.parametrize("storage", ["fp32", "bf16", "fp8"])
+@pytest.mark.parametrize("n,d,deg", [(3000, 40, 24), (60000, 8, 48), (300, 230, 64)])
+def test_few_queries_equal_the_sequential_search(dev, n, d, deg, storage):
+    g = torch.Generator().manual_seed(n + d)
+    X, Q = torch.randn(n, d, generator=g), torch.randn(1030, d, generator=g).to(dev)
+    off, idx = graph(n, deg, n + d)
+    ix = rg.rg_index_from_csr(X.to(dev), off, idx, 7)
+    if storage != "fp32":
+        rg.rg_index_set_storage(ix, rg.RG_STORE_BF16 if storage == "bf16" else rg.RG_STORE_FP8E4M3)
+    for nq, k, L in ((1, 1, 1), (1, 10, 128), (5, 10, 129), (256, 100, 512), (257, 5, 513), (300, 10, 1024),
+                     (2, 10, 1024), (512, 10, 64), (513, 10, 100), (1024, 10, 20), (1025, 10, 20)):
+        print(f"few queries n={n} {storage} nq={nq} k={k} L={L}", flush=True)
+        ids, ds, hops, ev = exact(ix, Q[:nq].contiguous(), k, L)
+        a = rg.rg_search(ix, Q[:nq].contiguous(), k, L, stats=True)
+        torch.cuda.synchronize()
+        assert torch.equal(a[0], ids) and torch.equal(a[1], ds) and torch.equal(a[2], hops), (nq, k, L)
+        assert torch.equal(a[3], ev) if storage == "fp32" and n / 8 <= 8.0 * L * d else (a[3] >= ev).all(), (nq, k, L)
