@@ -545,7 +545,7 @@ int rg_build(const float *base, int64_t n, int32_t d, const float *train, int64_
     rc = upload_base(ix, base, st);
     HostGraph g;
     if (!rc) {
-        GpuCtx gpu{ix->d_base, ix->pitch, st};
+        GpuCtx gpu{ix->d_base, ix->pitch, st, canon_enhance};
         rc = host_construct(xh.data(), n, d, knn.data(), nt, Nq, M, L, m_pj, m_ce, threads, &gpu, o.keep_stages != 0,
                             &g);
     }
@@ -816,14 +816,16 @@ int rg_insert(rg_index *ix, const float *vectors, int64_t nv, int32_t L, void *s
         rc = grow_device_base(ix, vectors, nv, st);
         if (rc) return undo(rc);
         const int64_t B = std::min<int64_t>(nv, 1 << 15);
-        DevBuf di, dd, dn;
-        rc = di.alloc(sizeof(uint32_t) * B * L);
+        DevBuf di, dd, dn, dm;
+        rc = dm.alloc(8);
+        if (!rc) rc = launch_max_norm(ix->d_base, n0, ix->pitch, dm.as<double>(), st);
+        if (!rc) rc = di.alloc(sizeof(uint32_t) * B * L);
         if (!rc) rc = dd.alloc(sizeof(double) * B * L);
         if (!rc) rc = dn.alloc(sizeof(int32_t) * B);
         for (int64_t x0 = 0; x0 < nv && !rc; x0 += B) {
             const int64_t cnt = std::min(B, nv - x0);
-            rc = launch_canon_search(ix->d_base, d, ix->pitch, ix->d_adj, ix->ell, ix->entry, L, n0 + x0, cnt,
-                                     di.as<uint32_t>(), dd.as<double>(), dn.as<int32_t>(), st);
+            rc = launch_canon_search(ix->d_base, n0, d, ix->pitch, ix->d_adj, ix->ell, ix->entry, L, n0 + x0, cnt,
+                                     dm.as<double>(), di.as<uint32_t>(), dd.as<double>(), dn.as<int32_t>(), st);
             if (!rc && (hipMemcpyAsync(qid.data() + x0 * L, di.p, sizeof(uint32_t) * cnt * L, hipMemcpyDeviceToHost,
                                        st) != hipSuccess ||
                         hipMemcpyAsync(qn.data() + x0, dn.p, sizeof(int32_t) * cnt, hipMemcpyDeviceToHost, st) !=

@@ -58,7 +58,6 @@ struct BeamOps {
 #ifdef RG_BEAM_STORAGE
 namespace {
 
-constexpr uint32_t kEmpty = 0xFFFFFFFFu;
 
 struct Lds {
     float *qs;      // the query, zero padded to the row pitch
@@ -212,28 +211,6 @@ __device__ __forceinline__ void dot_rows(const SearchArgs &a, const uint32_t (&u
     }
 }
 
-// lane l reads lane l + n of its 16-lane row (row shift left) or lane
-// l ^ 2 / l ^ 1 (quad permutes); lanes past the row read 0
-template <int CTRL>
-__device__ __forceinline__ float dpp_read(float v) {
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, true));
-}
-
-// Sum of the G lanes of each group, valid in the group's first lane.  The
-// steps are those of an xor butterfly with the largest offset first, as
-// seen from the first lane, so the value is the butterfly's bit for bit;
-// inside a 16-lane row they use DPP (no LDS round trip), across rows
-// (G = 32) a shuffle.
-template <int G>
-__device__ __forceinline__ float group_sum(float v) {
-    if constexpr (G >= 32) v += __shfl_down(v, 16);
-    if constexpr (G >= 16) v += dpp_read<0x108>(v);  // row_shl:8: lane + 8
-    if constexpr (G >= 8) v += dpp_read<0x104>(v);   // row_shl:4: lane + 4
-    if constexpr (G >= 4) v += dpp_read<0x4E>(v);    // quad_perm [2,3,0,1]: lane ^ 2
-    if constexpr (G >= 2) v += dpp_read<0xB1>(v);    // quad_perm [1,0,3,2]: lane ^ 1
-    return v;
-}
-
 // delta of this group's row from its group-summed dot product (and, for
 // E4M3, the row's power-of-two scale: the product is exact)
 template <int ST>
@@ -271,110 +248,6 @@ __device__ __forceinline__ void score_batch(const SearchArgs &a, const float *qs
         }
     }
 }
-
-__device__ __forceinline__ uint32_t hslot(uint32_t u, int hb) { return (u * 2654435761u) >> (32 - hb); }
-
-// Visited set kept in LDS: open addressing, cleared when it passes half load
-// (clearing only costs re-scoring; see the file comment).
-struct VisitLds {
-    uint32_t *htab;
-    int hb, H, hcount;
-    __device__ __forceinline__ VisitLds(uint32_t *t, int hash_bits, int) : htab(t), hb(hash_bits), H(1 << hb), hcount(0) {}
-    __device__ __forceinline__ void clear() {
-        for (int i = lane_id(); i < H; i += 64) htab[i] = kEmpty;
-        hcount = 0;
-    }
-    __device__ __forceinline__ void mark_entry(uint32_t u) {  // lane 0, table just cleared
-        htab[hslot(u, hb)] = u;
-    }
-    __device__ __forceinline__ void begin_hop(int ell) {
-        if (hcount + ell > (H >> 1)) {
-            clear();
-            wave_sync();
-        }
-    }
-    __device__ __forceinline__ bool insert(uint32_t u) {
-        const uint32_t hmask = (uint32_t)H - 1u;
-        uint32_t h = hslot(u, hb);
-        for (int probe = 0; probe < H; ++probe) {
-            const uint32_t old = atomicCAS(&htab[h], kEmpty, u);
-            if (old == kEmpty) return true;
-            if (old == u) return false;
-            h = (h + 1u) & hmask;
-        }
-        return false;
-    }
-    __device__ __forceinline__ void added(int k) { hcount += k; }
-    // what a resumed search needs beside the table's words
-    __device__ __forceinline__ int count() const { return hcount; }
-    __device__ __forceinline__ void restore(int c) { hcount = c; }
-};
-
-// Visited set kept in LDS that forgets one node at a time: 2^set_bits sets of
-// four 16-bit entries, the newest first; a new node pushes its set's oldest
-// one out.  A node's bits are spread by an odd multiplier (a bijection of the
-// id_bits-bit numbers); the product's top set_bits bits name the set and the
-// rest, which must fit 16 bits, is the entry, so an entry is one node and no
-// other.  Half the bytes of an id per node, and never cleared: at any time it
-// holds the last 4 * 2^set_bits nodes (up to uneven sets), where a table
-// cleared at half load holds a quarter of its ids on average.  Rows scored
-// per query, 10k queries a launch: 2M x 512 E4M3 at L = 409 26,160 -> 20,400
-// (2 KB; 16,560 distinct) and 40.0 -> 34.1 ms, 500k x 200 BF16 at L = 805,
-// 3,001 queries, 44,310 -> 33,200 (26,890) and 11.1 -> 8.8 ms, 700k x 100
-// FP32 at L = 32, 4,096 queries, 2,190 -> 1,713 (1,704) and 0.83 -> 0.69 ms.
-//
-// Lanes of one expansion that meet in a set take turns: each turn one lane's
-// compare-and-swap succeeds and the others look at the set again, so a node
-// that stands twice in an adjacency row is taken once.  That needs the row in
-// one turn (at most 64 ids).  The entry 0xFFFF marks a free place; the one
-// node per set that would have it (16-bit entries only) is never remembered,
-// and copies of it within a row are told apart by a vote.
-struct VisitSets {
-    unsigned long long *tab;
-    int set_bits, rest_bits;
-    uint32_t idmask;
-    __device__ __forceinline__ VisitSets(uint32_t *t, int hash_bits, int id_bits)
-        : tab(reinterpret_cast<unsigned long long *>(t)), set_bits(hash_bits - 1), rest_bits(id_bits - hash_bits + 1),
-          idmask(id_bits >= 32 ? 0xFFFFFFFFu : (1u << id_bits) - 1u) {}
-    __device__ __forceinline__ void clear() {
-        for (int i = lane_id(); i < (1 << set_bits); i += 64) tab[i] = ~0ull;
-    }
-    __device__ __forceinline__ void mark_entry(uint32_t u) { (void)insert(u); }
-    __device__ __forceinline__ void begin_hop(int) {}
-    __device__ __forceinline__ void added(int) {}
-    __device__ __forceinline__ int count() const { return 0; }
-    __device__ __forceinline__ void restore(int) {}
-    // whether one of a set's four entries is rest (twice = rest * 0x10001): a
-    // 16-bit half of the difference is zero
-    static __device__ __forceinline__ bool among(unsigned long long set, uint32_t twice) {
-        const uint32_t a = (uint32_t)set ^ twice, b = (uint32_t)(set >> 32) ^ twice;
-        return ((((a - 0x10001u) & ~a) | ((b - 0x10001u) & ~b)) & 0x80008000u) != 0u;
-    }
-    __device__ __forceinline__ bool holds(uint32_t u) const {
-        const uint32_t h = (u * 2654435761u) & idmask, rest = h & ((1u << rest_bits) - 1u);
-        return rest != 0xFFFFu && among(tab[h >> rest_bits], rest * 0x10001u);
-    }
-    __device__ __forceinline__ bool insert(uint32_t u) {
-        const uint32_t h = (u * 2654435761u) & idmask;
-        const uint32_t rest = h & ((1u << rest_bits) - 1u), twice = rest * 0x10001u;
-        unsigned long long *p = tab + (h >> rest_bits);
-        bool fresh = true;
-        for (uint64_t m = ballot64(rest == 0xFFFFu); m; m &= m - 1) {
-            const int src = (int)__builtin_ctzll(m);
-            // readlane: the lanes after src compare with it, whichever are active
-            const uint32_t first = (uint32_t)__builtin_amdgcn_readlane((int)u, src);
-            if (u == first && lane_id() > src) fresh = false;
-        }
-        if (rest == 0xFFFFu) return fresh;
-        unsigned long long old = *p;
-        for (;;) {
-            if (among(old, twice)) return false;
-            const unsigned long long got = atomicCAS(p, old, (old << 16) | rest);
-            if (got == old) return true;
-            old = got;
-        }
-    }
-};
 
 // Exact visited set of a small base: one bit per node in LDS, 32 per
 // word of the table.

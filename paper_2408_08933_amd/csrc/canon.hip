@@ -1,28 +1,64 @@
-// Construction-time beam search with the canonical FP64 distance.
+// Construction-time searches, selections and reverse updates with the
+// canonical FP64 distance.
 //
 // Connectivity enhancement (Algorithm 1; Sec. 4.2.4) searches the projected
 // graph once per base vector, with the base vector as the query and a queue
-// of length L, and uses the final queue as candidate neighbours.  Those
-// candidates decide the graph, so they are computed with the same
-// canonical distance the host uses everywhere in construction:
-// delta(a, b) = -sum_i a_i b_i, accumulated in FP64 in increasing i.  On the
-// GPU each lane computes one neighbour's sum as a chain of FP64 fused
-// multiply-adds; the product of two floats is exact in FP64, so every step
-// rounds exactly like the host's add, and the value is bit-identical.
+// of length L, uses the final queue as candidate neighbours, and lets every
+// selected node reconsider its list.  All of it decides the graph, so it is
+// computed with the same canonical distance the host uses everywhere in
+// construction: delta(a, b) = -sum_i a_i b_i, accumulated in FP64 in
+// increasing i.  On the GPU one lane computes one sum as a chain of FP64
+// fused multiply-adds; the product of two floats is exact in FP64, so every
+// step rounds exactly like the host's add, and the value is bit-identical.
 //
-// One wavefront per searched node; the queue (FP64 keys), candidate batch
-// and visited table live in LDS; the expansion rule, the lossy visited table
-// and the merge are those of the query-time search, so the final queue
-// equals the host searcher's.
+// Such a chain is a lane's walk over a whole row, hundreds of dependent steps,
+// and what decides is hardly ever its last bits.  So sums that many lanes
+// share go first, with a bound on how far they can be from the canonical
+// value, and only what the bound leaves open takes the chain: the searches
+// compare FP64 sums, the selections FP32 ones.
 #include "queue_ops.h"
 #include "rg_internal.h"
 #include "wave_ops.h"
 
+#include <chrono>
+#include <cstdio>
+#include <cstdlib>
+
 namespace rg {
 namespace {
 
-constexpr uint32_t kEmpty = 0xFFFFFFFFu;
-constexpr int kCand = 128;
+// -delta(q, row), q and row 16-byte aligned; the next 16 elements are loaded
+// while the current ones are added
+__device__ __forceinline__ double canon_sum(const float *q, const float *row, int d) {
+    double s = 0.0;
+    const float4 *q4 = reinterpret_cast<const float4 *>(q);
+    const float4 *r4 = reinterpret_cast<const float4 *>(row);
+    const int d4 = d >> 2, full = d4 & ~3;
+    float4 nx[4];
+    if (full > 0) {
+#pragma unroll
+        for (int t = 0; t < 4; ++t) nx[t] = r4[t];
+    }
+    for (int c = 0; c < full; c += 4) {
+        float4 b[4];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) b[t] = nx[t];
+        if (c + 4 < full) {
+#pragma unroll
+            for (int t = 0; t < 4; ++t) nx[t] = r4[c + 4 + t];
+        }
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            const float4 a = q4[c + t];
+            s = fma((double)a.x, (double)b[t].x, s);
+            s = fma((double)a.y, (double)b[t].y, s);
+            s = fma((double)a.z, (double)b[t].z, s);
+            s = fma((double)a.w, (double)b[t].w, s);
+        }
+    }
+    for (int i = full * 4; i < d; ++i) s = fma((double)q[i], (double)row[i], s);
+    return s;
+}
 
 struct CanonArgs {
     const float *X;         // n x pitch (zero padded)
@@ -31,59 +67,132 @@ struct CanonArgs {
     double *out_d;          // count x L
     int32_t *out_n;         // count
     int64_t x0, count;
-    int32_t d, pitch, ell, L, hash_bits;
+    int32_t d, pitch, ell, L, hash_bits, id_bits, cand, redo;
     uint32_t entry;
+    const double *xmax2;    // the largest squared row norm
+    double gam, gam32;      // |shared sum - canonical sum| <= gam |q| |x|; of FP32 sums
 };
 
-__device__ __forceinline__ double canon_delta(const float *q, const float *row, int d) {
-    double s = 0.0;
-    const float4 *q4 = reinterpret_cast<const float4 *>(q);
-    const float4 *r4 = reinterpret_cast<const float4 *>(row);
-    const int d4 = d >> 2;
-    for (int c = 0; c < d4; ++c) {
-        const float4 a = q4[c], b = r4[c];
-        s = fma((double)a.x, (double)b.x, s);
-        s = fma((double)a.y, (double)b.y, s);
-        s = fma((double)a.z, (double)b.z, s);
-        s = fma((double)a.w, (double)b.w, s);
+// LDS of one search; qd is 8-byte aligned
+struct CanonLds {
+    float *qrow;
+    double *qd;
+    uint32_t *htab;
+    QueueLds<double> ql;
+    __device__ __forceinline__ CanonLds(unsigned char *smem, const CanonArgs &a) {
+        qrow = reinterpret_cast<float *>(smem);
+        qd = reinterpret_cast<double *>(qrow + a.pitch);
+        double *cd = qd + a.L, *sd = cd + a.cand;
+        uint32_t *ci = reinterpret_cast<uint32_t *>(sd + a.cand), *si = ci + a.cand;
+        int32_t *slb = reinterpret_cast<int32_t *>(si + a.cand);
+        htab = reinterpret_cast<uint32_t *>(slb + a.cand);  // cand is even: 8-byte aligned
+        ql = QueueLds<double>{qd, htab + (1 << a.hash_bits), cd, ci, sd, si, slb};
     }
-    for (int i = d4 * 4; i < d; ++i) s = fma((double)q[i], (double)row[i], s);
-    return -s;
+};
+size_t canon_lds_bytes(const CanonArgs &a) {
+    return (size_t)a.pitch * 4 + (size_t)a.L * 12 + (size_t)a.cand * 28 + ((size_t)4 << a.hash_bits);
 }
 
-__device__ __forceinline__ uint32_t hslot(uint32_t u, int hb) { return (u * 2654435761u) >> (32 - hb); }
+// delta of q and each of the rows ids[0..cnt), up to gam |q| |x| (T = double)
+// or gam32 |q| |x| (float): 16 lanes per row, each adding the products of every
+// 16th 4-element piece, then a tree; the value depends on the two rows alone.
+// R rows per group in flight.
+template <typename T, int R>
+__device__ __forceinline__ void shared_sums(const CanonArgs &a, const float *q, const uint32_t *ids, int cnt, T *out) {
+    constexpr int G = 16, NG = 4;
+    const int g = lane_id() / G, j = lane_id() % G, nch = a.pitch >> 2;
+    const float4 *q4 = reinterpret_cast<const float4 *>(q);
+    for (int p = 0; p < cnt; p += NG * R) {
+        const float4 *row[R];
+        T s[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const int i = p + r * NG + g;
+            row[r] = reinterpret_cast<const float4 *>(a.X + (size_t)ids[i < cnt ? i : 0] * a.pitch);
+            s[r] = (T)0;
+        }
+#pragma unroll 4
+        for (int c = j; c < nch; c += G) {
+            const float4 x = q4[c];
+            const T x0 = (T)x.x, x1 = (T)x.y, x2 = (T)x.z, x3 = (T)x.w;
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const float4 y = row[r][c];
+                s[r] = fma(x0, (T)y.x, s[r]);
+                s[r] = fma(x1, (T)y.y, s[r]);
+                s[r] = fma(x2, (T)y.z, s[r]);
+                s[r] = fma(x3, (T)y.w, s[r]);
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            s[r] = group_sum<G>(s[r]);
+            const int i = p + r * NG + g;
+            if (j == 0 && i < cnt) out[i] = -s[r];
+        }
+    }
+}
 
+// One wavefront per searched node; the queue (FP64 keys), candidate batch and
+// visited table live in LDS.  The expansion rule, the forgetting visited
+// table and the merge are those of the query-time search, so the final queue
+// equals the host searcher's.
+//
+// NEAR: the keys are shared sums.  They decide while no two that are compared
+// lie within twice their error (2.5e-14 |q| |x| at d = 200) of each other; then
+// the queue is the canonical one, and its distances are computed at the end,
+// one lane per entry.  While the queue is full most candidates are far beyond
+// its last entry: FP32 sums with their own bound turn those away.  A search
+// that meets two closer keys (copies of a row, say) gives up, and a second
+// launch (redo) runs it with a canonical chain for every candidate, as all
+// searches did before.  60k rows of 200, L = 500 (about 550 expansions and
+// 16k rows scored each): 83 ms against 210; shared FP64 sums for every row
+// took 117 (their conversions keep the VALU busy), FP32 sums with chains for
+// what they leave open 129.
+template <class VIS, bool NEAR>
 __global__ __launch_bounds__(64) void k_canon_search(CanonArgs a) {
     extern __shared__ __align__(16) unsigned char smem[];
     const int lane = lane_id();
     const int L = a.L, ell = a.ell, d = a.d;
     const int64_t b = blockIdx.x;
     const int64_t x = a.x0 + b;
-    // LDS: query row, queue, batch, survivors, visited table
-    float *qrow = reinterpret_cast<float *>(smem);
-    double *qd = reinterpret_cast<double *>(qrow + a.pitch);
-    double *cd = qd + L;
-    double *sd = cd + kCand;
-    uint32_t *qi = reinterpret_cast<uint32_t *>(sd + kCand);
-    uint32_t *ci = qi + L;
-    uint32_t *si = ci + kCand;
-    int32_t *slb = reinterpret_cast<int32_t *>(si + kCand);
-    uint32_t *htab = reinterpret_cast<uint32_t *>(slb + kCand);
-    const int hb = a.hash_bits;
-    const int H = 1 << hb;
-    const uint32_t hmask = (uint32_t)H - 1u;
-    const QueueLds<double> ql{qd, qi, cd, ci, sd, si, slb};
+    if (!NEAR && a.redo && a.out_n[b] >= 0) return;
+    const CanonLds s(smem, a);
+    float *qrow = s.qrow;
+    double *qd = s.qd, *cd = s.ql.cd;
+    uint32_t *qi = s.ql.qi, *ci = s.ql.ci;
+    VIS vis(s.htab, a.hash_bits, a.id_bits);
 
-    for (int i = lane; i < a.pitch; i += 64) qrow[i] = a.X[x * a.pitch + i];
-    for (int i = lane; i < H; i += 64) htab[i] = kEmpty;
-    __syncthreads();
-    if (lane == 0) {
-        qd[0] = canon_delta(qrow, a.X + (size_t)a.entry * a.pitch, d);
-        qi[0] = a.entry;
-        htab[hslot(a.entry, hb)] = a.entry;
+    double n2 = 0.0;
+    for (int i = lane; i < a.pitch; i += 64) {
+        const float v = a.X[x * a.pitch + i];
+        qrow[i] = v;
+        n2 = fma((double)v, (double)v, n2);
     }
-    int qn = 1, ptr = 0, hcount = 1;
-    __syncthreads();
+    vis.clear();
+    double tol = 0.0, tol32 = 0.0;
+    if constexpr (NEAR) {
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) n2 += __shfl_xor(n2, o);
+        const double nn = sqrt(n2 * *a.xmax2) * (1.0 + 1e-9);
+        tol = 2.0 * a.gam * nn;
+        tol32 = (a.gam + a.gam32) * nn + 1e-30;  // and what underflow may lose
+    }
+    wave_sync();
+    if (NEAR) {
+        if (lane == 0) ci[0] = a.entry;
+        wave_sync();
+        shared_sums<double, 1>(a, qrow, ci, 1, qd);
+    } else if (lane == 0) {
+        qd[0] = -canon_sum(qrow, a.X + (size_t)a.entry * a.pitch, d);
+    }
+    if (lane == 0) {
+        qi[0] = a.entry;
+        vis.mark_entry(a.entry);
+    }
+    vis.added(1);
+    int qn = 1, ptr = 0;
+    wave_sync();
     for (;;) {
         int sel = -1;
         for (int bb = ptr; bb < qn; bb += 64) {
@@ -97,99 +206,145 @@ __global__ __launch_bounds__(64) void k_canon_search(CanonArgs a) {
         if (sel < 0) break;
         ptr = sel;
         const uint32_t v = qi[sel];
-        __syncthreads();
+        wave_sync();
         if (lane == 0) qi[sel] = v | kExpanded;
-        if (hcount + ell > (H >> 1)) {
-            for (int i = lane; i < H; i += 64) htab[i] = kEmpty;
-            hcount = 0;
-            __syncthreads();
-        }
+        vis.begin_hop(ell);
         int nnew = 0;
         for (int e0 = 0; e0 < ell; e0 += 64) {
             const int e = e0 + lane;
             const uint32_t u = e < ell ? a.adj[(size_t)v * ell + e] : kNone;
-            bool fresh = false;
-            if (u != kNone) {
-                uint32_t h = hslot(u, hb);
-                for (int probe = 0; probe < H; ++probe) {
-                    const uint32_t old = atomicCAS(&htab[h], kEmpty, u);
-                    if (old == kEmpty) {
-                        fresh = true;
-                        break;
-                    }
-                    if (old == u) break;
-                    h = (h + 1u) & hmask;
-                }
-            }
+            const bool fresh = u != kNone && vis.insert(u);
             const uint64_t m = ballot64(fresh);
             if (fresh) ci[nnew + lanes_below(m)] = u;
             nnew += (int)__popcll(m);
         }
-        hcount += nnew;
-        __syncthreads();
+        vis.added(nnew);
+        wave_sync();
         if (nnew == 0) continue;
-        for (int j = lane; j < nnew; j += 64) cd[j] = canon_delta(qrow, a.X + (size_t)ci[j] * a.pitch, d);
-        __syncthreads();
-        if (nnew <= 64)
-            merge_batch<1, double>(ql, nnew, L, qn, ptr);
-        else
-            merge_batch<2, double>(ql, nnew, L, qn, ptr);
+        if constexpr (NEAR) {
+            if (qn == L) {
+                float *fd = reinterpret_cast<float *>(s.ql.sd);
+                shared_sums<float, 4>(a, qrow, ci, nnew, fd);
+                wave_sync();
+                const double bar = qd[L - 1] + tol32;
+                const uint32_t u = ci[lane];
+                const bool keep = lane < nnew && !((double)fd[lane] > bar);
+                const uint64_t m = ballot64(keep);
+                nnew = (int)__popcll(m);
+                if (nnew == 0) continue;
+                wave_sync();
+                if (keep) ci[lanes_below(m)] = u;
+                wave_sync();
+            }
+            if (nnew <= 4)
+                shared_sums<double, 1>(a, qrow, ci, nnew, cd);
+            else
+                shared_sums<double, 4>(a, qrow, ci, nnew, cd);
+            wave_sync();
+            if (!merge_batch<1, double, kMaxL / 64, true>(s.ql, nnew, L, qn, ptr, tol)) {
+                if (lane == 0) a.out_n[b] = -1;
+                return;
+            }
+        } else {
+            for (int j = lane; j < nnew; j += 64) cd[j] = -canon_sum(qrow, a.X + (size_t)ci[j] * a.pitch, d);
+            wave_sync();
+            if (nnew <= 64)
+                merge_batch<1, double>(s.ql, nnew, L, qn, ptr);
+            else
+                merge_batch<2, double>(s.ql, nnew, L, qn, ptr);
+        }
+        wave_sync();
     }
     for (int i = lane; i < qn; i += 64) {
-        a.out_ids[b * L + i] = qi[i] & ~kExpanded;
-        a.out_d[b * L + i] = qd[i];
+        const uint32_t u = qi[i] & ~kExpanded;
+        a.out_ids[b * L + i] = u;
+        a.out_d[b * L + i] = NEAR ? -canon_sum(qrow, a.X + (size_t)u * a.pitch, d) : qd[i];
     }
     if (lane == 0) a.out_n[b] = qn;
+}
+
+// The largest squared row norm (the sums' own rounding is in the callers'
+// margin); *out starts at 0.  A NaN norm counts as infinite: nothing is then
+// far enough apart.
+__global__ __launch_bounds__(256) void k_max_norm(const float *X, int64_t n, int pitch, double *out) {
+    const int lane = lane_id();
+    double best = 0.0;
+    for (int64_t r = blockIdx.x * 4 + (threadIdx.x >> 6); r < n; r += (int64_t)gridDim.x * 4) {
+        double s = 0.0;
+        for (int i = lane; i < pitch; i += 64) {
+            const float v = X[r * pitch + i];
+            s = fma((double)v, (double)v, s);
+        }
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
+        best = s != s ? __builtin_inf() : fmax(best, s);
+    }
+    // the bits of values that are not negative order like the values
+    if (lane == 0) atomicMax(reinterpret_cast<unsigned long long *>(out), (unsigned long long)__double_as_longlong(best));
 }
 
 // AcquireNeighbors (Algorithm 3, without the fill) for every searched node,
 // on the device: the candidates are the node's final queue without the node
 // itself, already ranked by (delta, id); a candidate is kept iff
-// delta(x, c) < delta(c, p) for every kept p (strict), until m are kept.
-// Lane r computes delta(c, kept_r) as the same sequential FP64 chain as the
-// host (exact float products, one rounding per addition), so every decision
-// is the host's.  The kept rows sit in LDS when they fit.
+// delta(x, c) < delta(c, p) for every kept p (strict), until m are kept.  One
+// lane per candidate, 64 at a time in rank order.  FP32 sums (16 kept rows in
+// one pass over the candidate's row) settle what lies outside their bound,
+// gam |c| |p|; the rest takes the host's FP64 chain, so every decision is the
+// host's.  The kept rows sit in LDS when they fit.  60k queues of 500 rows of
+// 200, m = 31: 22 ms against 71 with a chain for every pair.
 struct SelectArgs {
     const float *X;          // n x pitch
     int32_t d, pitch;
     const uint32_t *ids;     // count x L search output
     const double *dists;
     const int32_t *counts;
-    int32_t L, m, head_len, kept_in_lds;
+    int32_t L, m, head_len;
     int64_t x0;
     uint32_t *sel_ids;       // count x m
     double *sel_d;
     int32_t *sel_n;
     uint32_t *head;          // count x head_len: the first candidates
     int32_t *head_n;         // candidates per node (without the node)
+    float gam;
 };
 
-// delta(c, kept row r) for r in [r0, r0 + nk), nk <= KG, for this lane's
-// candidate row c: one pass over c, one sequential FP64 chain per kept row
-// (each pair's sum runs in increasing i, as on the host).  kr(t) gives the
-// kept row r0 + t (in LDS, or in device memory when the rows do not fit).
 constexpr int KG = 16;
+
+// FP32 sums of this lane's candidate row with kept rows r0 .. r0 + nk, and
+// the candidate's squared norm.  kr(t) is kept row r0 + t.
 template <class KR>
-__device__ __forceinline__ void canon_against_kept(const float *crow, KR kr, int d, int nk, double (&acc)[KG]) {
-    const float *kp[KG];
+__device__ __forceinline__ void near_kept(const float *crow, KR kr, int nch, int nk, float (&acc)[KG], float &norm2) {
+    const float4 *kp[KG];
+    norm2 = 0.f;
 #pragma unroll
     for (int t = 0; t < KG; ++t) {
-        acc[t] = 0.0;
-        kp[t] = t < nk ? kr(t) : kr(0);
+        acc[t] = 0.f;
+        kp[t] = reinterpret_cast<const float4 *>(t < nk ? kr(t) : kr(0));
     }
-    for (int i = 0; i < d; ++i) {
-        const double ci = (double)crow[i];
+    const float4 *c4 = reinterpret_cast<const float4 *>(crow);
+#pragma unroll 2
+    for (int i = 0; i < nch; ++i) {
+        const float4 c = c4[i];
+        norm2 = fmaf(c.x, c.x, fmaf(c.y, c.y, fmaf(c.z, c.z, fmaf(c.w, c.w, norm2))));
 #pragma unroll
         for (int t = 0; t < KG; ++t)
-            if (t < nk) acc[t] = fma(ci, (double)kp[t][i], acc[t]);
+            if (t < nk) {
+                const float4 k = kp[t][i];
+                acc[t] = fmaf(c.x, k.x, acc[t]);
+                acc[t] = fmaf(c.y, k.y, acc[t]);
+                acc[t] = fmaf(c.z, k.z, acc[t]);
+                acc[t] = fmaf(c.w, k.w, acc[t]);
+            }
     }
 }
 
+template <bool KEPT_IN_LDS>
 __global__ __launch_bounds__(64) void k_canon_select(SelectArgs a) {
     extern __shared__ __align__(16) unsigned char smem[];
     uint32_t *kid = reinterpret_cast<uint32_t *>(smem);   // m kept ids
-    float *K = reinterpret_cast<float *>(smem) + ((a.m + 3) & ~3);  // m x pitch kept rows (if they fit)
-    const int lane = lane_id();
+    float *kn = reinterpret_cast<float *>(smem) + ((a.m + 3) & ~3);  // their norms (rounded up)
+    float *K = kn + ((a.m + 3) & ~3);                     // m x pitch kept rows (if they fit)
+    const int lane = lane_id(), nch = a.pitch >> 2;
     const int64_t b = blockIdx.x;
     const uint32_t x = (uint32_t)(a.x0 + b);
     const uint32_t *cid = a.ids + b * a.L;
@@ -197,9 +352,9 @@ __global__ __launch_bounds__(64) void k_canon_select(SelectArgs a) {
     const int qn = a.counts[b];
     int nr = 0, hn = 0;
     auto kept_row = [&](int r) -> const float * {
-        return a.kept_in_lds ? K + (size_t)r * a.pitch : a.X + (size_t)kid[r] * a.pitch;
+        if constexpr (KEPT_IN_LDS) return K + (size_t)r * a.pitch;
+        return a.X + (size_t)kid[r] * a.pitch;
     };
-    // 64 candidates at a time, one per lane, in rank order
     for (int j0 = 0; j0 < qn; j0 += 64) {
         const int j = j0 + lane;
         const uint32_t c = j < qn ? cid[j] : kNone;
@@ -211,95 +366,260 @@ __global__ __launch_bounds__(64) void k_canon_select(SelectArgs a) {
         if (nr >= a.m) continue;
         const double dxc = valid ? cdd[j] : 0.0;
         const float *crow = a.X + (size_t)(valid ? c : 0u) * a.pitch;
-        // rejected by a row kept before this batch?
         bool alive = valid;
-        for (int r0 = 0; r0 < nr && ballot64(alive) != 0; r0 += KG) {
-            const int nk = min(KG, nr - r0);
+        float cnorm = 0.f;
+        // this lane's candidate against kept rows r0 .. r0 + nk
+        auto against = [&](int r0, int nk) {
+            float acc[KG];
+            uint32_t open = 0;
             if (alive) {
-                double acc[KG];
-                canon_against_kept(crow, [&](int t) { return kept_row(r0 + t); }, a.d, nk, acc);
+                float n2;
+                near_kept(crow, [&](int t) { return kept_row(r0 + t); }, nch, nk, acc, n2);
+                cnorm = sqrtf(n2) * (1.0001f + a.gam);
 #pragma unroll
                 for (int t = 0; t < KG; ++t)
-                    if (t < nk && !(dxc < -acc[t])) alive = false;
+                    if (t < nk) {
+                        const double dcp = -(double)acc[t], tau = (double)fmaf(a.gam * cnorm, kn[r0 + t], 1e-30f);
+                        if (dxc >= dcp + tau)
+                            alive = false;
+                        else if (!(dxc < dcp - tau))
+                            open |= 1u << t;
+                    }
+                if (!alive) open = 0;
             }
-        }
+            while (ballot64(open != 0)) {
+                if (open) {
+                    const int t = __builtin_ctz(open);
+                    open &= open - 1;
+                    if (!(dxc < -canon_sum(crow, kept_row(r0 + t), a.d))) {
+                        alive = false;
+                        open = 0;
+                    }
+                }
+            }
+        };
+        // rejected by a row kept before this batch?
+        for (int r0 = 0; r0 < nr && ballot64(alive) != 0; r0 += KG) against(r0, min(KG, nr - r0));
         // in rank order: the lowest surviving candidate is kept, and the
         // later survivors are checked against it
         for (;;) {
             const uint64_t am = ballot64(alive);
             if (am == 0 || nr >= a.m) break;
             const int js = (int)__builtin_ctzll(am);
-            const uint32_t cs = (uint32_t)__shfl((int)c, js);
+            const uint32_t cs = (uint32_t)__builtin_amdgcn_readlane((int)c, js);
             const double ds = __shfl(dxc, js);
-            if (a.kept_in_lds)
-                for (int i = lane; i < a.pitch; i += 64) K[(size_t)nr * a.pitch + i] = a.X[(size_t)cs * a.pitch + i];
+            float n2 = 0.f;
+            for (int i = lane; i < a.pitch; i += 64) {
+                const float y = a.X[(size_t)cs * a.pitch + i];
+                if (KEPT_IN_LDS) K[(size_t)nr * a.pitch + i] = y;
+                n2 = fmaf(y, y, n2);
+            }
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) n2 += __shfl_xor(n2, o);
             if (lane == 0) {
                 kid[nr] = cs;
-                a.sel_ids[b * a.m + nr] = cs;
-                a.sel_d[b * a.m + nr] = ds;
+                kn[nr] = sqrtf(n2) * (1.0001f + a.gam);
+                a.sel_ids[(a.x0 + b) * a.m + nr] = cs;
+                a.sel_d[(a.x0 + b) * a.m + nr] = ds;
             }
             ++nr;
-            __syncthreads();
+            wave_sync();
             if (lane == js) alive = false;
-            if (alive) {
-                double acc[KG];
-                const int rn = nr - 1;
-                canon_against_kept(crow, [&](int t) { return kept_row(rn + t); }, a.d, 1, acc);
-                if (!(dxc < -acc[0])) alive = false;
-            }
+            against(nr - 1, 1);
         }
     }
     if (lane == 0) {
-        a.sel_n[b] = nr;
+        a.sel_n[a.x0 + b] = nr;
         a.head_n[b] = hn;
     }
 }
 
+// Reverse updates.  Node p's list starts as its own selection; every later
+// node x that selected p asks it, in ascending x, to take x in: p's list
+// becomes AcquireNeighbors (without fill) of the list and x.  The list is the
+// outcome of such a selection, so its entries stand in rank order and each is
+// nearer to p than to all before it.  Then x, of rank r, is kept iff it is
+// nearer to p than to the r entries before it; if not (or if r = m) nothing
+// changes; if so, the entries behind it stay iff they are nearer to p than to
+// x, as far as m go.  That takes the canonical distances of x to p and to the
+// entries only: one lane each.  One wavefront per list; lists of updates are
+// short (at most 189 where 20k nodes made 535k).  60k rows of 200, m = 31: 3.4
+// ms; on 16 host threads it took 260.
+struct ReplayArgs {
+    const float *X;
+    int32_t d, pitch, m;
+    const uint32_t *sel_ids;  // n x m
+    const double *sel_d;
+    const int32_t *sel_n;
+    const int64_t *off;       // n + 1: the nodes that selected p
+    const uint32_t *src;      // ascending per p where they are more than 64
+    uint32_t *out;            // n x m
+    int32_t *out_n;
+};
+
+__global__ __launch_bounds__(64) void k_replay(ReplayArgs a) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    float *xrow = reinterpret_cast<float *>(smem);
+    double *cd = reinterpret_cast<double *>(xrow + a.pitch);
+    uint32_t *ci = reinterpret_cast<uint32_t *>(cd + a.m + 1);
+    const int lane = lane_id();
+    const int64_t p = blockIdx.x;
+    int nc = a.sel_n[p];
+    for (int j = lane; j < nc; j += 64) {
+        ci[j] = a.sel_ids[p * a.m + j];
+        cd[j] = a.sel_d[p * a.m + j];
+    }
+    const int64_t e0 = a.off[p], ne = a.off[p + 1] - e0;
+    uint32_t ev[1] = {lane < ne ? a.src[e0 + lane] : kNone}, id[1] = {0};
+    if (ne <= 64) wave_sort<1, uint32_t>(ev, id);
+    wave_sync();
+    for (int64_t e = 0; e < ne; ++e) {
+        if (e > 0 && (e & 63) == 0) ev[0] = e + lane < ne ? a.src[e0 + e + lane] : kNone;
+        const uint32_t x = (uint32_t)__builtin_amdgcn_readlane((int)ev[0], (int)(e & 63));
+        if ((int64_t)x < p) continue;  // before p's own selection, which replaced it
+        bool there = false;
+        for (int j = lane; j < nc; j += 64) there |= ci[j] == x;
+        if (ballot64(there)) continue;
+        for (int i = lane; i < a.pitch; i += 64) xrow[i] = a.X[(size_t)x * a.pitch + i];
+        wave_sync();
+        // entry j (j == nc: p itself) in slot j / 64 of lane j % 64
+        double dj[2] = {0.0, 0.0}, key[2] = {0.0, 0.0};
+        uint32_t c[2] = {0, 0};
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            const int j = lane + 64 * s;
+            if (j <= nc) {
+                if (j < nc) {
+                    c[s] = ci[j];
+                    key[s] = cd[j];
+                } else {
+                    c[s] = (uint32_t)p;
+                }
+                dj[s] = -canon_sum(xrow, a.X + (size_t)c[s] * a.pitch, a.d);
+            }
+        }
+        const double d0 = __shfl(dj[0], nc & 63), d1 = __shfl(dj[1], nc & 63);
+        const double dx = nc < 64 ? d0 : d1;
+        bool before[2], occ[2], stay[2];
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            const int j = lane + 64 * s;
+            before[s] = j < nc && kless(key[s], c[s], dx, x);
+            occ[s] = before[s] && !(dx < dj[s]);
+            stay[s] = j < nc && !before[s] && key[s] < dj[s];
+        }
+        const int r = (int)__popcll(ballot64(before[0])) + (int)__popcll(ballot64(before[1]));
+        if (ballot64(occ[0] || occ[1]) || r >= a.m) continue;
+        const uint64_t s0 = ballot64(stay[0]), s1 = ballot64(stay[1]);
+        wave_sync();
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            const int to = r + 1 + (s == 0 ? lanes_below(s0) : (int)__popcll(s0) + lanes_below(s1));
+            if (stay[s] && to < a.m) {
+                ci[to] = c[s];
+                cd[to] = key[s];
+            }
+        }
+        if (lane == 0) {
+            ci[r] = x;
+            cd[r] = dx;
+        }
+        nc = min(a.m, r + 1 + (int)__popcll(s0) + (int)__popcll(s1));
+        wave_sync();
+    }
+    for (int j = lane; j < nc; j += 64) a.out[p * a.m + j] = ci[j];
+    if (lane == 0) a.out_n[p] = nc;
+}
+
+// The nodes that selected each node: counts, then places (in any order).
+__global__ __launch_bounds__(256) void k_count_events(const uint32_t *sel, const int32_t *sel_n, int64_t n, int m,
+                                                     uint32_t *cnt) {
+    for (int64_t x = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; x < n; x += (int64_t)gridDim.x * blockDim.x)
+        for (int j = 0; j < sel_n[x]; ++j) atomicAdd(&cnt[sel[x * m + j]], 1u);
+}
+
+__global__ __launch_bounds__(256) void k_place_events(const uint32_t *sel, const int32_t *sel_n, int64_t n, int m,
+                                                     const int64_t *off, uint32_t *cnt, uint32_t *src) {
+    for (int64_t x = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; x < n; x += (int64_t)gridDim.x * blockDim.x)
+        for (int j = 0; j < sel_n[x]; ++j) {
+            const uint32_t t = sel[x * m + j];
+            src[off[t] + (int64_t)atomicSub(&cnt[t], 1u) - 1] = (uint32_t)x;
+        }
+}
+
+// Ascending order of the lists longer than 64 (shorter ones are sorted by the
+// wavefront that replays them): a bitonic network whose comparators all point
+// the same way, so that a length that is no power of two needs no padding.
+__global__ __launch_bounds__(256) void k_sort_events(const int64_t *off, uint32_t *src) {
+    const int64_t p = blockIdx.x;
+    const int64_t n = off[p + 1] - off[p];
+    if (n <= 64) return;
+    uint32_t *a = src + off[p];
+    const uint32_t ne = (uint32_t)n;  // fewer than nodes
+    int top = 7;
+    while ((1u << top) < ne) ++top;
+    for (int k = 1; k <= top; ++k)
+        for (int j = k - 1; j >= 0; --j) {
+            for (uint32_t i = threadIdx.x; i < 1u << (top - 1); i += blockDim.x) {
+                // the lower element of pair i, and its partner: mirrored in its
+                // block of 2^k at first, then 2^j apart
+                const uint32_t lo = ((i >> j) << (j + 1)) | (i & ((1u << j) - 1u));
+                const uint32_t hi = j == k - 1 ? lo ^ ((1u << k) - 1u) : lo + (1u << j);
+                if (hi < ne && a[hi] < a[lo]) {
+                    const uint32_t t = a[lo];
+                    a[lo] = a[hi];
+                    a[hi] = t;
+                }
+            }
+            __syncthreads();
+        }
+}
+
+__global__ __launch_bounds__(256) void k_zero32(uint32_t *p, int64_t n) {
+    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
+        p[i] = 0u;
+}
+
+// How far an FP32 sum of `steps` fused steps and additions per term may be
+// from the exact one, as a share of the sum of magnitudes, with room for the
+// rounding of that sum, of the bound itself and of the canonical sum.
+float sum_bound(int d, int steps) {
+    const double u = 1.0 / 16777216.0;
+    return (float)((steps * u / (1.0 - steps * u) + (d + 1) * 0x1p-53) * (1.0 + 2.0 * steps * u) * 1.0001);
+}
+
+struct Dev {
+    void *p = nullptr;
+    Dev() = default;
+    Dev(const Dev &) = delete;
+    Dev &operator=(const Dev &) = delete;
+    ~Dev() {
+        if (p) (void)hipFree(p);
+    }
+    bool alloc(size_t bytes) { return hipMalloc(&p, bytes ? bytes : 1) == hipSuccess || (p = nullptr, false); }
+    template <class T>
+    T *as() const {
+        return static_cast<T *>(p);
+    }
+};
+
+unsigned blocks_for(int64_t items) { return (unsigned)std::max<int64_t>(1, std::min<int64_t>(65536, (items + 255) / 256)); }
+
 }  // namespace
 
-int launch_canon_select(const float *X, int32_t d, int32_t pitch, const uint32_t *ids, const double *dists,
-                        const int32_t *counts, int32_t L, int64_t x0, int64_t count, int32_t m, uint32_t *sel_ids,
-                        double *sel_d, int32_t *sel_n, uint32_t *head, int32_t head_len, int32_t *head_n,
-                        hipStream_t stream) {
-    if (count == 0) return RG_OK;
-    if (m < 1 || L < 1) {
-        set_error("canon select: bad arguments");
-        return RG_EINVAL;
-    }
-    SelectArgs a{};
-    a.X = X;
-    a.d = d;
-    a.pitch = pitch;
-    a.ids = ids;
-    a.dists = dists;
-    a.counts = counts;
-    a.L = L;
-    a.m = m;
-    a.head_len = head_len;
-    a.x0 = x0;
-    a.sel_ids = sel_ids;
-    a.sel_d = sel_d;
-    a.sel_n = sel_n;
-    a.head = head;
-    a.head_n = head_n;
-    const size_t id_bytes = (size_t)((m + 3) & ~3) * sizeof(uint32_t);
-    const size_t kept_bytes = (size_t)m * pitch * sizeof(float);
-    a.kept_in_lds = id_bytes + kept_bytes <= (48u << 10);
-    hipLaunchKernelGGL(k_canon_select, dim3((unsigned)count), dim3(64), id_bytes + (a.kept_in_lds ? kept_bytes : 0),
-                       stream, a);
+int launch_max_norm(const float *X, int64_t n, int32_t pitch, double *xmax2, hipStream_t stream) {
+    hipLaunchKernelGGL(k_zero32, dim3(1), dim3(256), 0, stream, reinterpret_cast<uint32_t *>(xmax2), (int64_t)2);
+    hipLaunchKernelGGL(k_max_norm, dim3((unsigned)std::max<int64_t>(1, std::min<int64_t>(512, (n + 3) / 4))), dim3(256),
+                       0, stream, X, n, pitch, xmax2);
     RG_HIP(hipGetLastError());
     return RG_OK;
 }
 
-size_t canon_lds_bytes(int L, int pitch, int hash_bits) {
-    return (size_t)pitch * 4 + (size_t)L * 12 + (size_t)kCand * 24 + ((size_t)4 << hash_bits);
-}
-
-int launch_canon_search(const float *X, int32_t d, int32_t pitch, const uint32_t *adj, int32_t ell,
-                        uint32_t entry, int32_t L, int64_t x0, int64_t count, uint32_t *ids, double *dists,
-                        int32_t *counts, hipStream_t stream) {
+int launch_canon_search(const float *X, int64_t n, int32_t d, int32_t pitch, const uint32_t *adj, int32_t ell,
+                        uint32_t entry, int32_t L, int64_t x0, int64_t count, const double *xmax2, uint32_t *ids,
+                        double *dists, int32_t *counts, hipStream_t stream) {
     if (count == 0) return RG_OK;
-    if (L < 1 || L > kMaxL || ell > kCand || pitch % 4 != 0) {
+    if (L < 1 || L > kMaxL || ell > kMaxEll || pitch % 4 != 0) {
         set_error("canon search: unsupported L, row width or pitch");
         return RG_EINVAL;
     }
@@ -315,11 +635,149 @@ int launch_canon_search(const float *X, int32_t d, int32_t pitch, const uint32_t
     a.pitch = pitch;
     a.ell = ell;
     a.L = L;
-    a.hash_bits = 11;  // 8 KB of LDS: fastest at L = 500 (the table size bounds work, not results)
+    a.cand = ell <= 64 ? 64 : 128;
     a.entry = entry;
-    const size_t lds = canon_lds_bytes(L, pitch, a.hash_bits);
-    hipLaunchKernelGGL(k_canon_search, dim3((unsigned)count), dim3(64), lds, stream, a);
+    a.xmax2 = xmax2;
+    // both sums err by at most d + 8 roundings' worth of sum |q_i x_i|
+    a.gam = 2.0 * (d + 8) * 0x1p-53 * 1.01;
+    a.gam32 = sum_bound(d, (pitch + 63) / 64 * 4 + 6);
+    // the table bounds work, not results: sets of 16-bit entries in 2 KB, or
+    // ids in 8 KB
+    SearchArgs t{};
+    t.n_rows = n;
+    t.ell = ell;
+    set_table(t, 9);
+    auto run = [&](auto kernel) -> int {
+        const size_t lds = canon_lds_bytes(a);
+        if (lds > (64u << 10))
+            RG_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(kernel),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+        hipLaunchKernelGGL(kernel, dim3((unsigned)count), dim3(64), lds, stream, a);
+        RG_HIP(hipGetLastError());
+        return RG_OK;
+    };
+    if (t.sets) {
+        a.hash_bits = t.hash_bits;
+        a.id_bits = t.id_bits;
+        a.redo = 1;
+        const int rc = run(k_canon_search<VisitSets, true>);
+        return rc ? rc : run(k_canon_search<VisitSets, false>);
+    }
+    a.hash_bits = 11;
+    return run(k_canon_search<VisitLds, false>);
+}
+
+// The searches and selections run in batches (their queues are the large
+// buffers); selections, reverse updates and the lists stay on the device.
+int canon_enhance(const GpuCtx &gpu, int64_t n, int32_t d, const std::vector<uint32_t> &adj, int32_t ell,
+                  uint32_t entry, int32_t L, int32_t m, int32_t head_len, std::vector<uint32_t> *ce,
+                  std::vector<int32_t> *ce_n, uint32_t *head, int32_t *head_n, double *t_search) {
+    if (m < 1 || m >= kMaxEll || L < 1) {
+        set_error("build: bad list bound");
+        return RG_EINVAL;
+    }
+    using Clock = std::chrono::steady_clock;
+    const auto t0 = Clock::now();
+    const bool log = std::getenv("RG_LOG") != nullptr;
+    hipStream_t st = gpu.stream;
+    const int64_t B = std::min<int64_t>(n, 1 << 15);
+    Dev d_adj, d_q, d_qd, d_qn, d_sid, d_sd, d_sn, d_hd, d_hn, d_max;
+    if (!d_max.alloc(8) || !d_adj.alloc(sizeof(uint32_t) * adj.size()) || !d_q.alloc(sizeof(uint32_t) * B * L) ||
+        !d_qd.alloc(sizeof(double) * B * L) || !d_qn.alloc(sizeof(int32_t) * B) ||
+        !d_sid.alloc(sizeof(uint32_t) * n * m) || !d_sd.alloc(sizeof(double) * n * m) ||
+        !d_sn.alloc(sizeof(int32_t) * n) || !d_hd.alloc(sizeof(uint32_t) * n * head_len) ||
+        !d_hn.alloc(sizeof(int32_t) * n)) {
+        set_error("build: out of memory for enhancement searches");
+        return RG_ENOMEM;
+    }
+    RG_HIP(hipMemcpyAsync(d_adj.p, adj.data(), sizeof(uint32_t) * adj.size(), hipMemcpyHostToDevice, st));
+    int rc = launch_max_norm(gpu.X, n, gpu.pitch, d_max.as<double>(), st);
+    if (rc) return rc;
+    SelectArgs s{};
+    s.X = gpu.X;
+    s.d = d;
+    s.pitch = gpu.pitch;
+    s.ids = d_q.as<uint32_t>();
+    s.dists = d_qd.as<double>();
+    s.counts = d_qn.as<int32_t>();
+    s.L = L;
+    s.m = m;
+    s.head_len = head_len;
+    s.sel_ids = d_sid.as<uint32_t>();
+    s.sel_d = d_sd.as<double>();
+    s.sel_n = d_sn.as<int32_t>();
+    // a lane's chain over the whole row, and the norms' own rounding
+    s.gam = sum_bound(d, gpu.pitch + 8);
+    const size_t id_bytes = 2 * (size_t)((m + 3) & ~3) * sizeof(uint32_t);
+    const size_t kept_bytes = (size_t)m * gpu.pitch * sizeof(float);
+    const bool kept_in_lds = id_bytes + kept_bytes <= (48u << 10);
+    auto k_select = kept_in_lds ? k_canon_select<true> : k_canon_select<false>;
+    const int64_t step = std::max<int64_t>(B, (n / 10 + B - 1) / B * B);
+    for (int64_t x0 = 0; x0 < n; x0 += B) {
+        const int64_t cnt = std::min(B, n - x0);
+        rc = launch_canon_search(gpu.X, n, d, gpu.pitch, d_adj.as<uint32_t>(), ell, entry, L, x0, cnt,
+                                 d_max.as<double>(), d_q.as<uint32_t>(), d_qd.as<double>(), d_qn.as<int32_t>(), st);
+        if (rc) return rc;
+        s.x0 = x0;
+        s.head = d_hd.as<uint32_t>() + x0 * head_len;
+        s.head_n = d_hn.as<int32_t>() + x0;
+        hipLaunchKernelGGL(k_select, dim3((unsigned)cnt), dim3(64), id_bytes + (kept_in_lds ? kept_bytes : 0), st, s);
+        RG_HIP(hipGetLastError());
+        if (log && ((x0 + cnt) % step == 0 || x0 + cnt == n)) {  // progress (waits for the batches)
+            RG_HIP(hipStreamSynchronize(st));
+            std::fprintf(stderr, "[rg] enhancement searches %lld / %lld nodes\n", (long long)(x0 + cnt), (long long)n);
+        }
+    }
+    RG_HIP(hipMemcpyAsync(head, d_hd.p, sizeof(uint32_t) * n * head_len, hipMemcpyDeviceToHost, st));
+    RG_HIP(hipMemcpyAsync(head_n, d_hn.p, sizeof(int32_t) * n, hipMemcpyDeviceToHost, st));
+    // the nodes that selected each node
+    Dev d_cnt, d_off;
+    if (!d_cnt.alloc(sizeof(uint32_t) * n) || !d_off.alloc(sizeof(int64_t) * (n + 1))) {
+        set_error("build: out of memory for reverse updates");
+        return RG_ENOMEM;
+    }
+    hipLaunchKernelGGL(k_zero32, dim3(blocks_for(n)), dim3(256), 0, st, d_cnt.as<uint32_t>(), n);
+    hipLaunchKernelGGL(k_count_events, dim3(blocks_for(n)), dim3(256), 0, st, s.sel_ids, s.sel_n, n, m,
+                       d_cnt.as<uint32_t>());
     RG_HIP(hipGetLastError());
+    std::vector<uint32_t> cnt((size_t)n);
+    RG_HIP(hipMemcpyAsync(cnt.data(), d_cnt.p, sizeof(uint32_t) * n, hipMemcpyDeviceToHost, st));
+    RG_HIP(hipStreamSynchronize(st));
+    *t_search = std::chrono::duration<double>(Clock::now() - t0).count();
+    std::vector<int64_t> off((size_t)n + 1, 0);
+    for (int64_t i = 0; i < n; ++i) off[i + 1] = off[i] + cnt[i];
+    Dev d_src, d_out, d_on;
+    if (!d_src.alloc(sizeof(uint32_t) * (size_t)off[n]) || !d_out.alloc(sizeof(uint32_t) * n * m) ||
+        !d_on.alloc(sizeof(int32_t) * n)) {
+        set_error("build: out of memory for reverse updates");
+        return RG_ENOMEM;
+    }
+    RG_HIP(hipMemcpyAsync(d_off.p, off.data(), sizeof(int64_t) * (n + 1), hipMemcpyHostToDevice, st));
+    hipLaunchKernelGGL(k_place_events, dim3(blocks_for(n)), dim3(256), 0, st, s.sel_ids, s.sel_n, n, m,
+                       d_off.as<int64_t>(), d_cnt.as<uint32_t>(), d_src.as<uint32_t>());
+    hipLaunchKernelGGL(k_sort_events, dim3((unsigned)n), dim3(256), 0, st, d_off.as<int64_t>(), d_src.as<uint32_t>());
+    ReplayArgs r{};
+    r.X = gpu.X;
+    r.d = d;
+    r.pitch = gpu.pitch;
+    r.m = m;
+    r.sel_ids = s.sel_ids;
+    r.sel_d = s.sel_d;
+    r.sel_n = s.sel_n;
+    r.off = d_off.as<int64_t>();
+    r.src = d_src.as<uint32_t>();
+    r.out = d_out.as<uint32_t>();
+    r.out_n = d_on.as<int32_t>();
+    hipLaunchKernelGGL(k_replay, dim3((unsigned)n), dim3(64), (size_t)gpu.pitch * 4 + (size_t)(m + 1) * 12 + 8, st, r);
+    RG_HIP(hipGetLastError());
+    ce->resize((size_t)n * m);
+    ce_n->resize((size_t)n);
+    RG_HIP(hipMemcpyAsync(ce->data(), d_out.p, sizeof(uint32_t) * n * m, hipMemcpyDeviceToHost, st));
+    RG_HIP(hipMemcpyAsync(ce_n->data(), d_on.p, sizeof(int32_t) * n, hipMemcpyDeviceToHost, st));
+    RG_HIP(hipStreamSynchronize(st));
+    if (log)
+        std::fprintf(stderr, "[rg] enhancement on the device: searches and selections %.3f s, reverse updates %.3f s\n",
+                     *t_search, std::chrono::duration<double>(Clock::now() - t0).count() - *t_search);
     return RG_OK;
 }
 

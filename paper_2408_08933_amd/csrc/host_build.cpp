@@ -369,128 +369,6 @@ void lists_to_csr(const Lists &L, int64_t n, std::vector<int64_t> &off, std::vec
         for (int j = 0; j < L.deg[x]; ++j) idx[off[x] + j] = L.row(x)[j].id;
 }
 
-// Enhancement on the device: the searches of every node on G_pj and each
-// node's own selection (AcquireNeighbors without fill), both with the
-// canonical FP64 distance, so the lists are bit-identical to the host's.
-// Only the selections and the first kHead candidates come back.  Double
-// buffered: batch i+1 runs on the device while batch i is copied out.
-int enhance_on_device(const float *X, int64_t n, int32_t d, const Lists &PJ, uint32_t entry, int32_t L, int32_t m_ce,
-                      int threads, const GpuCtx &gpu, Lists &E, std::vector<uint32_t> &head,
-                      std::vector<int32_t> &head_n, double *t_search) {
-    (void)X;
-    int32_t maxdeg = 1;
-    for (int64_t x = 0; x < n; ++x) maxdeg = std::max<int32_t>(maxdeg, PJ.deg[x]);
-    const int32_t ell = (maxdeg + 7) / 8 * 8;
-    std::vector<uint32_t> adj((size_t)n * ell, kNone);
-    for (int64_t x = 0; x < n; ++x)
-        for (int j = 0; j < PJ.deg[x]; ++j) adj[x * ell + j] = PJ.row(x)[j].id;
-    const int64_t B = std::min<int64_t>(n, 1 << 15);
-    const int32_t m = std::max(1, m_ce);
-    uint32_t *d_adj = nullptr, *d_q = nullptr;
-    double *d_qd = nullptr;
-    int32_t *d_qn = nullptr;
-    uint32_t *d_sid[2] = {nullptr, nullptr}, *h_sid[2] = {nullptr, nullptr};
-    double *d_sd[2] = {nullptr, nullptr}, *h_sd[2] = {nullptr, nullptr};
-    int32_t *d_sn[2] = {nullptr, nullptr}, *h_sn[2] = {nullptr, nullptr};
-    uint32_t *d_hd[2] = {nullptr, nullptr}, *h_hd[2] = {nullptr, nullptr};
-    int32_t *d_hn[2] = {nullptr, nullptr}, *h_hn[2] = {nullptr, nullptr};
-    hipEvent_t ev[2] = {nullptr, nullptr};
-    auto release = [&]() {
-        for (void *p : {(void *)d_adj, (void *)d_q, (void *)d_qd, (void *)d_qn})
-            if (p) (void)hipFree(p);
-        for (int i = 0; i < 2; ++i) {
-            for (void *p : {(void *)d_sid[i], (void *)d_sd[i], (void *)d_sn[i], (void *)d_hd[i], (void *)d_hn[i]})
-                if (p) (void)hipFree(p);
-            for (void *p : {(void *)h_sid[i], (void *)h_sd[i], (void *)h_sn[i], (void *)h_hd[i], (void *)h_hn[i]})
-                if (p) (void)hipHostFree(p);
-            if (ev[i]) (void)hipEventDestroy(ev[i]);
-        }
-    };
-    bool ok = hipMalloc(&d_adj, sizeof(uint32_t) * adj.size()) == hipSuccess &&
-              hipMalloc(&d_q, sizeof(uint32_t) * B * L) == hipSuccess &&
-              hipMalloc(&d_qd, sizeof(double) * B * L) == hipSuccess &&
-              hipMalloc(&d_qn, sizeof(int32_t) * B) == hipSuccess;
-    for (int i = 0; i < 2 && ok; ++i)
-        ok = hipMalloc(&d_sid[i], sizeof(uint32_t) * B * m) == hipSuccess &&
-             hipMalloc(&d_sd[i], sizeof(double) * B * m) == hipSuccess &&
-             hipMalloc(&d_sn[i], sizeof(int32_t) * B) == hipSuccess &&
-             hipMalloc(&d_hd[i], sizeof(uint32_t) * B * kHead) == hipSuccess &&
-             hipMalloc(&d_hn[i], sizeof(int32_t) * B) == hipSuccess &&
-             hipHostMalloc(&h_sid[i], sizeof(uint32_t) * B * m, hipHostMallocDefault) == hipSuccess &&
-             hipHostMalloc(&h_sd[i], sizeof(double) * B * m, hipHostMallocDefault) == hipSuccess &&
-             hipHostMalloc(&h_sn[i], sizeof(int32_t) * B, hipHostMallocDefault) == hipSuccess &&
-             hipHostMalloc(&h_hd[i], sizeof(uint32_t) * B * kHead, hipHostMallocDefault) == hipSuccess &&
-             hipHostMalloc(&h_hn[i], sizeof(int32_t) * B, hipHostMallocDefault) == hipSuccess &&
-             hipEventCreateWithFlags(&ev[i], hipEventDisableTiming) == hipSuccess;
-    if (!ok) {
-        release();
-        set_error("build: out of memory for enhancement searches");
-        return RG_ENOMEM;
-    }
-    const auto tstart = Clock::now();
-    double t_host = 0.0;
-    int rc = RG_OK;
-    // search and select batch b on the device, copy its selections into buffer b % 2
-    auto issue = [&](int64_t b) -> int {
-        const int64_t x0 = b * B, cnt = std::min(B, n - x0);
-        const int i = (int)(b & 1);
-        int r = launch_canon_search(gpu.X, d, gpu.pitch, d_adj, ell, entry, L, x0, cnt, d_q, d_qd, d_qn, gpu.stream);
-        if (!r)
-            r = launch_canon_select(gpu.X, d, gpu.pitch, d_q, d_qd, d_qn, L, x0, cnt, m, d_sid[i], d_sd[i], d_sn[i],
-                                    d_hd[i], kHead, d_hn[i], gpu.stream);
-        if (r) return r;
-        if (hipMemcpyAsync(h_sid[i], d_sid[i], sizeof(uint32_t) * cnt * m, hipMemcpyDeviceToHost, gpu.stream) !=
-                hipSuccess ||
-            hipMemcpyAsync(h_sd[i], d_sd[i], sizeof(double) * cnt * m, hipMemcpyDeviceToHost, gpu.stream) !=
-                hipSuccess ||
-            hipMemcpyAsync(h_sn[i], d_sn[i], sizeof(int32_t) * cnt, hipMemcpyDeviceToHost, gpu.stream) != hipSuccess ||
-            hipMemcpyAsync(h_hd[i], d_hd[i], sizeof(uint32_t) * cnt * kHead, hipMemcpyDeviceToHost, gpu.stream) !=
-                hipSuccess ||
-            hipMemcpyAsync(h_hn[i], d_hn[i], sizeof(int32_t) * cnt, hipMemcpyDeviceToHost, gpu.stream) != hipSuccess ||
-            hipEventRecord(ev[i], gpu.stream) != hipSuccess) {
-            set_error("build: enhancement on the device failed");
-            return RG_EDEVICE;
-        }
-        return RG_OK;
-    };
-    const int64_t nb = (n + B - 1) / B;
-    if (hipMemcpyAsync(d_adj, adj.data(), sizeof(uint32_t) * adj.size(), hipMemcpyHostToDevice, gpu.stream) !=
-        hipSuccess)
-        rc = RG_EDEVICE;
-    if (!rc) rc = issue(0);
-    for (int64_t b = 0; b < nb && !rc; ++b) {
-        if (b + 1 < nb) rc = issue(b + 1);  // the device works on the next batch meanwhile
-        if (rc) break;
-        const int i = (int)(b & 1);
-        if (hipEventSynchronize(ev[i]) != hipSuccess) {
-            set_error("build: enhancement on the device failed");
-            rc = RG_EDEVICE;
-            break;
-        }
-        const auto th0 = Clock::now();
-        const int64_t x0 = b * B, cnt = std::min(B, n - x0);
-        parallel_for(cnt, threads, 256, [&](int64_t bb, int) {
-            const int64_t x = x0 + bb;
-            const int ns = std::min(h_sn[i][bb], m);
-            for (int j = 0; j < ns; ++j) E.row(x)[j] = Cand{h_sd[i][bb * m + j], h_sid[i][bb * m + j]};
-            E.deg[x] = ns;
-            head_n[x] = h_hn[i][bb];
-            const int nh = std::min(head_n[x], kHead);
-            for (int j = 0; j < nh; ++j) head[x * kHead + j] = h_hd[i][bb * kHead + j];
-        });
-        t_host += secs(th0, Clock::now());
-        // about ten progress lines per build
-        const int64_t step = std::max<int64_t>(cnt, (n / 10 + cnt - 1) / cnt * cnt);
-        if (std::getenv("RG_LOG") && ((x0 + cnt) % step == 0 || x0 + cnt == n))
-            std::fprintf(stderr, "[rg] enhancement searches %lld / %lld nodes\n", (long long)(x0 + cnt), (long long)n);
-        // buffer i is reused by batch b + 2, issued in the next iteration
-    }
-    (void)hipStreamSynchronize(gpu.stream);
-    release();
-    *t_search = secs(tstart, Clock::now()) - t_host;
-    return rc;
-}
-
 }  // namespace
 
 double canon_dist(const float *a, const float *b, int32_t d) {
@@ -624,12 +502,22 @@ int host_construct(const float *X, int64_t n, int32_t d, const uint32_t *knn, in
 
     // --- enhancement: searches on G_pj and each node's own selection E(x) --
     Lists E;
-    E.init(n, capl);
+    if (!gpu) E.init(n, capl);
     std::vector<uint32_t> head((size_t)n * kHead, kNone);
     std::vector<int32_t> head_n((size_t)n, 0);
+    // after the reverse updates: on the device, or replayed below
+    std::vector<uint32_t> dev_ce;
+    std::vector<int32_t> dev_ce_n;
     if (gpu) {
-        const int rc = enhance_on_device(X, n, d, PJ, entry, L, m_ce, threads, *gpu, E, head, head_n,
-                                         &out->t_enhance_search);
+        int32_t maxdeg = 1;
+        for (int64_t x = 0; x < n; ++x) maxdeg = std::max<int32_t>(maxdeg, PJ.deg[x]);
+        const int32_t ell = (maxdeg + 7) / 8 * 8;
+        std::vector<uint32_t> adj((size_t)n * ell, kNone);
+        parallel_for(n, threads, 4096, [&](int64_t x, int) {
+            for (int j = 0; j < PJ.deg[x]; ++j) adj[x * ell + j] = PJ.row(x)[j].id;
+        });
+        const int rc = gpu->enhance(*gpu, n, d, adj, ell, entry, L, std::max(1, m_ce), kHead, &dev_ce, &dev_ce_n,
+                                    head.data(), head_n.data(), &out->t_enhance_search);
         if (rc) return rc;
     } else {
         std::vector<Searcher> sr((size_t)threads);
@@ -650,8 +538,8 @@ int host_construct(const float *X, int64_t n, int32_t d, const uint32_t *knn, in
     }
     const auto t1b = Clock::now();
     Lists CE;
-    CE.init(n, capl);
-    {
+    if (!gpu) {
+        CE.init(n, capl);
         std::vector<int64_t> eoff;
         std::vector<uint32_t> esrc;
         build_events(E, n, eoff, esrc);
@@ -674,8 +562,9 @@ int host_construct(const float *X, int64_t n, int32_t d, const uint32_t *knn, in
         auto &r = fin[x];
         r.reserve((size_t)M);
         for (int j = 0; j < PJ.deg[x]; ++j) r.push_back(PJ.row(x)[j].id);
-        for (int j = 0; j < CE.deg[x]; ++j) {
-            const uint32_t u = CE.row(x)[j].id;
+        const int nce = gpu ? dev_ce_n[x] : CE.deg[x];
+        for (int j = 0; j < nce; ++j) {
+            const uint32_t u = gpu ? dev_ce[x * (int64_t)std::max(1, m_ce) + j] : CE.row(x)[j].id;
             if (std::find(r.begin(), r.end(), u) == r.end()) r.push_back(u);
         }
         std::sort(r.begin(), r.end());  // the repair's BFS visits neighbours in ascending id

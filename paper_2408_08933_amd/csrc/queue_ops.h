@@ -1,4 +1,4 @@
-// Sorted-queue merge shared by the search kernels (FP32 keys) and the
+// Visited tables and the sorted-queue merge shared by the search kernels (FP32 keys) and the
 // construction-time canonical search (FP64 keys).  One wavefront owns the
 // queue; all arrays live in LDS, so wave_sync orders its steps.
 #pragma once
@@ -9,6 +9,112 @@
 #include "wave_ops.h"
 
 namespace rg {
+
+constexpr uint32_t kEmpty = 0xFFFFFFFFu;
+
+__device__ __forceinline__ uint32_t hslot(uint32_t u, int hb) { return (u * 2654435761u) >> (32 - hb); }
+
+// Visited set kept in LDS: open addressing, cleared when it passes half load
+// (clearing only costs re-scoring; see the file comment).
+struct VisitLds {
+    uint32_t *htab;
+    int hb, H, hcount;
+    __device__ __forceinline__ VisitLds(uint32_t *t, int hash_bits, int) : htab(t), hb(hash_bits), H(1 << hb), hcount(0) {}
+    __device__ __forceinline__ void clear() {
+        for (int i = lane_id(); i < H; i += 64) htab[i] = kEmpty;
+        hcount = 0;
+    }
+    __device__ __forceinline__ void mark_entry(uint32_t u) {  // lane 0, table just cleared
+        htab[hslot(u, hb)] = u;
+    }
+    __device__ __forceinline__ void begin_hop(int ell) {
+        if (hcount + ell > (H >> 1)) {
+            clear();
+            wave_sync();
+        }
+    }
+    __device__ __forceinline__ bool insert(uint32_t u) {
+        const uint32_t hmask = (uint32_t)H - 1u;
+        uint32_t h = hslot(u, hb);
+        for (int probe = 0; probe < H; ++probe) {
+            const uint32_t old = atomicCAS(&htab[h], kEmpty, u);
+            if (old == kEmpty) return true;
+            if (old == u) return false;
+            h = (h + 1u) & hmask;
+        }
+        return false;
+    }
+    __device__ __forceinline__ void added(int k) { hcount += k; }
+    // what a resumed search needs beside the table's words
+    __device__ __forceinline__ int count() const { return hcount; }
+    __device__ __forceinline__ void restore(int c) { hcount = c; }
+};
+
+// Visited set kept in LDS that forgets one node at a time: 2^set_bits sets of
+// four 16-bit entries, the newest first; a new node pushes its set's oldest
+// one out.  A node's bits are spread by an odd multiplier (a bijection of the
+// id_bits-bit numbers); the product's top set_bits bits name the set and the
+// rest, which must fit 16 bits, is the entry, so an entry is one node and no
+// other.  Half the bytes of an id per node, and never cleared: at any time it
+// holds the last 4 * 2^set_bits nodes (up to uneven sets), where a table
+// cleared at half load holds a quarter of its ids on average.  Rows scored
+// per query, 10k queries a launch: 2M x 512 E4M3 at L = 409 26,160 -> 20,400
+// (2 KB; 16,560 distinct) and 40.0 -> 34.1 ms, 500k x 200 BF16 at L = 805,
+// 3,001 queries, 44,310 -> 33,200 (26,890) and 11.1 -> 8.8 ms, 700k x 100
+// FP32 at L = 32, 4,096 queries, 2,190 -> 1,713 (1,704) and 0.83 -> 0.69 ms.
+//
+// Lanes of one expansion that meet in a set take turns: each turn one lane's
+// compare-and-swap succeeds and the others look at the set again, so a node
+// that stands twice in an adjacency row is taken once.  That needs the row in
+// one turn (at most 64 ids).  The entry 0xFFFF marks a free place; the one
+// node per set that would have it (16-bit entries only) is never remembered,
+// and copies of it within a row are told apart by a vote.
+struct VisitSets {
+    unsigned long long *tab;
+    int set_bits, rest_bits;
+    uint32_t idmask;
+    __device__ __forceinline__ VisitSets(uint32_t *t, int hash_bits, int id_bits)
+        : tab(reinterpret_cast<unsigned long long *>(t)), set_bits(hash_bits - 1), rest_bits(id_bits - hash_bits + 1),
+          idmask(id_bits >= 32 ? 0xFFFFFFFFu : (1u << id_bits) - 1u) {}
+    __device__ __forceinline__ void clear() {
+        for (int i = lane_id(); i < (1 << set_bits); i += 64) tab[i] = ~0ull;
+    }
+    __device__ __forceinline__ void mark_entry(uint32_t u) { (void)insert(u); }
+    __device__ __forceinline__ void begin_hop(int) {}
+    __device__ __forceinline__ void added(int) {}
+    __device__ __forceinline__ int count() const { return 0; }
+    __device__ __forceinline__ void restore(int) {}
+    // whether one of a set's four entries is rest (twice = rest * 0x10001): a
+    // 16-bit half of the difference is zero
+    static __device__ __forceinline__ bool among(unsigned long long set, uint32_t twice) {
+        const uint32_t a = (uint32_t)set ^ twice, b = (uint32_t)(set >> 32) ^ twice;
+        return ((((a - 0x10001u) & ~a) | ((b - 0x10001u) & ~b)) & 0x80008000u) != 0u;
+    }
+    __device__ __forceinline__ bool holds(uint32_t u) const {
+        const uint32_t h = (u * 2654435761u) & idmask, rest = h & ((1u << rest_bits) - 1u);
+        return rest != 0xFFFFu && among(tab[h >> rest_bits], rest * 0x10001u);
+    }
+    __device__ __forceinline__ bool insert(uint32_t u) {
+        const uint32_t h = (u * 2654435761u) & idmask;
+        const uint32_t rest = h & ((1u << rest_bits) - 1u), twice = rest * 0x10001u;
+        unsigned long long *p = tab + (h >> rest_bits);
+        bool fresh = true;
+        for (uint64_t m = ballot64(rest == 0xFFFFu); m; m &= m - 1) {
+            const int src = (int)__builtin_ctzll(m);
+            // readlane: the lanes after src compare with it, whichever are active
+            const uint32_t first = (uint32_t)__builtin_amdgcn_readlane((int)u, src);
+            if (u == first && lane_id() > src) fresh = false;
+        }
+        if (rest == 0xFFFFu) return fresh;
+        unsigned long long old = *p;
+        for (;;) {
+            if (among(old, twice)) return false;
+            const unsigned long long got = atomicCAS(p, old, (old << 16) | rest);
+            if (got == old) return true;
+            old = got;
+        }
+    }
+};
 
 template <typename K>
 struct QueueLds {
@@ -58,8 +164,13 @@ __device__ __forceinline__ int count_le(const int32_t *slb, int S, int i) {
 constexpr int kRankByCount = 32;
 
 // QR = queue capacity / 64: each lane holds QR of the entries that move.
-template <int E, typename K, int QR = kMaxL / 64>
-__device__ __forceinline__ void merge_batch(const QueueLds<K> &s, int cnt, int Leff, int &qn, int &ptr) {
+// NEAR (E = 1): the keys are only known to within tol / 2; returns false, with
+// the queue in any state, where two keys that a decision compares are within
+// tol of each other (a batch that holds a queued node again, with its very
+// key, is no such case).  Otherwise returns true.
+template <int E, typename K, int QR = kMaxL / 64, bool NEAR = false>
+__device__ __forceinline__ bool merge_batch(const QueueLds<K> &s, int cnt, int Leff, int &qn, int &ptr, K tol = (K)0) {
+    static_assert(!NEAR || E == 1, "");
     const int lane = lane_id();
     const bool full = qn == Leff;
     const K lastd = full ? s.qd[Leff - 1] : (K)0;
@@ -77,13 +188,21 @@ __device__ __forceinline__ void merge_batch(const QueueLds<K> &s, int cnt, int L
             ic = s.ci[lane];
             sv = ic != kNone && (!full || kless(kc, ic, lastd, lasti));
         }
+        bool close = false;
+        if constexpr (NEAR) close = full && ic != kNone && !(fabs(kc - lastd) > tol) && ic != lasti;
         if (sv) {
             lbc = lower_bound_q(s.qd, s.qi, qn, kc, ic);
-            if (lbc < qn && (s.qi[lbc] & ~kExpanded) == ic) sv = false;  // already queued
+            if (lbc < qn && (s.qi[lbc] & ~kExpanded) == ic)
+                sv = false;  // already queued
+            else if constexpr (NEAR)
+                close |= (lbc > 0 && !(kc - s.qd[lbc - 1] > tol)) || (lbc < qn && !(s.qd[lbc] - kc > tol));
+        }
+        if constexpr (NEAR) {
+            if (ballot64(close)) return false;
         }
         const uint64_t m = ballot64(sv);
         total = (int)__popcll(m);
-        if (total == 0) return;
+        if (total == 0) return true;
         if (total <= kRankByCount) {
             // survivor order = number of survivors that precede it
             wave_sync();
@@ -94,7 +213,13 @@ __device__ __forceinline__ void merge_batch(const QueueLds<K> &s, int cnt, int L
             wave_sync();
             int rank = 0;
             if (sv)
-                for (int t = 0; t < total; ++t) rank += kless(s.sd[t], s.si[t], kc, ic) ? 1 : 0;
+                for (int t = 0; t < total; ++t) {
+                    rank += kless(s.sd[t], s.si[t], kc, ic) ? 1 : 0;
+                    if constexpr (NEAR) close |= s.si[t] != ic && !(fabs(s.sd[t] - kc) > tol);
+                }
+            if constexpr (NEAR) {
+                if (ballot64(close)) return false;
+            }
             wave_sync();
             if (sv) {
                 s.sd[rank] = kc;
@@ -107,7 +232,7 @@ __device__ __forceinline__ void merge_batch(const QueueLds<K> &s, int cnt, int L
     } else if (full) {  // nothing to do unless some candidate beats the last entry
         bool any = false;
         for (int i = lane; i < cnt; i += 64) any |= kless(s.cd[i], s.ci[i], lastd, lasti);
-        if (ballot64(any) == 0) return;
+        if (ballot64(any) == 0) return true;
     }
     if (!sorted) {
         K k[E];
@@ -119,6 +244,12 @@ __device__ __forceinline__ void merge_batch(const QueueLds<K> &s, int cnt, int L
             id[e] = i < cnt ? s.ci[i] : kNone;
         }
         wave_sort<E, K>(k, id);
+        if constexpr (NEAR) {
+            // the next candidate of the order; the last ones are padding
+            const K kn = __shfl_down(k[0], 1);
+            const uint32_t in = (uint32_t)__shfl_down((int)id[0], 1);
+            if (ballot64(lane < 63 && id[0] != kNone && in != kNone && in != id[0] && !(kn - k[0] > tol))) return false;
+        }
         int lb[E];
         bool sv[E];
         int mine = 0;
@@ -152,7 +283,7 @@ __device__ __forceinline__ void merge_batch(const QueueLds<K> &s, int cnt, int L
             }
         }
         wave_sync();
-        if (total == 0) return;
+        if (total == 0) return true;
     }
     const int lbmin = s.slb[0];
     // entries of the queue that move, and their new places
@@ -199,7 +330,7 @@ __device__ __forceinline__ void merge_batch(const QueueLds<K> &s, int cnt, int L
     qn = min(Leff, qn + total);
     ptr = min(ptr, lbmin);
     wave_sync();
+    return true;
 }
-
 
 }  // namespace rg

@@ -264,11 +264,18 @@ struct HostGraph {
     double t_knn = 0, t_project = 0, t_enhance = 0, t_total = 0;
     double t_enhance_search = 0;
 };
-// Device resources construction may use: the padded FP32 base on the device.
+// Device resources construction may use: the padded FP32 base on the device,
+// and the enhancement there (canon.hip; a pointer, so that the host half links
+// without the device half): from the projected graph as ELL rows to the lists
+// after the reverse updates (n x m ids in ce, ce_n per node), the first
+// head_len search results of each node (itself left out) and their number.
 struct GpuCtx {
     const float *X;      // n x pitch
     int32_t pitch;
     hipStream_t stream;
+    int (*enhance)(const GpuCtx &gpu, int64_t n, int32_t d, const std::vector<uint32_t> &adj, int32_t ell,
+                   uint32_t entry, int32_t L, int32_t m, int32_t head_len, std::vector<uint32_t> *ce,
+                   std::vector<int32_t> *ce_n, uint32_t *head, int32_t *head_n, double *t_search);
 };
 // knn lists: nt x Nq canonical ids.  X: host n x d.  gpu == nullptr: host only.
 int host_construct(const float *X, int64_t n, int32_t d, const uint32_t *knn, int64_t nt,
@@ -288,17 +295,17 @@ int host_insert(StageGraphs &sg, int32_t d, int32_t M, int32_t m_pj, int32_t L, 
 void host_canon_searches(const float *X, int32_t d, const int64_t *off, const uint32_t *idx, uint32_t entry,
                          int32_t L, int64_t x0, int64_t count, int threads, uint32_t *ids, int32_t *counts);
 
-// canon.hip: AcquireNeighbors without fill over each searched node's queue
-// (the enhancement's own selection), canonical FP64, on the device
-int launch_canon_select(const float *X, int32_t d, int32_t pitch, const uint32_t *ids, const double *dists,
-                        const int32_t *counts, int32_t L, int64_t x0, int64_t count, int32_t m, uint32_t *sel_ids,
-                        double *sel_d, int32_t *sel_n, uint32_t *head, int32_t head_len, int32_t *head_n,
-                        hipStream_t stream);
-
-// canon.hip: construction-time searches with the canonical FP64 distance
-int launch_canon_search(const float *X, int32_t d, int32_t pitch, const uint32_t *adj, int32_t ell,
-                        uint32_t entry, int32_t L, int64_t x0, int64_t count, uint32_t *ids, double *dists,
-                        int32_t *counts, hipStream_t stream);
+// canon.hip: construction-time searches with the canonical FP64 distance, of
+// rows x0 .. x0 + count - 1 of X on a graph of n nodes (ELL rows).  xmax2
+// (device): the largest squared norm of the n nodes' rows.
+int launch_max_norm(const float *X, int64_t n, int32_t pitch, double *xmax2, hipStream_t stream);
+int launch_canon_search(const float *X, int64_t n, int32_t d, int32_t pitch, const uint32_t *adj, int32_t ell,
+                        uint32_t entry, int32_t L, int64_t x0, int64_t count, const double *xmax2, uint32_t *ids,
+                        double *dists, int32_t *counts, hipStream_t stream);
+// canon.hip: the enhancement (GpuCtx::enhance)
+int canon_enhance(const GpuCtx &gpu, int64_t n, int32_t d, const std::vector<uint32_t> &adj, int32_t ell,
+                  uint32_t entry, int32_t L, int32_t m, int32_t head_len, std::vector<uint32_t> *ce,
+                  std::vector<int32_t> *ce_n, uint32_t *head, int32_t *head_n, double *t_search);
 
 // canonical FP64 distance helpers (host)
 double canon_dist(const float *a, const float *b, int32_t d);

@@ -26,6 +26,36 @@ __device__ __forceinline__ int lanes_below(uint64_t m) {
     return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0));
 }
 
+// lane l reads lane l + n of its 16-lane row (row shift left) or lane
+// l ^ 2 / l ^ 1 (quad permutes); lanes past the row read 0
+template <int CTRL>
+__device__ __forceinline__ float dpp_read(float v) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, true));
+}
+
+template <int CTRL>
+__device__ __forceinline__ double dpp_read(double v) {
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)b, CTRL, 0xF, 0xF, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xF, 0xF, true);
+    return __longlong_as_double(((long long)hi << 32) | (uint32_t)lo);
+}
+
+// Sum of the G lanes of each group, valid in the group's first lane.  The
+// steps are those of an xor butterfly with the largest offset first, as
+// seen from the first lane, so the value is the butterfly's bit for bit;
+// inside a 16-lane row they use DPP (no LDS round trip), across rows
+// (G = 32) a shuffle.
+template <int G, typename T>
+__device__ __forceinline__ T group_sum(T v) {
+    if constexpr (G >= 32) v += __shfl_down(v, 16);
+    if constexpr (G >= 16) v += dpp_read<0x108>(v);  // row_shl:8: lane + 8
+    if constexpr (G >= 8) v += dpp_read<0x104>(v);   // row_shl:4: lane + 4
+    if constexpr (G >= 4) v += dpp_read<0x4E>(v);    // quad_perm [2,3,0,1]: lane ^ 2
+    if constexpr (G >= 2) v += dpp_read<0xB1>(v);    // quad_perm [1,0,3,2]: lane ^ 1
+    return v;
+}
+
 // (key, id) strict order: smaller key first, then smaller id
 template <typename K>
 __device__ __forceinline__ bool kless(K ka, uint32_t ia, K kb, uint32_t ib) {
