@@ -154,9 +154,12 @@ namespace {
 // x 1e-3) at 20 / 16 / 11 workgroups per CU, BF16 d = 128 0.54 / 0.67 at 24 /
 // 16, and counts between two multiples of 4 run like the lower one (a SIMD
 // more or less).  The LDS is handed out in 1,280-byte pieces, which the
-// occupancy query leaves out.  BF16 rows of 768 bytes and more wait for
-// bandwidth instead (d = 512: 1.54 / 1.61 / 1.55 at 20 / 18 / 14) and take the
-// largest table.
+// occupancy query leaves out.  Rows of d > 256 keep more loads in flight on
+// fewer wavefronts, so rescoring costs them more than the wavefronts do: they
+// take the largest table (4 / 2 / 1 KB, ms for 10,000 queries: E4M3 2M x 512
+// L = 409 29.4 / 30.4 / 31.6, 1M x 384 L = 300 17.3 / 18.0 / 18.6; BF16 1M x
+// 512 L = 409 28.1 / 30.2 / 32.4; 300k x 1000 L = 200, 5,000 queries 13.0 /
+// 14.2 / 15.5).
 int choose_table(SearchArgs &a, int cus) {
     const int width = a.adj_off ? kMaxEll : a.ell;  // ids inserted per batch
     const int64_t want = (a.nq + cus - 1) / std::max(1, cus);
@@ -175,7 +178,7 @@ int choose_table(SearchArgs &a, int cus) {
             occ = o;
             best = hb;
         }
-        if (hb == 10 && a.storage == RG_STORE_BF16 && a.d >= 384 && o >= 12) break;
+        if (hb == 10 && a.d > 256 && o >= 8) break;
     }
     set_table(a, best);
     return RG_OK;

@@ -110,7 +110,15 @@ constexpr int shape_nch(int st, int cls) {
     constexpr int n32[6] = {1, 2, 7, 4, 8, 8}, n16[6] = {1, 1, 4, 4, 4, 4}, n8[6] = {2, 2, 2, 3, 3, 3};
     return st == RG_STORE_FP32 ? n32[cls] : st == RG_STORE_BF16 ? n16[cls] : n8[cls];
 }
-constexpr int shape_r(int st, int cls) { return st == RG_STORE_FP8E4M3 && cls <= 2 ? 4 : 2; }
+// R: what the registers hold beside the chunks.  With four rows in flight the
+// BF16 and E4M3 shapes of d > 256 need the registers of 4 wavefronts per SIMD
+// instead of 5, and are faster all the same, as each wavefront waits half as
+// often (10,000 queries, 4 KB of visited set, two rows -> four, ms: E4M3 2M x
+// 512 L = 409 33.6 -> 29.4, 1M x 512 L = 150 11.9 -> 11.1, 1M x 384 L = 300
+// 18.6 -> 17.3; BF16 1M x 512 L = 409 27.8 -> 27.7, L = 805 55.2 -> 54.1).  At
+// d <= 256 the fifth wavefront is worth more (E4M3 1M x 256 L = 409, 1 KB:
+// 14.7 -> 17.8).
+constexpr int shape_r(int st, int cls) { return (st == RG_STORE_FP8E4M3 && cls <= 2) || (st != RG_STORE_FP32 && cls >= 4) ? 4 : 2; }
 
 // Copy the query into LDS, zero padded to qpad (every element a row chunk
 // can reach, so bytes past d meet a zero).
@@ -470,7 +478,7 @@ __device__ __forceinline__ void write_result(const SearchArgs &a, const Lds &s, 
 // VIS: VisitSets, or VisitLds (rg_search_hashbits, wide rows, huge bases).
 template <int ST, int CLS, int QR, class VIS>
 __global__ __launch_bounds__(64)
-__attribute__((amdgpu_waves_per_eu(ST == RG_STORE_FP32 || QR > kMaxL / 64 ? 4 : 5))) void k_search(SearchArgs a) {
+__attribute__((amdgpu_waves_per_eu(ST == RG_STORE_FP32 || QR > kMaxL / 64 || CLS >= 4 ? 4 : 5))) void k_search(SearchArgs a) {
     extern __shared__ __align__(16) unsigned char smem[];
     const int64_t q = blockIdx.x;
     const Lds s = carve(smem, a.Leff, a.qpad, a.cand);
@@ -522,7 +530,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
 // search in progress; -1 = finished (its record written; the slot is
 // skipped until the host admits a new request into it).
 template <int ST, int CLS, class VIS>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5))) void k_serve_step(SlotArgs sa) {
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(ST == RG_STORE_FP32 || CLS >= 4 ? 4 : 5))) void k_serve_step(SlotArgs sa) {
     extern __shared__ __align__(16) unsigned char smem[];
     const int slot = sa.active[blockIdx.x];
     if (sa.slot_state[(size_t)slot * 8] < 0) return;
