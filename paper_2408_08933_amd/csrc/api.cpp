@@ -42,8 +42,10 @@ void par_rows(int64_t n, int threads, F &&f) {
 
 struct DevBuf {
     void *p = nullptr;
-    ~DevBuf() {
+    ~DevBuf() { release(); }
+    void release() {
         if (p) (void)hipFree(p);
+        p = nullptr;
     }
     int alloc(size_t bytes) {
         if (hipMalloc(&p, bytes ? bytes : 1) != hipSuccess) {
@@ -520,17 +522,19 @@ int rg_build(const float *base, int64_t n, int32_t d, const float *train, int64_
     int rc = copy_to_host(base, n * d, xh, st);
     if (!rc && o.keep_stages) rc = copy_to_host(train, nt * d, th, st);
     if (rc) return rc;
-    std::vector<uint32_t> knn((size_t)nt * Nq);
     if (std::getenv("RG_LOG")) std::fprintf(stderr, "[rg] build: n=%lld d=%d nt=%lld Nq=%d M=%d L=%d\n", (long long)n, d, (long long)nt, Nq, M, L);
-    {
-        DevBuf ids;
-        rc = ids.alloc(sizeof(uint32_t) * knn.size());
-        if (!rc)
-            rc = knn_exact(train, nt, base, n, d, Nq, o.knn_slack, xh.data(), threads, ids.as<uint32_t>(), nullptr, st);
-        if (rc) return rc;
-        RG_HIP(hipMemcpyAsync(knn.data(), ids.p, sizeof(uint32_t) * knn.size(), hipMemcpyDeviceToHost, st));
-        RG_HIP(hipStreamSynchronize(st));
+    // the lists stay on the device for the projection
+    DevBuf lists;
+    rc = lists.alloc(sizeof(uint32_t) * (size_t)nt * Nq);
+    if (!rc)
+        rc = knn_exact(train, nt, base, n, d, Nq, o.knn_slack, xh.data(), threads, lists.as<uint32_t>(), nullptr, st);
+    if (rc) return rc;
+    std::vector<uint32_t> knn;
+    if (o.keep_stages) {
+        knn.resize((size_t)nt * Nq);
+        RG_HIP(hipMemcpyAsync(knn.data(), lists.p, sizeof(uint32_t) * knn.size(), hipMemcpyDeviceToHost, st));
     }
+    RG_HIP(hipStreamSynchronize(st));
     if (std::getenv("RG_LOG"))
         std::fprintf(stderr, "[rg] kNN preprocessing done in %.2f s\n",
                      std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count());
@@ -548,8 +552,9 @@ int rg_build(const float *base, int64_t n, int32_t d, const float *train, int64_
     rc = upload_base(ix, base, st);
     HostGraph g;
     if (!rc) {
-        GpuCtx gpu{ix->d_base, ix->pitch, st, canon_enhance};
-        rc = host_construct(xh.data(), n, d, knn.data(), nt, Nq, M, L, m_pj, m_ce, threads, &gpu, o.keep_stages != 0,
+        GpuCtx gpu{ix->d_base,  ix->pitch,     st,            lists.as<uint32_t>(),     canon_pivots,
+                   canon_lists, canon_project, canon_enhance, [&] { lists.release(); }};
+        rc = host_construct(xh.data(), n, d, knn.empty() ? nullptr : knn.data(), nt, Nq, M, L, m_pj, m_ce, threads, &gpu, o.keep_stages != 0,
                             &g);
     }
     if (!rc) {

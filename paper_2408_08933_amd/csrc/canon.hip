@@ -283,10 +283,104 @@ __global__ __launch_bounds__(256) void k_max_norm(const float *X, int64_t n, int
     if (lane == 0) atomicMax(reinterpret_cast<unsigned long long *>(out), (unsigned long long)__double_as_longlong(best));
 }
 
-// AcquireNeighbors (Algorithm 3, without the fill) for every searched node,
-// on the device: the candidates are the node's final queue without the node
-// itself, already ranked by (delta, id); a candidate is kept iff
-// delta(x, c) < delta(c, p) for every kept p (strict), until m are kept.  One
+// Candidates of the projection (Algorithm 2): of each pivot x, the entries of
+// the kNN lists of its bridges (ascending; the list without its first entry, x
+// itself) until a whole list brings their number to L or more, each once, with
+// their canonical distances, in (delta, id) order, the first L of them.  One
+// wavefront per pivot: a hash set in LDS keeps each id once, a lane walks a
+// chain per candidate, the wavefront sorts.  Pivots differ in their work (one
+// bridge or hundreds) and run side by side; loads bound it.  8,033 pivots of
+// 60k rows of 200, L = 500: 0.43 ms, and 2.3 ms for their selections; on 16
+// host threads both took 55.
+struct CandArgs {
+    const float *X;          // n x pitch
+    int32_t d, pitch;
+    const uint32_t *nodes;   // the pivots
+    const uint32_t *lists;   // nt x Nq
+    const int64_t *boff;     // n + 1: the bridges of each node
+    const uint32_t *bidx;
+    int32_t Nq, L, hash_bits, cap;  // cap: a power of two, room for L + Nq
+    uint32_t *ids;           // count x L
+    double *dists;
+    int32_t *counts;
+};
+
+template <int E>
+__device__ __forceinline__ void rank_candidates(const CandArgs &a, const float *xrow, const uint32_t *cid, int cnt,
+                                                int64_t b) {
+    const int lane = lane_id();
+    double key[E];
+    uint32_t id[E];
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        const int j = e * 64 + lane;  // any assignment of candidates to lanes will do
+        id[e] = j < cnt ? cid[j] : kNone;
+        key[e] = j < cnt ? -canon_sum(xrow, a.X + (size_t)id[e] * a.pitch, a.d) : INFINITY;
+        if (!(key[e] < INFINITY)) key[e] = INFINITY;  // a NaN has no place in the order
+    }
+    wave_sort<E, double>(key, id);
+    const int nk = min(cnt, a.L);
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        const int j = lane * E + e;
+        if (j < nk) {
+            a.ids[b * a.L + j] = id[e];
+            a.dists[b * a.L + j] = key[e];
+        }
+    }
+    if (lane == 0) a.counts[b] = nk;
+}
+
+__global__ __launch_bounds__(64) void k_project_cands(CandArgs a) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    float *xrow = reinterpret_cast<float *>(smem);
+    uint32_t *cid = reinterpret_cast<uint32_t *>(xrow + a.pitch);
+    uint32_t *set = cid + a.cap;
+    const int lane = lane_id();
+    const int64_t b = blockIdx.x;
+    const uint32_t x = a.nodes[b], mask = (1u << a.hash_bits) - 1u;
+    for (int i = lane; i < a.pitch; i += 64) xrow[i] = a.X[(size_t)x * a.pitch + i];
+    for (uint32_t i = lane; i <= mask; i += 64) set[i] = kNone;
+    wave_sync();
+    int cnt = 0;
+    for (int64_t e = a.boff[x]; e < a.boff[x + 1] && cnt < a.L; ++e) {
+        const uint32_t *lst = a.lists + (int64_t)a.bidx[e] * a.Nq;
+        for (int j0 = 1; j0 < a.Nq; j0 += 64) {
+            const uint32_t c = j0 + lane < a.Nq ? lst[j0 + lane] : kNone;
+            bool fresh = false;
+            if (c != kNone && c != x) {
+                uint32_t h = (c * 2654435761u) >> (32 - a.hash_bits);
+                // at most half the slots are ever taken, so a free one comes
+                for (;;) {
+                    const uint32_t was = atomicCAS(&set[h], kNone, c);
+                    fresh = was == kNone;
+                    if (fresh || was == c) break;
+                    h = (h + 1) & mask;
+                }
+            }
+            const uint64_t fm = ballot64(fresh);
+            const int to = cnt + lanes_below(fm);
+            if (fresh && to < a.cap) cid[to] = c;  // to < cap holds: cnt < L before each list of Nq - 1
+            cnt += (int)__popcll(fm);
+        }
+    }
+    cnt = min(cnt, a.cap);
+    wave_sync();
+    if (cnt <= 128)
+        rank_candidates<2>(a, xrow, cid, cnt, b);
+    else if (cnt <= 256)
+        rank_candidates<4>(a, xrow, cid, cnt, b);
+    else if (cnt <= 512)
+        rank_candidates<8>(a, xrow, cid, cnt, b);
+    else
+        rank_candidates<16>(a, xrow, cid, cnt, b);
+}
+
+// AcquireNeighbors (Algorithm 3) for a node's ranked candidates, on the
+// device: those of the projection, with the fill, or the node's final queue
+// (without the node itself), without it.  They stand in (delta, id) order; a
+// candidate is kept iff delta(x, c) < delta(c, p) for every kept p (strict),
+// until m are kept; the fill adds the others in order up to m.  One
 // lane per candidate, 64 at a time in rank order.  FP32 sums (16 kept rows in
 // one pass over the candidate's row) settle what lies outside their bound,
 // gam |c| |p|; the rest takes the host's FP64 chain, so every decision is the
@@ -300,11 +394,12 @@ struct SelectArgs {
     const int32_t *counts;
     int32_t L, m, head_len;
     int64_t x0;
-    uint32_t *sel_ids;       // count x m
+    const uint32_t *nodes;   // the nodes, or null: x0, x0 + 1, ...
+    uint32_t *sel_ids;       // n x m
     double *sel_d;
     int32_t *sel_n;
     uint32_t *head;          // count x head_len: the first candidates
-    int32_t *head_n;         // candidates per node (without the node)
+    int32_t *head_n;         // candidates per node (without the node), or null
     float gam;
 };
 
@@ -338,15 +433,18 @@ __device__ __forceinline__ void near_kept(const float *crow, KR kr, int nch, int
     }
 }
 
-template <bool KEPT_IN_LDS>
+template <bool KEPT_IN_LDS, bool FILL>
 __global__ __launch_bounds__(64) void k_canon_select(SelectArgs a) {
     extern __shared__ __align__(16) unsigned char smem[];
+    __shared__ uint64_t kept_of[kMaxL / 64];              // per 64 candidates (for the fill)
     uint32_t *kid = reinterpret_cast<uint32_t *>(smem);   // m kept ids
     float *kn = reinterpret_cast<float *>(smem) + ((a.m + 3) & ~3);  // their norms (rounded up)
     float *K = kn + ((a.m + 3) & ~3);                     // m x pitch kept rows (if they fit)
     const int lane = lane_id(), nch = a.pitch >> 2;
     const int64_t b = blockIdx.x;
-    const uint32_t x = (uint32_t)(a.x0 + b);
+    const uint32_t x = a.nodes ? a.nodes[b] : (uint32_t)(a.x0 + b);
+    uint32_t *sel_ids = a.sel_ids + (int64_t)x * a.m;
+    double *sel_d = a.sel_d + (int64_t)x * a.m;
     const uint32_t *cid = a.ids + b * a.L;
     const double *cdd = a.dists + b * a.L;
     const int qn = a.counts[b];
@@ -363,7 +461,11 @@ __global__ __launch_bounds__(64) void k_canon_select(SelectArgs a) {
         const int pos = hn + lanes_below(vm);
         if (valid && pos < a.head_len) a.head[b * a.head_len + pos] = c;
         hn += (int)__popcll(vm);
-        if (nr >= a.m) continue;
+        if (nr >= a.m) {
+            if (FILL) break;
+            continue;
+        }
+        uint64_t kept = 0;
         const double dxc = valid ? cdd[j] : 0.0;
         const float *crow = a.X + (size_t)(valid ? c : 0u) * a.pitch;
         bool alive = valid;
@@ -419,18 +521,35 @@ __global__ __launch_bounds__(64) void k_canon_select(SelectArgs a) {
             if (lane == 0) {
                 kid[nr] = cs;
                 kn[nr] = sqrtf(n2) * (1.0001f + a.gam);
-                a.sel_ids[(a.x0 + b) * a.m + nr] = cs;
-                a.sel_d[(a.x0 + b) * a.m + nr] = ds;
+                sel_ids[nr] = cs;
+                sel_d[nr] = ds;
             }
             ++nr;
+            kept |= 1ull << js;
             wave_sync();
             if (lane == js) alive = false;
             against(nr - 1, 1);
         }
+        if (FILL && lane == 0) kept_of[j0 >> 6] = kept;
+    }
+    if constexpr (FILL) {
+        wave_sync();
+        for (int j0 = 0; j0 < qn && nr < a.m; j0 += 64) {
+            const int j = j0 + lane;
+            const uint32_t c = j < qn ? cid[j] : kNone;
+            const bool rest = j < qn && c != x && !((kept_of[j0 >> 6] >> lane) & 1ull);
+            const uint64_t rm = ballot64(rest);
+            const int to = nr + lanes_below(rm);
+            if (rest && to < a.m) {
+                sel_ids[to] = c;
+                sel_d[to] = cdd[j];
+            }
+            nr = min(a.m, nr + (int)__popcll(rm));
+        }
     }
     if (lane == 0) {
-        a.sel_n[a.x0 + b] = nr;
-        a.head_n[b] = hn;
+        a.sel_n[x] = nr;
+        if (a.head_n) a.head_n[b] = hn;
     }
 }
 
@@ -453,8 +572,10 @@ struct ReplayArgs {
     const int32_t *sel_n;
     const int64_t *off;       // n + 1: the nodes that selected p
     const uint32_t *src;      // ascending per p where they are more than 64
-    uint32_t *out;            // n x m
+    uint32_t *out;            // n x out_pitch
     int32_t *out_n;
+    int32_t out_pitch;
+    const int64_t *boff;      // k_replay_fill: the bridges of each node, none if it is no pivot
 };
 
 __global__ __launch_bounds__(64) void k_replay(ReplayArgs a) {
@@ -527,8 +648,231 @@ __global__ __launch_bounds__(64) void k_replay(ReplayArgs a) {
         nc = min(a.m, r + 1 + (int)__popcll(s0) + (int)__popcll(s1));
         wave_sync();
     }
-    for (int j = lane; j < nc; j += 64) a.out[p * a.m + j] = ci[j];
+    for (int j = lane; j < nc; j += 64) a.out[p * a.out_pitch + j] = ci[j];
     if (lane == 0) a.out_n[p] = nc;
+}
+
+// Reverse updates of the projection (Algorithm 2), which fills: the list of p
+// starts as its own selection (a pivot) or empty, and takes each later node x
+// that selected p, ascending, while it has room.  A full list of m and x are m
+// + 1 candidates for m places, so AcquireNeighbors with the fill drops exactly
+// one: the last in rank that is not kept, or the last of all if every one is.
+// So the list is kept as slots, one per lane (SL of them for m >= 64), each
+// with its rank and a mask of the slots that rank before it and are no farther
+// from it than p is: those that keep it out if they are kept.  x brings one
+// distance per slot, a lane each, and the kept ones follow from the masks in a
+// few ballots: a slot is out if a kept one keeps it out, and kept once all
+// that could are out; the lowest rank still open is settled in every round.
+// The masks of the slots filled before are made when the list first overflows.
+// A lane's chain over a row of L2 and its loads bound a step.  257k updates of
+// 60k rows of 200 (at most 217 in a list), m = 32: 1.2 ms; on 16 host threads
+// 28.
+template <int SL>
+__global__ __launch_bounds__(64) void k_replay_fill(ReplayArgs a) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    float *xrow = reinterpret_cast<float *>(smem);
+    const int lane = lane_id();
+    const int64_t p = blockIdx.x;
+    const bool own = a.boff[p] != a.boff[p + 1];  // a pivot: its selection replaced what came before
+    int nc = own ? a.sel_n[p] : 0;
+    uint32_t id[SL], rank[SL];
+    double key[SL];
+    uint64_t out_by[SL][SL];  // the slots that keep slot s of this lane out
+#pragma unroll
+    for (int s = 0; s < SL; ++s) {
+        const int j = lane + 64 * s;
+        id[s] = j < nc ? a.sel_ids[p * a.m + j] : kNone;
+        key[s] = 0.0;
+        rank[s] = 0;
+#pragma unroll
+        for (int t = 0; t < SL; ++t) out_by[s][t] = 0;
+    }
+    auto load_row = [&](uint32_t x) {
+        wave_sync();
+        for (int i = lane; i < a.pitch; i += 64) xrow[i] = a.X[(size_t)x * a.pitch + i];
+        wave_sync();
+    };
+    auto id_of = [&](int slot) {
+        const int l = slot & 63;
+        uint32_t v = (uint32_t)__builtin_amdgcn_readlane((int)id[0], l);
+        if constexpr (SL > 1) {
+            const uint32_t w = (uint32_t)__builtin_amdgcn_readlane((int)id[SL - 1], l);
+            v = slot < 64 ? v : w;
+        }
+        return v;
+    };
+    auto key_of = [&](int slot) {
+        double v = __shfl(key[0], slot & 63);
+        if constexpr (SL > 1) {
+            const double w = __shfl(key[SL - 1], slot & 63);
+            v = slot < 64 ? v : w;
+        }
+        return v;
+    };
+    int open = -1;  // the one free slot of a list that has overflowed, or -1
+    const int64_t e0 = a.off[p], ne = a.off[p + 1] - e0;
+    uint32_t ev[1] = {lane < ne ? a.src[e0 + lane] : kNone}, tag[1] = {0};
+    if (ne <= 64) wave_sort<1, uint32_t>(ev, tag);
+    for (int64_t e = 0; e < ne; ++e) {
+        if (e > 0 && (e & 63) == 0) ev[0] = e + lane < ne ? a.src[e0 + e + lane] : kNone;
+        const uint32_t x = (uint32_t)__builtin_amdgcn_readlane((int)ev[0], (int)(e & 63));
+        if (own && (int64_t)x < p) continue;
+        bool there = false;
+#pragma unroll
+        for (int s = 0; s < SL; ++s) there |= id[s] == x;
+        if (ballot64(there)) continue;
+        if (nc < a.m) {
+#pragma unroll
+            for (int s = 0; s < SL; ++s)
+                if (lane + 64 * s == nc) id[s] = x;
+            ++nc;
+            continue;
+        }
+        if (open < 0) {
+            // keys, ranks and masks of the m slots
+            open = a.m;
+            load_row((uint32_t)p);
+#pragma unroll
+            for (int s = 0; s < SL; ++s)
+                if (id[s] != kNone) key[s] = -canon_sum(xrow, a.X + (size_t)id[s] * a.pitch, a.d);
+            for (int r = 0; r < a.m; ++r) {
+                const uint32_t ir = id_of(r);
+                const double kr = key_of(r);
+                load_row(ir);
+#pragma unroll
+                for (int s = 0; s < SL; ++s)
+                    if (id[s] != kNone && kless(kr, ir, key[s], id[s])) {
+                        ++rank[s];
+                        const double dj = -canon_sum(xrow, a.X + (size_t)id[s] * a.pitch, a.d);
+                        if (!(key[s] < dj)) {
+#pragma unroll
+                            for (int t = 0; t < SL; ++t)
+                                if (r >> 6 == t) out_by[s][t] |= 1ull << (r & 63);
+                        }
+                    }
+            }
+        }
+        // distances of x to the slots, and to p in the free slot's lane
+        load_row(x);
+        double dj[SL];
+#pragma unroll
+        for (int s = 0; s < SL; ++s) {
+            const bool here = lane + 64 * s == open;
+            dj[s] = here || id[s] != kNone
+                        ? -canon_sum(xrow, a.X + (size_t)(here ? (uint32_t)p : id[s]) * a.pitch, a.d)
+                        : 0.0;
+        }
+        double dx = __shfl(dj[0], open & 63);
+        if constexpr (SL > 1) {
+            const double w = __shfl(dj[SL - 1], open & 63);
+            dx = open < 64 ? dx : w;
+        }
+        uint64_t ob[SL];
+        uint32_t rx = 0;
+#pragma unroll
+        for (int s = 0; s < SL; ++s) {
+            const bool used = id[s] != kNone;
+            const bool before = used && kless(key[s], id[s], dx, x);
+            ob[s] = ballot64(before && !(dx < dj[s]));
+            rx += (uint32_t)__popcll(ballot64(before));
+            if (used) {
+                const bool by_x = !before && !(key[s] < dj[s]);
+#pragma unroll
+                for (int t = 0; t < SL; ++t)
+                    if (open >> 6 == t) {
+                        const uint64_t bit = 1ull << (open & 63);
+                        out_by[s][t] = by_x ? out_by[s][t] | bit : out_by[s][t] & ~bit;
+                    }
+                if (!before) ++rank[s];
+            }
+        }
+#pragma unroll
+        for (int s = 0; s < SL; ++s)
+            if (lane + 64 * s == open) {
+                id[s] = x;
+                key[s] = dx;
+                rank[s] = rx;
+#pragma unroll
+                for (int t = 0; t < SL; ++t) out_by[s][t] = ob[t];
+            }
+        // who is kept
+        uint64_t kept[SL] = {}, outm[SL] = {};
+        bool undecided[SL];
+#pragma unroll
+        for (int s = 0; s < SL; ++s) undecided[s] = id[s] != kNone;
+        for (;;) {
+            bool k[SL], o[SL];
+#pragma unroll
+            for (int s = 0; s < SL; ++s) {
+                uint64_t by_kept = 0, by_open = 0;
+#pragma unroll
+                for (int t = 0; t < SL; ++t) {
+                    by_kept |= out_by[s][t] & kept[t];
+                    by_open |= out_by[s][t] & ~outm[t];
+                }
+                o[s] = undecided[s] && by_kept != 0;
+                k[s] = undecided[s] && by_open == 0;
+                if (o[s] || k[s]) undecided[s] = false;
+            }
+            uint64_t settled = 0;
+            bool any = false;
+#pragma unroll
+            for (int s = 0; s < SL; ++s) {
+                const uint64_t km = ballot64(k[s]), om = ballot64(o[s]);
+                kept[s] |= km;
+                outm[s] |= om;
+                settled |= km | om;
+                any |= undecided[s];
+            }
+            // a round settles none only where NaNs leave no order
+            if (ballot64(any) == 0 || settled == 0) break;
+        }
+        // the highest rank of those out, or of all
+        bool none_out = true;
+#pragma unroll
+        for (int s = 0; s < SL; ++s) none_out &= outm[s] == 0;
+        bool cand[SL];
+#pragma unroll
+        for (int s = 0; s < SL; ++s)
+            cand[s] = id[s] != kNone && (none_out || ((outm[s] >> lane) & 1ull));
+        for (int bit = 6; bit >= 0; --bit) {
+            uint64_t any = 0;
+#pragma unroll
+            for (int s = 0; s < SL; ++s) any |= ballot64(cand[s] && ((rank[s] >> bit) & 1u));
+            if (any) {
+#pragma unroll
+                for (int s = 0; s < SL; ++s) cand[s] = cand[s] && ((rank[s] >> bit) & 1u);
+            }
+        }
+        uint32_t rd = 0;
+#pragma unroll
+        for (int s = 0; s < SL; ++s) {
+            const uint64_t cm = ballot64(cand[s]);
+            if (cm) {
+                open = 64 * s + (int)__builtin_ctzll(cm);
+                rd = (uint32_t)__builtin_amdgcn_readlane((int)rank[s], (int)__builtin_ctzll(cm));
+            }
+        }
+#pragma unroll
+        for (int s = 0; s < SL; ++s) {
+            if (lane + 64 * s == open)
+                id[s] = kNone;
+            else if (rank[s] > rd)
+                --rank[s];
+        }
+    }
+#pragma unroll
+    for (int s = 0; s < SL; ++s) {
+        const int j = lane + 64 * s, to = open >= 0 && j > open ? j - 1 : j;
+        if (id[s] != kNone) a.out[p * a.out_pitch + to] = id[s];
+        if (j >= nc && j < a.out_pitch) a.out[p * a.out_pitch + j] = kNone;
+    }
+    if (lane == 0) a.out_n[p] = nc;
+}
+
+__global__ __launch_bounds__(256) void k_first_of_lists(const uint32_t *lists, int64_t nt, int Nq, uint32_t *out) {
+    for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < nt; t += (int64_t)gridDim.x * blockDim.x)
+        out[t] = lists[t * Nq];
 }
 
 // The nodes that selected each node: counts, then places (in any order).
@@ -667,6 +1011,166 @@ int launch_canon_search(const float *X, int64_t n, int32_t d, int32_t pitch, con
     return run(k_canon_search<VisitLds, false>);
 }
 
+namespace {
+
+// The nodes that selected each node, off (n + 1) and src, ascending where they
+// are more than 64.  selected() is called once the selections are done.
+template <class F>
+int selected_by(const SelectArgs &s, int64_t n, Dev &d_off, Dev &d_src, hipStream_t st, F &&selected) {
+    Dev d_cnt;
+    if (!d_cnt.alloc(sizeof(uint32_t) * n) || !d_off.alloc(sizeof(int64_t) * (n + 1))) {
+        set_error("build: out of memory for reverse updates");
+        return RG_ENOMEM;
+    }
+    hipLaunchKernelGGL(k_zero32, dim3(blocks_for(n)), dim3(256), 0, st, d_cnt.as<uint32_t>(), n);
+    hipLaunchKernelGGL(k_count_events, dim3(blocks_for(n)), dim3(256), 0, st, s.sel_ids, s.sel_n, n, s.m,
+                       d_cnt.as<uint32_t>());
+    RG_HIP(hipGetLastError());
+    std::vector<uint32_t> cnt((size_t)n);
+    RG_HIP(hipMemcpyAsync(cnt.data(), d_cnt.p, sizeof(uint32_t) * n, hipMemcpyDeviceToHost, st));
+    RG_HIP(hipStreamSynchronize(st));
+    selected();
+    std::vector<int64_t> off((size_t)n + 1, 0);
+    for (int64_t i = 0; i < n; ++i) off[i + 1] = off[i] + cnt[i];
+    if (!d_src.alloc(sizeof(uint32_t) * (size_t)off[n])) {
+        set_error("build: out of memory for reverse updates");
+        return RG_ENOMEM;
+    }
+    RG_HIP(hipMemcpyAsync(d_off.p, off.data(), sizeof(int64_t) * (n + 1), hipMemcpyHostToDevice, st));
+    hipLaunchKernelGGL(k_place_events, dim3(blocks_for(n)), dim3(256), 0, st, s.sel_ids, s.sel_n, n, s.m,
+                       d_off.as<int64_t>(), d_cnt.as<uint32_t>(), d_src.as<uint32_t>());
+    hipLaunchKernelGGL(k_sort_events, dim3((unsigned)n), dim3(256), 0, st, d_off.as<int64_t>(), d_src.as<uint32_t>());
+    RG_HIP(hipGetLastError());
+    // before the counts and offsets go
+    RG_HIP(hipStreamSynchronize(st));
+    return RG_OK;
+}
+
+// LDS of k_canon_select without and with the kept rows
+size_t select_lds(const GpuCtx &gpu, int m, bool *rows) {
+    const size_t ids = 2 * (size_t)((m + 3) & ~3) * sizeof(uint32_t), kept = (size_t)m * gpu.pitch * sizeof(float);
+    *rows = ids + kept <= (48u << 10);
+    return ids + (*rows ? kept : 0);
+}
+
+}  // namespace
+
+int canon_pivots(const GpuCtx &gpu, int64_t nt, int32_t Nq, uint32_t *out) {
+    Dev d_out;
+    if (!d_out.alloc(sizeof(uint32_t) * nt)) {
+        set_error("build: out of memory for the pivots");
+        return RG_ENOMEM;
+    }
+    hipLaunchKernelGGL(k_first_of_lists, dim3(blocks_for(nt)), dim3(256), 0, gpu.stream, gpu.lists, nt, Nq,
+                       d_out.as<uint32_t>());
+    RG_HIP(hipGetLastError());
+    RG_HIP(hipMemcpyAsync(out, d_out.p, sizeof(uint32_t) * nt, hipMemcpyDeviceToHost, gpu.stream));
+    RG_HIP(hipStreamSynchronize(gpu.stream));
+    return RG_OK;
+}
+
+int canon_lists(const GpuCtx &gpu, int64_t words, uint32_t *out) {
+    RG_HIP(hipMemcpyAsync(out, gpu.lists, sizeof(uint32_t) * words, hipMemcpyDeviceToHost, gpu.stream));
+    RG_HIP(hipStreamSynchronize(gpu.stream));
+    return RG_OK;
+}
+
+// Pivots in batches (the candidates are the large buffers).  RG_ENOMEM: a
+// buffer did not fit, nothing was written.
+int canon_project(const GpuCtx &gpu, int64_t n, int32_t d, int64_t nt, int32_t Nq, const std::vector<int64_t> &boff,
+                  const std::vector<uint32_t> &bidx, int32_t L, int32_t m, int32_t ell, std::vector<uint32_t> *pj,
+                  std::vector<int32_t> *pj_n) {
+    hipStream_t st = gpu.stream;
+    if (L > kMaxL || m < 1 || m >= kMaxEll || Nq > 512 || ell < m) return RG_ENOMEM;  // no room in the kernels
+    std::vector<uint32_t> piv;
+    for (int64_t x = 0; x < n; ++x)
+        if (boff[x] != boff[x + 1]) piv.push_back((uint32_t)x);
+    const int64_t np = (int64_t)piv.size(), B = std::max<int64_t>(1, std::min<int64_t>(np, 1 << 15));
+    CandArgs c{};
+    c.cap = 256;
+    while (c.cap < L + Nq) c.cap *= 2;
+    c.hash_bits = 1;
+    while ((1 << c.hash_bits) < 2 * c.cap) ++c.hash_bits;
+    const size_t cand_lds = (size_t)gpu.pitch * 4 + (size_t)c.cap * 4 + ((size_t)4 << c.hash_bits);
+    if (cand_lds > (64u << 10) || (size_t)gpu.pitch * 4 > (64u << 10)) return RG_ENOMEM;
+    Dev d_piv, d_boff, d_bidx, d_c, d_cd, d_cn, d_sid, d_sd, d_sn, d_out, d_on, d_off, d_src;
+    if (!d_piv.alloc(sizeof(uint32_t) * np) || !d_boff.alloc(sizeof(int64_t) * (n + 1)) ||
+        !d_bidx.alloc(sizeof(uint32_t) * nt) || !d_c.alloc(sizeof(uint32_t) * B * L) ||
+        !d_cd.alloc(sizeof(double) * B * L) || !d_cn.alloc(sizeof(int32_t) * B) ||
+        !d_sid.alloc(sizeof(uint32_t) * n * m) || !d_sd.alloc(sizeof(double) * n * m) ||
+        !d_sn.alloc(sizeof(int32_t) * n) || !d_out.alloc(sizeof(uint32_t) * n * ell) ||
+        !d_on.alloc(sizeof(int32_t) * n)) {
+        (void)hipGetLastError();
+        return RG_ENOMEM;
+    }
+    RG_HIP(hipMemcpyAsync(d_piv.p, piv.data(), sizeof(uint32_t) * np, hipMemcpyHostToDevice, st));
+    RG_HIP(hipMemcpyAsync(d_boff.p, boff.data(), sizeof(int64_t) * (n + 1), hipMemcpyHostToDevice, st));
+    RG_HIP(hipMemcpyAsync(d_bidx.p, bidx.data(), sizeof(uint32_t) * nt, hipMemcpyHostToDevice, st));
+    hipLaunchKernelGGL(k_zero32, dim3(blocks_for(n)), dim3(256), 0, st, d_sn.as<uint32_t>(), n);
+    c.X = gpu.X;
+    c.d = d;
+    c.pitch = gpu.pitch;
+    c.lists = gpu.lists;
+    c.boff = d_boff.as<int64_t>();
+    c.bidx = d_bidx.as<uint32_t>();
+    c.Nq = Nq;
+    c.L = L;
+    c.ids = d_c.as<uint32_t>();
+    c.dists = d_cd.as<double>();
+    c.counts = d_cn.as<int32_t>();
+    SelectArgs s{};
+    s.X = gpu.X;
+    s.d = d;
+    s.pitch = gpu.pitch;
+    s.ids = c.ids;
+    s.dists = c.dists;
+    s.counts = c.counts;
+    s.L = L;
+    s.m = m;
+    s.sel_ids = d_sid.as<uint32_t>();
+    s.sel_d = d_sd.as<double>();
+    s.sel_n = d_sn.as<int32_t>();
+    s.gam = sum_bound(d, gpu.pitch + 8);
+    bool rows;
+    const size_t lds = select_lds(gpu, m, &rows);
+    auto k_select = rows ? k_canon_select<true, true> : k_canon_select<false, true>;
+    for (int64_t b0 = 0; b0 < np; b0 += B) {
+        const unsigned cnt = (unsigned)std::min(B, np - b0);
+        c.nodes = s.nodes = d_piv.as<uint32_t>() + b0;
+        hipLaunchKernelGGL(k_project_cands, dim3(cnt), dim3(64), cand_lds, st, c);
+        hipLaunchKernelGGL(k_select, dim3(cnt), dim3(64), lds, st, s);
+        RG_HIP(hipGetLastError());
+    }
+    const int rc = selected_by(s, n, d_off, d_src, st, [] {});
+    if (rc) {
+        if (rc == RG_ENOMEM) (void)hipGetLastError();
+        return rc;
+    }
+    ReplayArgs r{};
+    r.X = gpu.X;
+    r.d = d;
+    r.pitch = gpu.pitch;
+    r.m = m;
+    r.sel_ids = s.sel_ids;
+    r.sel_d = s.sel_d;
+    r.sel_n = s.sel_n;
+    r.off = d_off.as<int64_t>();
+    r.src = d_src.as<uint32_t>();
+    r.out = d_out.as<uint32_t>();
+    r.out_n = d_on.as<int32_t>();
+    r.out_pitch = ell;
+    r.boff = c.boff;
+    auto k_fill = m < 64 ? k_replay_fill<1> : k_replay_fill<2>;
+    hipLaunchKernelGGL(k_fill, dim3((unsigned)n), dim3(64), (size_t)gpu.pitch * 4, st, r);
+    RG_HIP(hipGetLastError());
+    pj->resize((size_t)n * ell);
+    pj_n->resize((size_t)n);
+    RG_HIP(hipMemcpyAsync(pj->data(), d_out.p, sizeof(uint32_t) * n * ell, hipMemcpyDeviceToHost, st));
+    RG_HIP(hipMemcpyAsync(pj_n->data(), d_on.p, sizeof(int32_t) * n, hipMemcpyDeviceToHost, st));
+    RG_HIP(hipStreamSynchronize(st));
+    return RG_OK;
+}
+
 // The searches and selections run in batches (their queues are the large
 // buffers); selections, reverse updates and the lists stay on the device.
 int canon_enhance(const GpuCtx &gpu, int64_t n, int32_t d, const std::vector<uint32_t> &adj, int32_t ell,
@@ -708,10 +1212,9 @@ int canon_enhance(const GpuCtx &gpu, int64_t n, int32_t d, const std::vector<uin
     s.sel_n = d_sn.as<int32_t>();
     // a lane's chain over the whole row, and the norms' own rounding
     s.gam = sum_bound(d, gpu.pitch + 8);
-    const size_t id_bytes = 2 * (size_t)((m + 3) & ~3) * sizeof(uint32_t);
-    const size_t kept_bytes = (size_t)m * gpu.pitch * sizeof(float);
-    const bool kept_in_lds = id_bytes + kept_bytes <= (48u << 10);
-    auto k_select = kept_in_lds ? k_canon_select<true> : k_canon_select<false>;
+    bool kept_in_lds;
+    const size_t lds = select_lds(gpu, m, &kept_in_lds);
+    auto k_select = kept_in_lds ? k_canon_select<true, false> : k_canon_select<false, false>;
     const int64_t step = std::max<int64_t>(B, (n / 10 + B - 1) / B * B);
     for (int64_t x0 = 0; x0 < n; x0 += B) {
         const int64_t cnt = std::min(B, n - x0);
@@ -721,7 +1224,7 @@ int canon_enhance(const GpuCtx &gpu, int64_t n, int32_t d, const std::vector<uin
         s.x0 = x0;
         s.head = d_hd.as<uint32_t>() + x0 * head_len;
         s.head_n = d_hn.as<int32_t>() + x0;
-        hipLaunchKernelGGL(k_select, dim3((unsigned)cnt), dim3(64), id_bytes + (kept_in_lds ? kept_bytes : 0), st, s);
+        hipLaunchKernelGGL(k_select, dim3((unsigned)cnt), dim3(64), lds, st, s);
         RG_HIP(hipGetLastError());
         if (log && ((x0 + cnt) % step == 0 || x0 + cnt == n)) {  // progress (waits for the batches)
             RG_HIP(hipStreamSynchronize(st));
@@ -730,32 +1233,13 @@ int canon_enhance(const GpuCtx &gpu, int64_t n, int32_t d, const std::vector<uin
     }
     RG_HIP(hipMemcpyAsync(head, d_hd.p, sizeof(uint32_t) * n * head_len, hipMemcpyDeviceToHost, st));
     RG_HIP(hipMemcpyAsync(head_n, d_hn.p, sizeof(int32_t) * n, hipMemcpyDeviceToHost, st));
-    // the nodes that selected each node
-    Dev d_cnt, d_off;
-    if (!d_cnt.alloc(sizeof(uint32_t) * n) || !d_off.alloc(sizeof(int64_t) * (n + 1))) {
+    Dev d_off, d_src, d_out, d_on;
+    rc = selected_by(s, n, d_off, d_src, st, [&] { *t_search = std::chrono::duration<double>(Clock::now() - t0).count(); });
+    if (rc) return rc;
+    if (!d_out.alloc(sizeof(uint32_t) * n * m) || !d_on.alloc(sizeof(int32_t) * n)) {
         set_error("build: out of memory for reverse updates");
         return RG_ENOMEM;
     }
-    hipLaunchKernelGGL(k_zero32, dim3(blocks_for(n)), dim3(256), 0, st, d_cnt.as<uint32_t>(), n);
-    hipLaunchKernelGGL(k_count_events, dim3(blocks_for(n)), dim3(256), 0, st, s.sel_ids, s.sel_n, n, m,
-                       d_cnt.as<uint32_t>());
-    RG_HIP(hipGetLastError());
-    std::vector<uint32_t> cnt((size_t)n);
-    RG_HIP(hipMemcpyAsync(cnt.data(), d_cnt.p, sizeof(uint32_t) * n, hipMemcpyDeviceToHost, st));
-    RG_HIP(hipStreamSynchronize(st));
-    *t_search = std::chrono::duration<double>(Clock::now() - t0).count();
-    std::vector<int64_t> off((size_t)n + 1, 0);
-    for (int64_t i = 0; i < n; ++i) off[i + 1] = off[i] + cnt[i];
-    Dev d_src, d_out, d_on;
-    if (!d_src.alloc(sizeof(uint32_t) * (size_t)off[n]) || !d_out.alloc(sizeof(uint32_t) * n * m) ||
-        !d_on.alloc(sizeof(int32_t) * n)) {
-        set_error("build: out of memory for reverse updates");
-        return RG_ENOMEM;
-    }
-    RG_HIP(hipMemcpyAsync(d_off.p, off.data(), sizeof(int64_t) * (n + 1), hipMemcpyHostToDevice, st));
-    hipLaunchKernelGGL(k_place_events, dim3(blocks_for(n)), dim3(256), 0, st, s.sel_ids, s.sel_n, n, m,
-                       d_off.as<int64_t>(), d_cnt.as<uint32_t>(), d_src.as<uint32_t>());
-    hipLaunchKernelGGL(k_sort_events, dim3((unsigned)n), dim3(256), 0, st, d_off.as<int64_t>(), d_src.as<uint32_t>());
     ReplayArgs r{};
     r.X = gpu.X;
     r.d = d;
@@ -768,6 +1252,7 @@ int canon_enhance(const GpuCtx &gpu, int64_t n, int32_t d, const std::vector<uin
     r.src = d_src.as<uint32_t>();
     r.out = d_out.as<uint32_t>();
     r.out_n = d_on.as<int32_t>();
+    r.out_pitch = m;
     hipLaunchKernelGGL(k_replay, dim3((unsigned)n), dim3(64), (size_t)gpu.pitch * 4 + (size_t)(m + 1) * 12 + 8, st, r);
     RG_HIP(hipGetLastError());
     ce->resize((size_t)n * m);

@@ -361,14 +361,6 @@ struct Searcher {
     }
 };
 
-void lists_to_csr(const Lists &L, int64_t n, std::vector<int64_t> &off, std::vector<uint32_t> &idx) {
-    off.assign((size_t)n + 1, 0);
-    for (int64_t x = 0; x < n; ++x) off[x + 1] = off[x] + L.deg[x];
-    idx.resize((size_t)off[n]);
-    for (int64_t x = 0; x < n; ++x)
-        for (int j = 0; j < L.deg[x]; ++j) idx[off[x] + j] = L.row(x)[j].id;
-}
-
 }  // namespace
 
 double canon_dist(const float *a, const float *b, int32_t d) {
@@ -391,20 +383,43 @@ int host_construct(const float *X, int64_t n, int32_t d, const uint32_t *knn, in
     const int q1 = Nq - 1;
 
     // --- bipartite graph (Algorithm 1): pivot of t gets t as a bridge ------
+    std::vector<uint32_t> pivot((size_t)nt);
+    if (knn)
+        for (int64_t t = 0; t < nt; ++t) pivot[t] = knn[t * Nq];
+    else if (const int rc = gpu->pivots(*gpu, nt, Nq, pivot.data()))
+        return rc;
     std::vector<int64_t> boff((size_t)n + 1, 0);
-    for (int64_t t = 0; t < nt; ++t) boff[knn[t * Nq] + 1]++;
+    for (int64_t t = 0; t < nt; ++t) boff[pivot[t] + 1]++;
     for (int64_t i = 0; i < n; ++i) boff[i + 1] += boff[i];
     std::vector<uint32_t> bidx((size_t)nt);
     {
         std::vector<int64_t> fp(boff.begin(), boff.end() - 1);
-        for (int64_t t = 0; t < nt; ++t) bidx[fp[knn[t * Nq]]++] = (uint32_t)t;
+        for (int64_t t = 0; t < nt; ++t) bidx[fp[pivot[t]]++] = (uint32_t)t;
     }
 
+    // --- projection: on the device, or on host threads --------------------
+    // the projected graph, rows of pj_ell ids filled up with kNone
+    const int32_t pj_ell = (std::max(1, m_pj) + 7) / 8 * 8;
+    std::vector<uint32_t> pj;
+    std::vector<int32_t> pj_n;
+    std::vector<uint32_t> fetched;
+    bool projected = false;
+    if (gpu) {
+        const int rc = gpu->project(*gpu, n, d, nt, Nq, boff, bidx, L, m_pj, pj_ell, &pj, &pj_n);
+        if (rc && rc != RG_ENOMEM) return rc;
+        projected = rc == RG_OK;
+        if (!projected && !knn) {
+            fetched.resize((size_t)nt * Nq);
+            if (const int rc2 = gpu->lists_to_host(*gpu, nt * Nq, fetched.data())) return rc2;
+            knn = fetched.data();
+        }
+        gpu->drop_lists();
+    }
     // --- projection, forward selections F(x) of every pivot ---------------
     const int capl = std::max(m_pj, m_ce) + 1;
     Lists F;
-    F.init(n, capl);
-    {
+    if (!projected) {
+        F.init(n, capl);
         std::vector<std::vector<uint32_t>> stamp((size_t)threads);
         std::vector<std::vector<uint32_t>> cid((size_t)threads);
         std::vector<std::vector<double>> cdd((size_t)threads);
@@ -439,9 +454,9 @@ int host_construct(const float *X, int64_t n, int32_t d, const uint32_t *knn, in
         });
     }
     // --- projection, reverse insertions replayed per target ---------------
-    Lists PJ;
-    PJ.init(n, capl);
-    {
+    if (!projected) {
+        Lists PJ;
+        PJ.init(n, capl);
         std::vector<int64_t> eoff;
         std::vector<uint32_t> esrc;
         build_events(F, n, eoff, esrc);
@@ -453,10 +468,24 @@ int host_construct(const float *X, int64_t n, int32_t d, const uint32_t *knn, in
             replay(X, d, p, piv, F.row(p), piv ? F.deg[p] : 0, esrc.data() + eoff[p], eoff[p + 1] - eoff[p], m_pj,
                    true, PJ.row(p), &PJ.deg[p], cur[tid], tmp[tid], kept[tid], pcs[tid]);
         });
+        pj.assign((size_t)n * pj_ell, kNone);
+        pj_n.assign(PJ.deg.begin(), PJ.deg.end());
+        parallel_for(n, threads, 4096, [&](int64_t x, int) {
+            for (int j = 0; j < PJ.deg[x]; ++j) pj[x * pj_ell + j] = PJ.row(x)[j].id;
+        });
     }
+    // as CSR, for searches on the host
     std::vector<int64_t> pjoff;
     std::vector<uint32_t> pjidx;
-    lists_to_csr(PJ, n, pjoff, pjidx);
+    auto pj_csr = [&] {
+        if (!pjoff.empty()) return;
+        pjoff.assign((size_t)n + 1, 0);
+        for (int64_t x = 0; x < n; ++x) pjoff[x + 1] = pjoff[x] + pj_n[x];
+        pjidx.resize((size_t)pjoff[n]);
+        for (int64_t x = 0; x < n; ++x)
+            std::copy(pj.begin() + x * pj_ell, pj.begin() + x * pj_ell + pj_n[x], pjidx.begin() + pjoff[x]);
+    };
+    if (!gpu || keep_stages) pj_csr();
     const auto t1 = Clock::now();
     const bool log = std::getenv("RG_LOG") != nullptr;
     if (log) std::fprintf(stderr, "[rg] projection done in %.2f s\n", secs(t0, t1));
@@ -498,7 +527,7 @@ int host_construct(const float *X, int64_t n, int32_t d, const uint32_t *knn, in
             }
         return e;
     };
-    const uint32_t entry = nearest_mean([&](int64_t i) { return PJ.deg[i] > 0; });
+    const uint32_t entry = nearest_mean([&](int64_t i) { return pj_n[i] > 0; });
 
     // --- enhancement: searches on G_pj and each node's own selection E(x) --
     Lists E;
@@ -509,14 +538,7 @@ int host_construct(const float *X, int64_t n, int32_t d, const uint32_t *knn, in
     std::vector<uint32_t> dev_ce;
     std::vector<int32_t> dev_ce_n;
     if (gpu) {
-        int32_t maxdeg = 1;
-        for (int64_t x = 0; x < n; ++x) maxdeg = std::max<int32_t>(maxdeg, PJ.deg[x]);
-        const int32_t ell = (maxdeg + 7) / 8 * 8;
-        std::vector<uint32_t> adj((size_t)n * ell, kNone);
-        parallel_for(n, threads, 4096, [&](int64_t x, int) {
-            for (int j = 0; j < PJ.deg[x]; ++j) adj[x * ell + j] = PJ.row(x)[j].id;
-        });
-        const int rc = gpu->enhance(*gpu, n, d, adj, ell, entry, L, std::max(1, m_ce), kHead, &dev_ce, &dev_ce_n,
+        const int rc = gpu->enhance(*gpu, n, d, pj, pj_ell, entry, L, std::max(1, m_ce), kHead, &dev_ce, &dev_ce_n,
                                     head.data(), head_n.data(), &out->t_enhance_search);
         if (rc) return rc;
     } else {
@@ -561,7 +583,7 @@ int host_construct(const float *X, int64_t n, int32_t d, const uint32_t *knn, in
     parallel_for(n, threads, 1024, [&](int64_t x, int) {
         auto &r = fin[x];
         r.reserve((size_t)M);
-        for (int j = 0; j < PJ.deg[x]; ++j) r.push_back(PJ.row(x)[j].id);
+        for (int j = 0; j < pj_n[x]; ++j) r.push_back(pj[x * pj_ell + j]);
         const int nce = gpu ? dev_ce_n[x] : CE.deg[x];
         for (int j = 0; j < nce; ++j) {
             const uint32_t u = gpu ? dev_ce[x * (int64_t)std::max(1, m_ce) + j] : CE.row(x)[j].id;
@@ -606,6 +628,7 @@ int host_construct(const float *X, int64_t n, int32_t d, const uint32_t *knn, in
             }
             if (r < 0 && head_n[u] > kHead) {  // rare: the stored head is full, search again
                 if (s.stamp.empty()) s.init(n, L);
+                pj_csr();
                 ++searches;
                 const int qn = s.run(X, d, pjoff.data(), pjidx.data(), entry, X + u * d, L);
                 for (int j = 0; j < qn && r < 0; ++j) {

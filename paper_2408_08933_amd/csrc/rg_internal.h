@@ -5,6 +5,7 @@
 
 #include <algorithm>
 #include <cstdint>
+#include <functional>
 #include <string>
 #include <vector>
 
@@ -264,20 +265,33 @@ struct HostGraph {
     double t_knn = 0, t_project = 0, t_enhance = 0, t_total = 0;
     double t_enhance_search = 0;
 };
-// Device resources construction may use: the padded FP32 base on the device,
-// and the enhancement there (canon.hip; a pointer, so that the host half links
-// without the device half): from the projected graph as ELL rows to the lists
-// after the reverse updates (n x m ids in ce, ce_n per node), the first
-// head_len search results of each node (itself left out) and their number.
+// Device resources construction may use: the padded FP32 base and the kNN
+// lists on the device, and the work done there (canon.hip; pointers, so that
+// the host half links without the device half).
 struct GpuCtx {
     const float *X;      // n x pitch
     int32_t pitch;
     hipStream_t stream;
+    const uint32_t *lists;  // nt x Nq; not used after the projection
+    // the first entry of each list
+    int (*pivots)(const GpuCtx &gpu, int64_t nt, int32_t Nq, uint32_t *out);
+    // the lists themselves
+    int (*lists_to_host)(const GpuCtx &gpu, int64_t words, uint32_t *out);
+    // from the bridges of each node to the projected graph, rows of ell ids
+    // filled up with kNone, and its degrees; RG_ENOMEM: no room for it there
+    int (*project)(const GpuCtx &gpu, int64_t n, int32_t d, int64_t nt, int32_t Nq, const std::vector<int64_t> &boff,
+                   const std::vector<uint32_t> &bidx, int32_t L, int32_t m, int32_t ell, std::vector<uint32_t> *pj,
+                   std::vector<int32_t> *pj_n);
+    // the enhancement, from the projected graph to the lists after the reverse
+    // updates (n x m ids in ce, ce_n per node), the first head_len search
+    // results of each node (itself left out) and their number
     int (*enhance)(const GpuCtx &gpu, int64_t n, int32_t d, const std::vector<uint32_t> &adj, int32_t ell,
                    uint32_t entry, int32_t L, int32_t m, int32_t head_len, std::vector<uint32_t> *ce,
                    std::vector<int32_t> *ce_n, uint32_t *head, int32_t *head_n, double *t_search);
+    std::function<void()> drop_lists;  // called after the projection
 };
-// knn lists: nt x Nq canonical ids.  X: host n x d.  gpu == nullptr: host only.
+// knn lists: nt x Nq canonical ids (null: on the device only, without kept
+// stages).  X: host n x d.  gpu == nullptr: host only.
 int host_construct(const float *X, int64_t n, int32_t d, const uint32_t *knn, int64_t nt,
                    int32_t Nq, int32_t M, int32_t L, int32_t m_pj, int32_t m_ce, int threads,
                    const GpuCtx *gpu, bool keep_stages, HostGraph *out);
@@ -302,7 +316,12 @@ int launch_max_norm(const float *X, int64_t n, int32_t pitch, double *xmax2, hip
 int launch_canon_search(const float *X, int64_t n, int32_t d, int32_t pitch, const uint32_t *adj, int32_t ell,
                         uint32_t entry, int32_t L, int64_t x0, int64_t count, const double *xmax2, uint32_t *ids,
                         double *dists, int32_t *counts, hipStream_t stream);
-// canon.hip: the enhancement (GpuCtx::enhance)
+// canon.hip: GpuCtx's functions
+int canon_pivots(const GpuCtx &gpu, int64_t nt, int32_t Nq, uint32_t *out);
+int canon_lists(const GpuCtx &gpu, int64_t words, uint32_t *out);
+int canon_project(const GpuCtx &gpu, int64_t n, int32_t d, int64_t nt, int32_t Nq, const std::vector<int64_t> &boff,
+                  const std::vector<uint32_t> &bidx, int32_t L, int32_t m, int32_t ell, std::vector<uint32_t> *pj,
+                  std::vector<int32_t> *pj_n);
 int canon_enhance(const GpuCtx &gpu, int64_t n, int32_t d, const std::vector<uint32_t> &adj, int32_t ell,
                   uint32_t entry, int32_t L, int32_t m, int32_t head_len, std::vector<uint32_t> *ce,
                   std::vector<int32_t> *ce_n, uint32_t *head, int32_t *head_n, double *t_search);

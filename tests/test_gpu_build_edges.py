@@ -47,3 +47,23 @@ def test_build_edges(dev, oracle_lib, case, n, nt, d, Nq, M, L, m_pj, m_ce):
         X[5] *= 6
         X[17] *= 1.5
     check(dev, oracle_lib, X, T, Nq, M, L, m_pj, m_ce)
+
+
+# the projection: lists of 63 and 64 entries (one and two slots per lane) that
+# overflow, few pivots with many bridges (over 512 candidates), lists of two
+# entries, pivots with fewer candidates than places
+@pytest.mark.parametrize("case,n,nt,d,Nq,M,L,m_pj,m_ce", [
+    ("plain", 1200, 4000, 24, 120, 128, 200, 63, 40), ("copies", 1200, 4000, 24, 120, 128, 200, 64, 40),
+    ("few", 1000, 3000, 40, 224, 64, 500, 0, 0), ("hub", 1500, 3000, 20, 50, 8, 100, 2, 3),
+    ("plain", 400, 60, 130, 2, 40, 64, 20, 8)])
+def test_projection_edges(dev, oracle_lib, case, n, nt, d, Nq, M, L, m_pj, m_ce):
+    g = datagen.Generator(3, n=n, n_train=nt, n_test=1, d=max(d, 32))
+    X, T = np.ascontiguousarray(g.base()[:, :d]), np.ascontiguousarray(g.train()[:, :d])
+    if case == "copies":
+        X[1::3] = X[0::3][:len(X[1::3])]
+        X[700:760] = X[3]
+    if case == "hub":
+        X[5:9] *= 5
+    if case == "few":
+        X[::40] *= 3
+    check(dev, oracle_lib, X, T, Nq, M, L, m_pj, m_ce)
