@@ -110,15 +110,21 @@ constexpr int shape_nch(int st, int cls) {
     constexpr int n32[6] = {1, 2, 7, 4, 8, 8}, n16[6] = {1, 1, 4, 4, 4, 4}, n8[6] = {2, 2, 2, 3, 3, 3};
     return st == RG_STORE_FP32 ? n32[cls] : st == RG_STORE_BF16 ? n16[cls] : n8[cls];
 }
-// R: what the registers hold beside the chunks.  With four rows in flight the
-// BF16 and E4M3 shapes of d > 256 need the registers of 4 wavefronts per SIMD
-// instead of 5, and are faster all the same, as each wavefront waits half as
-// often (10,000 queries, 4 KB of visited set, two rows -> four, ms: E4M3 2M x
-// 512 L = 409 33.6 -> 29.4, 1M x 512 L = 150 11.9 -> 11.1, 1M x 384 L = 300
-// 18.6 -> 17.3; BF16 1M x 512 L = 409 27.8 -> 27.7, L = 805 55.2 -> 54.1).  At
+// R: what the registers hold beside the chunks; a wavefront waits once per
+// round of rows.  Two rows -> R, ms for 10,000 queries at the same visited
+// set: FP32 1M x 64 L = 200 4.86 -> 4.55, 1M x 96 L = 100 2.95 -> 2.84 (eight
+// rows 3.12), 1M x 250 L = 200 12.96 -> 12.77; BF16 1M x 64 L = 200 3.86 ->
+// 3.58, 1M x 100 L = 200 4.74 -> 4.46 (four rows 4.58), 1M x 200 L = 409
+// unchanged by three; E4M3 1M x 256 L = 300 11.0 -> 10.6 with three.  With four
+// the BF16 and E4M3 shapes of d > 256 need the registers of 4 wavefronts per
+// SIMD instead of 5 and are faster all the same: E4M3 2M x 512 L = 409 33.6 ->
+// 29.4, 1M x 512 L = 150 11.9 -> 11.1; BF16 1M x 512 L = 805 55.2 -> 54.1.  At
 // d <= 256 the fifth wavefront is worth more (E4M3 1M x 256 L = 409, 1 KB:
 // 14.7 -> 17.8).
-constexpr int shape_r(int st, int cls) { return (st == RG_STORE_FP8E4M3 && cls <= 2) || (st != RG_STORE_FP32 && cls >= 4) ? 4 : 2; }
+constexpr int shape_r(int st, int cls) {
+    constexpr int r32[6] = {8, 4, 2, 4, 2, 2}, r16[6] = {8, 8, 2, 2, 4, 4}, r8[6] = {4, 4, 4, 3, 4, 4};
+    return st == RG_STORE_FP32 ? r32[cls] : st == RG_STORE_BF16 ? r16[cls] : r8[cls];
+}
 
 // Copy the query into LDS, zero padded to qpad (every element a row chunk
 // can reach, so bytes past d meet a zero).
@@ -525,12 +531,14 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
 
 // One scheduler step of the serving loop: advance each listed slot by up to
 // hops_budget expansions, keeping its whole state in device memory.  Five
-// resident wavefronts per SIMD, as for k_search: the step is latency-bound.
+// resident wavefronts per SIMD where the registers hold the rows in flight:
+// the step is latency-bound.
 // Slot state word 0: 0 = admitted, not started; > 0 = queue length of a
 // search in progress; -1 = finished (its record written; the slot is
 // skipped until the host admits a new request into it).
 template <int ST, int CLS, class VIS>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(ST == RG_STORE_FP32 || CLS >= 4 ? 4 : 5))) void k_serve_step(SlotArgs sa) {
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(ST == RG_STORE_FP32 || CLS >= 3 ? 4 : 5)))
+void k_serve_step(SlotArgs sa) {
     extern __shared__ __align__(16) unsigned char smem[];
     const int slot = sa.active[blockIdx.x];
     if (sa.slot_state[(size_t)slot * 8] < 0) return;
