@@ -253,18 +253,19 @@ int rg_index_set_storage(rg_index *idx, int32_t storage, void *stream);
  * The search expands the closest unexpanded queue entry until none is left;
  * a neighbour enters the queue if the queue is not full or it beats the last
  * entry.  With reduced-precision storage the final L_eff queue is rescored
- * against the FP32 rows and the best k are returned.  FP32 storage keeps an
- * exact visited set per query (a bitmap in device memory or, for small bases,
- * in LDS; for few queries a table in LDS that overflows into one) while n/8
- * bytes
- * stay below 5% of a query's expected row bytes (40 L_eff rows of 4d
- * bytes) or the graph is held as CSR (rows over 128 ids);
- * otherwise, and for BF16 / FP8, a visited table in LDS that forgets and
- * rescores (the results are the same; evals counts the rescoring): 4, 2 or 1
- * KB of it, the largest that keeps the most wavefronts at work (1 KB only
- * while twice a row batch is at most 256 ids).  For n up to 2^24 (4 KB: 2^25;
- * 1 KB: 2^23) and rows of at most 64 ids it holds 16-bit entries in sets of
- * four that drop their oldest; otherwise node ids, cleared at half load.
+ * against the FP32 rows and the best k are returned.  With FP32 storage
+ * evals are the exact counts while n/8 bytes stay below 5% of a query's
+ * expected row bytes (40 L_eff rows of 4d bytes) or the graph is held as CSR
+ * (rows over 128 ids): an exact visited set per query (a bitmap in device
+ * memory or, for small bases, in LDS; for few queries a table in LDS that
+ * overflows into one).  Larger batches that do not ask for evals, other FP32
+ * indexes, BF16 and FP8 use a visited table in LDS that forgets and rescores
+ * (the results are the same; evals counts the rescoring): 4, 2 or 1 KB of it,
+ * the largest that keeps the most wavefronts at work (1 KB only while twice a
+ * row batch is at most 256 ids), or 8 KB for FP32 rows of d > 128.  For n up
+ * to 2^24 (4 KB: 2^25; 1 KB: 2^23) and rows of at most 64 ids it holds 16-bit
+ * entries in sets of four that drop their oldest; otherwise node ids, cleared
+ * at half load.
  * Asynchronous on stream.
  * Errors: RG_EINVAL, RG_EDEVICE.
  */

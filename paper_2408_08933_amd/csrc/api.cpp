@@ -150,23 +150,26 @@ void set_table(SearchArgs &a, int hash_bits) {
 namespace {
 
 // The size: the largest of 4, 2 and 1 KB that keeps the most wavefronts per
-// SIMD at work, as far as there are queries for them.  A smaller table scores
-// more rows (about 7% from one size to the next), fewer wavefronts wait
-// longer for each: per row, E4M3 d = 200 L = 409 takes 0.69 / 0.80 / 1.00 (us
-// x 1e-3) at 20 / 16 / 11 workgroups per CU, BF16 d = 128 0.54 / 0.67 at 24 /
-// 16, and counts between two multiples of 4 run like the lower one (a SIMD
-// more or less).  The LDS is handed out in 1,280-byte pieces, which the
-// occupancy query leaves out.  Rows of d > 256 keep more loads in flight on
-// fewer wavefronts, so rescoring costs them more than the wavefronts do: they
-// take the largest table (4 / 2 / 1 KB, ms for 10,000 queries: E4M3 2M x 512
-// L = 409 29.4 / 30.4 / 31.6, 1M x 384 L = 300 17.3 / 18.0 / 18.6; BF16 1M x
-// 512 L = 409 28.1 / 30.2 / 32.4; 300k x 1000 L = 200, 5,000 queries 13.0 /
-// 14.2 / 15.5).
+// SIMD at work, up to five, as far as there are queries for them.  A smaller
+// table scores more rows (about 7% from one size to the next), fewer
+// wavefronts wait longer for each: per row, E4M3 d = 200 L = 409 takes 0.69 /
+// 0.80 / 1.00 (us x 1e-3) at 20 / 16 / 11 workgroups per CU, and counts between
+// two multiples of 4 run like the lower one (a SIMD more or less).  A sixth per
+// SIMD is not worth a smaller table (BF16 1M x 100 L = 200 at 20 / 24: 4.5 /
+// 5.2 ms; 1M x 256 L = 300 11.1 / 12.0).  The LDS is handed out in 1,280-byte
+// pieces, which the occupancy query leaves out.  Long rows keep more loads in
+// flight on fewer wavefronts, so rescoring costs them more than the wavefronts
+// do: d > 256 takes 4 KB (4 / 2 / 1 KB, ms for 10,000 queries: E4M3 2M x 512 L
+// = 409 29.4 / 30.4 / 31.6, 1M x 384 L = 300 17.3 / 18.0 / 18.6; BF16 1M x 512
+// L = 409 28.1 / 30.2 / 32.4), and FP32 rows of d > 128 8 KB while that leaves
+// two wavefronts per SIMD (16 / 8 / 4 KB: 1M x 200 L = 100 10.3 / 10.3 / 10.8,
+// L = 400 24.0 / 21.1 / 22.6, 1M x 150 L = 200 9.97 / 8.42 / 8.69, 1M x 384
+// 20.6 / 20.9 / 21.7; 1M x 128 L = 400 19.2 / 13.9 / 12.8).
 int choose_table(SearchArgs &a, int cus) {
     const int width = a.adj_off ? kMaxEll : a.ell;  // ids inserted per batch
     const int64_t want = (a.nq + cus - 1) / std::max(1, cus);
     int best = 10, occ = -1;
-    for (int hb = 10; hb >= 8; --hb) {
+    for (int hb = a.storage == RG_STORE_FP32 && a.d > 128 ? 11 : 10; hb >= 8; --hb) {
         if ((1 << hb) < 2 * width + 2) break;
         int o = 0;
         set_table(a, hb);
@@ -175,12 +178,15 @@ int choose_table(SearchArgs &a, int cus) {
         const int piece = 1280, lds = (int)search_lds_bytes(a.Leff, a.qpad, hb, a.cand);
         o = std::min(o, (160 << 10) / ((lds + piece - 1) / piece * piece));
         if (o >= 4) o &= ~3;
-        o = (int)std::min<int64_t>(o, want);
+        o = (int)std::min<int64_t>(std::min(o, 20), want);
         if (o > occ) {
             occ = o;
             best = hb;
         }
-        if (hb == 10 && a.d > 256 && o >= 8) break;
+        if ((hb == 11 || (hb == 10 && a.d > 256)) && o >= 8) {
+            best = hb;
+            break;
+        }
     }
     set_table(a, best);
     return RG_OK;
@@ -996,35 +1002,42 @@ int rg_search(const rg_index *ix, const float *queries, int64_t nq, int32_t k, i
     SearchArgs a = search_args(ix, queries, nq, k, L, ids, dists, hops, evals);
     int cus = 0;
     RG_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, ix->device));
-    // FP32 rows keep an exact visited bitmap (about n/8 bytes per query: the
-    // clear, then the lines its atomics dirty) while that stays below 5% of a
-    // query's expected row bytes (about 40 L_eff rows of 4d bytes, as measured
-    // on built indexes: the graph's mean degree says little, the expanded
-    // nodes being its dense part), and always for CSR graphs, whose wide rows
-    // would overflow a table at every expansion.  Measured: the bitmap is
-    // faster at 1M x 200 (L = 183) and 8M x 512 (L = 500), the table at 10M x
-    // 200 (L = 439, by 28%).
+    // FP32 rows have an exact visited set where a bitmap (about n/8 bytes per
+    // query) stays below 5% of a query's expected row bytes (about 40 L_eff
+    // rows of 4d bytes, as measured on built indexes: the graph's mean degree
+    // says little, the expanded nodes being its dense part) and either LDS
+    // holds it, the caller asks for the number of rows scored, or a table could
+    // not have sets, and always for CSR graphs, whose wide rows would overflow
+    // a table at every expansion.  A bitmap in device memory costs more than the rows that a
+    // table scores again: its lines miss the caches, and each of its atomics
+    // reads and writes one.  Bitmap / table, 10,000 queries: 1M x 200 L = 100
+    // 14.0 / 10.3 ms (7,503 / 7,671 rows per query), L = 400 28.1 / 21.1, L =
+    // 800 51.2 / 44.0, 1M x 96 L = 200 9.0 / 5.0, 1M x 384 L = 200 29.1 / 20.9.
     const bool exact = ix->storage == RG_STORE_FP32 &&
                        (ix->d_adj_off || (double)ix->n / 8.0 <= 0.05 * 40.0 * std::max(L, k) * 4.0 * ix->d);
     a.bm_words = ((ix->n + 31) / 32 + 63) / 64 * 64;
     int rc = RG_OK;
     // Few queries: 8 wavefronts per query while that is one workgroup per CU
     // (two wavefronts per SIMD with this kernel's registers), 4 up to two
-    // workgroups, 2 up to four where the visited set is small.  Beyond, and
-    // at two wavefronts with queues over 512 entries or an exact set (which
-    // would overflow in the LDS left for it), one wavefront per query is
-    // faster.  Measured, us, one wavefront / several: FP32 300k x 200 L = 100
-    // 1 query 808 / 530, 256 1,330 / 950, 512 1,390 / 1,140, (768 1,470 /
-    // 1,520); BF16 200k x 512 L = 200 1 query 1,840 / 1,280, 512 2,660 / 2,060,
-    // 1,024 3,150 / 2,770; E4M3 500k x 512 L = 409 1,024 queries 9,000 / 6,200;
-    // BF16 500k x 200 L = 805 512 queries 7,600 / 7,200, (768 7,540 / 9,330).
+    // workgroups, both with an exact set where one is due, and 2 up to four
+    // with a table.  Beyond, and at two wavefronts with queues over 512 entries
+    // or on a base whose bitmap LDS holds, one wavefront per query is faster.
+    // Measured, us, one wavefront / several: FP32 300k x 200 L = 100 1 query
+    // 808 / 530, 256 1,330 / 950, 512 1,390 / 1,140, 1M x 200 1,000 queries
+    // 1,560 / 1,270, 1M x 512 1,000 2,990 / 2,370, 10k x 64 L = 200 1,000 900 /
+    // 1,270; BF16 200k x 512 L = 200 1 query 1,840 / 1,280, 512 2,660 / 2,060,
+    // 1,024 3,150 / 2,770; E4M3 500k x 512 L = 409 1,024 9,000 / 6,200; BF16
+    // 500k x 200 L = 805 512 7,600 / 7,200, 768 7,540 / 9,330.
     set_table(a, 10);
-    const int64_t most = (exact || a.Leff > kMaxL ? 2 : 4) * (int64_t)cus;
-    if (!a.adj_off && a.ell <= 64 && (exact || a.sets) && nq <= most) {
+    // evals asks for the exact counts
+    const bool counts = exact && (evals || !a.sets);
+    const int64_t most = (counts || a.Leff > kMaxL ? 2 : 4) * (int64_t)cus;
+    const bool bits = exact && !a.adj_off && ix->n <= 32 << 10;
+    if (!a.adj_off && a.ell <= 64 && nq <= most && ((exact && nq <= 2 * (int64_t)cus) || (a.sets && !bits))) {
         a.grid = nq <= cus ? 8 : nq <= 2 * (int64_t)cus ? 4 : 2;
         a.prep = 2;
         void *ws = nullptr;
-        if (exact) {
+        if (exact && nq <= 2 * (int64_t)cus) {
             // room for twice the expected nodes, as LDS allows
             a.sets = 0;
             a.hash_bits = 11;
@@ -1044,20 +1057,20 @@ int rg_search(const rg_index *ix, const float *queries, int64_t nq, int32_t k, i
         }
         return rc;
     }
-    if (!exact) {
-        // BF16 / FP8 rows: the search waits on memory latency, not bandwidth;
-        // a small LDS visited table (no device atomics) is faster even though
-        // it forgets and rescores some rows (same results)
-        rc = choose_table(a, cus);
-        return rc ? rc : launch_search(a, st);
-    }
-    if (!a.adj_off && ix->n <= 32 << 10) {
+    if (bits) {
         // a small base: its bitmap fits in 4 KB of LDS, without the atomics'
         // way to device memory and back at every expansion (10k x 64, 1,000
         // queries, L = 50: 431 -> 360 us)
         a.hash_bits = 6;
         while ((32ll << a.hash_bits) < ix->n) ++a.hash_bits;
         return launch_search_bits(a, st);
+    }
+    if (!counts) {
+        // the search waits on memory latency: a small visited table in LDS (no
+        // device atomics) is faster even though it forgets and rescores some
+        // rows (same results)
+        rc = choose_table(a, cus);
+        return rc ? rc : launch_search(a, st);
     }
     // persistent grid: as many resident workgroups as the chip holds, each
     // with its own visited bitmap (bounded to 8 GiB in total)
