@@ -41,6 +41,19 @@ __device__ __forceinline__ double dpp_read(double v) {
     return __longlong_as_double(((long long)hi << 32) | (uint32_t)lo);
 }
 
+// v of lane src (the same for all lanes), whichever lanes are active
+__device__ __forceinline__ uint32_t lane_value(uint32_t v, int src) {
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, src);
+}
+__device__ __forceinline__ float lane_value(float v, int src) {
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), src));
+}
+__device__ __forceinline__ double lane_value(double v, int src) {
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_readlane((int)b, src), hi = __builtin_amdgcn_readlane((int)(b >> 32), src);
+    return __longlong_as_double(((long long)hi << 32) | (uint32_t)lo);
+}
+
 // Sum of the G lanes of each group, valid in the group's first lane.  The
 // steps are those of an xor butterfly with the largest offset first, as
 // seen from the first lane, so the value is the butterfly's bit for bit;
