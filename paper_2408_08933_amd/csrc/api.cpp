@@ -1021,17 +1021,20 @@ int rg_search(const rg_index *ix, const float *queries, int64_t nq, int32_t k, i
     // (two wavefronts per SIMD with this kernel's registers), 4 up to two
     // workgroups, both with an exact set where one is due, and 2 up to four
     // with a table.  Beyond, and at two wavefronts with queues over 512 entries
-    // or on a base whose bitmap LDS holds, one wavefront per query is faster.
-    // Measured, us, one wavefront / several: FP32 300k x 200 L = 100 1 query
-    // 808 / 530, 256 1,330 / 950, 512 1,390 / 1,140, 1M x 200 1,000 queries
-    // 1,560 / 1,270, 1M x 512 1,000 2,990 / 2,370, 10k x 64 L = 200 1,000 900 /
-    // 1,270; BF16 200k x 512 L = 200 1 query 1,840 / 1,280, 512 2,660 / 2,060,
-    // 1,024 3,150 / 2,770; E4M3 500k x 512 L = 409 1,024 9,000 / 6,200; BF16
-    // 500k x 200 L = 805 512 7,600 / 7,200, 768 7,540 / 9,330.
+    // or on a base whose bitmap LDS holds or with rows of under 512 bytes, one
+    // wavefront per query is faster.  Measured, us, one wavefront / several:
+    // FP32 300k x 200 L = 100 1 query 720 / 510, 512 1,390 / 1,140, 1M x 200 L =
+    // 200 700 queries 2,740 / 2,440, 1M x 512 L = 100 1,000 2,990 / 2,370, 1M x
+    // 96 L = 200 800 2,210 / 2,310, 10k x 64 L = 200 1,000 900 / 1,270; BF16
+    // 200k x 512 L = 200 16 queries 2,090 / 1,190, 500k x 512 L = 400 1,024
+    // 5,870 / 4,690, 500 with L = 800 9,620 / 6,410, 300k x 200 L = 400 700
+    // 3,570 / 4,190; E4M3 500k x 512 L = 400 1,024 7,300 / 5,800, 300k x 100 L =
+    // 200 1,000 1,750 / 2,250; BF16 500k x 200 L = 805 768 7,540 / 9,330.
     set_table(a, 10);
     // evals asks for the exact counts
     const bool counts = exact && (evals || !a.sets);
-    const int64_t most = (counts || a.Leff > kMaxL ? 2 : 4) * (int64_t)cus;
+    const int row_bytes = ix->d * (ix->storage == RG_STORE_FP32 ? 4 : ix->storage == RG_STORE_BF16 ? 2 : 1);
+    const int64_t most = (counts || a.Leff > kMaxL || row_bytes < 512 ? 2 : 4) * (int64_t)cus;
     const bool bits = exact && !a.adj_off && ix->n <= 32 << 10;
     if (!a.adj_off && a.ell <= 64 && nq <= most && ((exact && nq <= 2 * (int64_t)cus) || (a.sets && !bits))) {
         a.grid = nq <= cus ? 8 : nq <= 2 * (int64_t)cus ? 4 : 2;

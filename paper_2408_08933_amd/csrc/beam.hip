@@ -685,102 +685,62 @@ struct VisitSetsWide : VisitSets {
 };
 
 // Merge one candidate per lane (cand: it takes part) into the sorted queue of
-// up to 64 * QR entries: the result of merge_batch, in fewer dependent steps
-// (one wavefront has its SIMD to itself here and each LDS round trip and each
-// ballot counts).  The entries that move count the candidates ahead of them in
-// registers.  A candidate's place comes from counting the entries ahead of it
-// where they are two per lane (3.2k cycles a merge at L = 100 against 4.4k
-// with the search), else from a 4-ary search (6.2k against 7.1k at L = 200,
-// 8.5k against 17k at L = 805).  A candidate that is queued, or that stands
-// earlier in the batch, is dropped.
+// up to 64 * QR entries by counting, for two entries per lane: each survivor
+// is read out of its lane and compared with every entry, which gives its place
+// and the entries' moves without a look into LDS; three ballots or more each.
+// A candidate that is queued, or that stands earlier in the batch, is dropped.
+// One query, 300k x 200 L = 100: 525 us against 560 with merge_held; at more
+// entries per lane merge_held wins (16 queries BF16 200k x 512 L = 200 1,400 ->
+// 1,190 us, 500 queries 500k x 512 L = 800 7,500 -> 6,420).
 template <int QR>
 __device__ __forceinline__ void merge_lanes(float *qd, uint32_t *qi, int Leff, int &qn, int &ptr, float kc, uint32_t ic,
                                             bool cand) {
-    constexpr bool kCount = QR <= 2;
     const int lane = lane_id();
     bool sv = cand;
     if (qn == Leff) sv = cand && kless(kc, ic, qd[Leff - 1], qi[Leff - 1] & ~kExpanded);
-    uint64_t all = ballot64(sv);
+    const uint64_t all = ballot64(sv);
     if (all == 0) return;
     int sh[QR];  // candidates ahead of entry 64 r + lane
     float k[QR];
     uint32_t v[QR];
 #pragma unroll
-    for (int r = 0; r < QR; ++r) sh[r] = 0;
-    int lb = 0;  // queue entries ahead of this candidate
-    if constexpr (kCount) {
-#pragma unroll
-        for (int r = 0; r < QR; ++r) {
-            const int i = r * 64 + lane;
-            k[r] = __builtin_inff();
-            v[r] = kNone;
-            if (i < qn) {
-                k[r] = qd[i];
-                v[r] = qi[i];
-            }
+    for (int r = 0; r < QR; ++r) {
+        const int i = r * 64 + lane;
+        sh[r] = 0;
+        k[r] = __builtin_inff();
+        v[r] = kNone;
+        if (i < qn) {
+            k[r] = qd[i];
+            v[r] = qi[i];
         }
-    } else {
-        if (sv) {
-            // at most 1,023: a full queue of 1,024 has an entry behind every survivor
-            for (int st = qn >= 256 ? 256 : qn >= 64 ? 64 : qn >= 16 ? 16 : qn >= 4 ? 4 : 1; st > 0; st >>= 2) {
-                int c = 0;
-#pragma unroll
-                for (int j = 1; j <= 3; ++j) {
-                    const int i = lb + j * st - 1;
-                    if (i < qn) c += kless(qd[i], qi[i] & ~kExpanded, kc, ic) ? 1 : 0;
-                }
-                lb += c * st;
-            }
-            if (lb < qn && (qi[lb] & ~kExpanded) == ic) sv = false;  // queued already
-        }
-        all = ballot64(sv);
-        if (all == 0) return;
     }
-    int ahead = 0, total = 0, lbmin = INT_MAX;
+    int lb = 0, ahead = 0, total = 0, lbmin = INT_MAX;
     for (uint64_t m = all; m; m &= m - 1) {
         const int src = (int)__builtin_ctzll(m);
-        const float ks = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(kc), src));
-        const uint32_t is = (uint32_t)__builtin_amdgcn_readlane((int)ic, src);
+        const float ks = lane_value(kc, src);
+        const uint32_t is = lane_value(ic, src);
         uint64_t drop = ballot64(sv && ic == is && lane < src);
         int ls = 0;
-        if constexpr (kCount) {
-            bool less[QR];
+        bool less[QR];
 #pragma unroll
-            for (int r = 0; r < QR; ++r) {
-                const uint32_t id = v[r] & ~kExpanded;
-                less[r] = kless(k[r], id, ks, is);
-                ls += (int)__popcll(ballot64(less[r]));
-                drop |= ballot64(id == is);
-            }
-            if (drop) {
-                if (lane == src) sv = false;
-                continue;
-            }
-#pragma unroll
-            for (int r = 0; r < QR; ++r) sh[r] += less[r] ? 0 : 1;
-            if (lane == src) lb = ls;
-        } else {
-            if (drop) {
-                if (lane == src) sv = false;
-                continue;
-            }
-            ls = __builtin_amdgcn_readlane(lb, src);
-#pragma unroll
-            for (int r = 0; r < QR; ++r) sh[r] += r * 64 + lane >= ls ? 1 : 0;
+        for (int r = 0; r < QR; ++r) {
+            const uint32_t id = v[r] & ~kExpanded;
+            less[r] = kless(k[r], id, ks, is);
+            ls += (int)__popcll(ballot64(less[r]));
+            drop |= ballot64(id == is);
         }
+        if (drop) {
+            if (lane == src) sv = false;
+            continue;
+        }
+#pragma unroll
+        for (int r = 0; r < QR; ++r) sh[r] += less[r] ? 0 : 1;
+        if (lane == src) lb = ls;
         ahead += kless(ks, is, kc, ic) ? 1 : 0;
         lbmin = min(lbmin, ls);
         ++total;
     }
     if (total == 0) return;
-    if constexpr (!kCount) {
-#pragma unroll
-        for (int r = 0; r < QR; ++r)
-            if (r * 64 + 63 >= lbmin && r * 64 + lane < qn) {
-                k[r] = qd[r * 64 + lane];
-                v[r] = qi[r * 64 + lane];
-            }
-    }
     wave_sync();
 #pragma unroll
     for (int r = 0; r < QR; ++r)
@@ -812,6 +772,7 @@ struct alignas(16) WideLds {
     int n_done, state, qn, count;
     uint32_t hops, evals;
     int pad[2];
+    uint32_t bits[kMaxSearchL / 32];  // of the merge
 };
 // rows in flight per group: 32 chunks per lane, 4 to 8 rows
 constexpr int wide_r(int nch) { return nch >= 8 ? 4 : nch * 8 <= 32 ? 8 : 32 / nch; }
@@ -1005,7 +966,10 @@ __global__ __launch_bounds__(64 * kWide) __attribute__((amdgpu_waves_per_eu(2)))
             ++nd;
             ++hops;
             seen += (int)__popcll(m);
-            merge_lanes<QR>(qd, qi, Leff, qn, ptr, kc, x, scored);
+            if constexpr (QR <= 2)
+                merge_lanes<QR>(qd, qi, Leff, qn, ptr, kc, x, scored);
+            else
+                merge_held<float, false, true>(qd, qi, s.bits, Leff, qn, ptr, kc, scored ? x : kNone, 0.f);
         }
         if (lane == 0) s.n_done = nd;
     }

@@ -177,13 +177,17 @@ __device__ __forceinline__ int count_le(const int32_t *slb, int S, int i) {
 // after: FP32 10k x 64 L = 50, 1,000 queries 360 -> 315; E4M3 1M x 100 L = 200,
 // 10,000 queries 4,290 -> 4,110; BF16 300k x 200 L = 200, 1,500 queries 2,200 ->
 // 2,050.
-template <typename K, bool NEAR>
-__device__ __forceinline__ bool merge_one(const QueueLds<K> &s, int cnt, int Leff, int &qn, int &ptr, K tol) {
+// bits: kMaxSearchL / 32 words of LDS.  DUPS: a candidate may stand in several
+// lanes; all but the first are dropped.
+template <typename K, bool NEAR, bool DUPS>
+__device__ __forceinline__ bool merge_held(K *qd, uint32_t *qi, uint32_t *bits, int Leff, int &qn, int &ptr, K kc,
+                                           uint32_t ic, K tol) {
+    static_assert(!DUPS || sizeof(K) == 4, "");
     int lane = lane_id();
     asm volatile("" : "+v"(lane));  // places per lane are cheaper to make than to keep in registers
     const bool full = qn == Leff;
-    const K lastd = s.qd[qn - 1], kc = s.cd[lane];
-    const uint32_t lasti = s.qi[qn - 1] & ~kExpanded, ic = lane < cnt ? s.ci[lane] : kNone;
+    const K lastd = qd[qn - 1];
+    const uint32_t lasti = qi[qn - 1] & ~kExpanded;
     bool sv = ic != kNone && (!full || kless(kc, ic, lastd, lasti));
     bool close = false;
     if constexpr (NEAR) close = full && ic != kNone && !(fabs(kc - lastd) > tol) && ic != lasti;
@@ -199,8 +203,8 @@ __device__ __forceinline__ bool merge_one(const QueueLds<K> &s, int cnt, int Lef
 #pragma unroll
         for (int j = 0; j < 3; ++j) {
             const int i = min(lb + (j + 1) * st, qn) - 1;
-            k[j] = s.qd[i];
-            v[j] = s.qi[i] & ~kExpanded;
+            k[j] = qd[i];
+            v[j] = qi[i] & ~kExpanded;
         }
         int c = 0;
 #pragma unroll
@@ -208,23 +212,31 @@ __device__ __forceinline__ bool merge_one(const QueueLds<K> &s, int cnt, int Lef
         lb += c * st;
     }
     const int at = min(lb, qn - 1);
-    if (sv) sv = lb >= qn || (s.qi[at] & ~kExpanded) != ic;  // not queued already
+    if (sv) sv = lb >= qn || (qi[at] & ~kExpanded) != ic;  // not queued already
     if constexpr (NEAR) {
-        const K ka = s.qd[at], kb = s.qd[max(lb - 1, 0)];
+        const K ka = qd[at], kb = qd[max(lb - 1, 0)];
         close |= sv && ((lb > 0 && !(kc - kb > tol)) || (lb < qn && !(ka - kc > tol)));
         if (ballot64(close)) return false;
     }
-    const uint64_t all = ballot64(sv);
+    uint64_t all = ballot64(sv);
     if (all == 0) return true;
     int ahead = 0;
     if constexpr (sizeof(K) == 4) {
         // keys that order like (key, id)
         const uint32_t f = __float_as_uint(kc + 0.f), o = f ^ ((uint32_t)((int32_t)f >> 31) | 0x80000000u);
         const uint64_t mine = ((uint64_t)o << 32) | ic;
-        for (uint64_t m = all; m; m &= m - 1) {
-            const int src = (int)__builtin_ctzll(m);
-            const uint64_t other = ((uint64_t)lane_value(o, src) << 32) | lane_value(ic, src);
-            ahead += other < mine ? 1 : 0;
+        for (;;) {
+            bool dup = false;
+            for (uint64_t m = all; m; m &= m - 1) {
+                const int src = (int)__builtin_ctzll(m);
+                const uint64_t other = ((uint64_t)lane_value(o, src) << 32) | lane_value(ic, src);
+                ahead += other < mine ? 1 : 0;
+                if constexpr (DUPS) dup |= sv && other == mine && src < lane;
+            }
+            if (!DUPS || ballot64(dup) == 0) break;
+            sv = sv && !dup;
+            all = ballot64(sv);
+            ahead = 0;
         }
     } else {
         for (uint64_t m = all; m; m &= m - 1) {
@@ -242,11 +254,11 @@ __device__ __forceinline__ bool merge_one(const QueueLds<K> &s, int cnt, int Lef
     const int to = lb + ahead, qn2 = min(Leff, qn + (int)__popcll(all));
     const bool stays = sv && to < Leff;
     // the bitmap of the survivors' places
-    if (lane < kMaxSearchL / 32) s.si[lane] = 0u;
+    if (lane < kMaxSearchL / 32) bits[lane] = 0u;
     wave_sync();
-    if (stays) atomicOr(&s.si[to >> 5], 1u << (to & 31));
+    if (stays) atomicOr(&bits[to >> 5], 1u << (to & 31));
     wave_sync();
-    const uint32_t word = lane < kMaxSearchL / 32 ? s.si[lane] : 0u;
+    const uint32_t word = lane < kMaxSearchL / 32 ? bits[lane] : 0u;
     int before = (int)__popcll(ballot64(stays));
     for (int r = (qn2 - 1) >> 6; r >= lbmin >> 6; --r) {
         const uint64_t w = ((uint64_t)lane_value(word, 2 * r + 1) << 32) | lane_value(word, 2 * r);
@@ -254,23 +266,31 @@ __device__ __forceinline__ bool merge_one(const QueueLds<K> &s, int cnt, int Lef
         const int p = 64 * r + lane;
         // (without an order among NaN keys places could coincide: still an entry)
         const int i = max(0, min(p - before - lanes_below(w), qn - 1));
-        const K md = s.qd[i];
-        const uint32_t mi = s.qi[i];
+        const K md = qd[i];
+        const uint32_t mi = qi[i];
         wave_sync();
         if (p >= lbmin && p < qn2 && !((w >> lane) & 1ull)) {
-            s.qd[p] = md;
-            s.qi[p] = mi;
+            qd[p] = md;
+            qi[p] = mi;
         }
         wave_sync();
     }
     if (stays) {
-        s.qd[to] = kc;
-        s.qi[to] = ic;
+        qd[to] = kc;
+        qi[to] = ic;
     }
     qn = qn2;
     ptr = min(ptr, lbmin);
     wave_sync();
     return true;
+}
+
+template <typename K, bool NEAR>
+__device__ __forceinline__ bool merge_one(const QueueLds<K> &s, int cnt, int Leff, int &qn, int &ptr, K tol) {
+    const int lane = lane_id();
+    const K kc = s.cd[lane];
+    const uint32_t ic = lane < cnt ? s.ci[lane] : kNone;
+    return merge_held<K, NEAR, false>(s.qd, s.qi, s.si, Leff, qn, ptr, kc, ic, tol);
 }
 
 template <int E, typename K, int QR = kMaxL / 64, bool NEAR = false>

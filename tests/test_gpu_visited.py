@@ -95,22 +95,26 @@ def test_few_queries_equal_the_sequential_search(dev, n, d, deg, storage):
         assert torch.equal(a[3], ev) if storage == "fp32" and n / 8 <= 8.0 * L * d else (a[3] >= ev).all(), (nq, k, L)
 
 
-# FP32 batches past the few-query kernel: sets in LDS (8 KB for d > 128) unless
-# the rows scored are asked for; rows of more than 64 ids stay with the bitmap.
-# Longest queues leave the least LDS.
-@pytest.mark.parametrize("n,d,deg", [(40000, 8, 48), (40000, 60, 24), (33000, 129, 64), (40000, 100, 90)])
-def test_fp32_batches_equal_the_sequential_search(dev, n, d, deg):
+# Batches past the few-query kernel: sets in LDS (8 KB for FP32 rows of d > 128)
+# unless the rows scored of FP32 are asked for; rows of more than 64 ids stay
+# with the bitmap; two wavefronts per query up to four queries per CU for rows
+# of 512 bytes and more.  Longest queues leave the least LDS.
+@pytest.mark.parametrize("n,d,deg,storage", [(40000, 8, 48, "fp32"), (40000, 60, 24, "fp32"), (33000, 129, 64, "fp32"),
+                                             (40000, 100, 90, "fp32"), (33000, 256, 32, "bf16"), (33000, 513, 32, "fp8")])
+def test_batches_equal_the_sequential_search(dev, n, d, deg, storage):
     g = torch.Generator().manual_seed(n + d)
     X, Q = torch.randn(n, d, generator=g), torch.randn(1300, d, generator=g).to(dev)
     off, idx = graph(n, deg, n + d)
     ix = rg.rg_index_from_csr(X.to(dev), off, idx, 7)
-    for nq, k, L in ((513, 10, 100), (1025, 10, 200), (1300, 10, 20), (1100, 1, 512), (600, 700, 1024)):
-        print(f"fp32 batch n={n} d={d} nq={nq} k={k} L={L}", flush=True)
+    if storage != "fp32":
+        rg.rg_index_set_storage(ix, rg.RG_STORE_BF16 if storage == "bf16" else rg.RG_STORE_FP8E4M3)
+    for nq, k, L in ((513, 10, 100), (1024, 10, 130), (1025, 10, 200), (1300, 10, 20), (1100, 1, 512), (600, 700, 1024)):
+        print(f"batch n={n} d={d} {storage} nq={nq} k={k} L={L}", flush=True)
         ids, ds, hops, ev = exact(ix, Q[:nq].contiguous(), k, L)
         a = rg.rg_search(ix, Q[:nq].contiguous(), k, L)
         b = rg.rg_search(ix, Q[:nq].contiguous(), k, L, stats=True)
         torch.cuda.synchronize()
         assert torch.equal(a[0], ids) and torch.equal(a[1], ds), (nq, k, L)
         assert torch.equal(b[0], ids) and torch.equal(b[1], ds) and torch.equal(b[2], hops), (nq, k, L)
-        if n / 8 <= 8.0 * max(k, L) * d:
+        if storage == "fp32" and n / 8 <= 8.0 * max(k, L) * d:
             assert torch.equal(b[3], ev), (nq, k, L)
