@@ -733,10 +733,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
         // accumulator element r of block (i, j) is query row 16 i + 4 (lane / 16)
         // + r of the wave's half, base column lane % 16 of its block
         if constexpr (SAMPLE) {
-            const bool inside = x0 + BX16 <= a.n;
+            const int rows = (int)std::min<int64_t>(a.n - x0, BX16);
+            int col0 = wc * 64 + fr;
+            asm volatile("" : "+v"(col0));  // no column kept over the sweep
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                const bool ok = inside || x0 + wc * 64 + j * 16 + fr < a.n;
+                const bool ok = col0 + j * 16 < rows;
 #pragma unroll
                 for (int i = 0; i < 4; ++i)
 #pragma unroll
@@ -745,14 +747,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
             if ((xt + 1) % a.T == 0 || xt + 1 == xt1) {
                 int row0 = wr * 64 + 4 * fg;
                 asm volatile("" : "+v"(row0));  // no address kept over the sweep
-                const int grp = xt / a.T * 32 + wc * 16 + fr;
+                int grp = wc * 16 + fr;
+                asm volatile("" : "+v"(grp));
+                grp += xt / a.T * 32;
                 float *g0 = a.gm + (q0 + row0) * a.ngroups + grp;
 #pragma unroll
                 for (int i = 0; i < 4; ++i)
 #pragma unroll
                     for (int r = 0; r < 4; ++r) {
-                        g0[(i * 16 + r) * a.ngroups] = thr[i][r];
+                        *g0 = thr[i][r];
                         thr[i][r] = -__builtin_inff();
+                        g0 += r < 3 ? a.ngroups : 13 * a.ngroups;
+                        asm volatile("" : "+v"(g0));  // one address at a time
                     }
                 wait_vm_const<0>();
             }
