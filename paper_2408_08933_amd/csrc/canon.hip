@@ -576,6 +576,7 @@ struct ReplayArgs {
     int32_t *out_n;
     int32_t out_pitch;
     const int64_t *boff;      // k_replay_fill: the bridges of each node, none if it is no pivot
+    int64_t p0;               // the first workgroup's node
 };
 
 __global__ __launch_bounds__(64) void k_replay(ReplayArgs a) {
@@ -584,7 +585,7 @@ __global__ __launch_bounds__(64) void k_replay(ReplayArgs a) {
     double *cd = reinterpret_cast<double *>(xrow + a.pitch);
     uint32_t *ci = reinterpret_cast<uint32_t *>(cd + a.m + 1);
     const int lane = lane_id();
-    const int64_t p = blockIdx.x;
+    const int64_t p = a.p0 + blockIdx.x;
     int nc = a.sel_n[p];
     for (int j = lane; j < nc; j += 64) {
         ci[j] = a.sel_ids[p * a.m + j];
@@ -672,7 +673,7 @@ __global__ __launch_bounds__(64) void k_replay_fill(ReplayArgs a) {
     extern __shared__ __align__(16) unsigned char smem[];
     float *xrow = reinterpret_cast<float *>(smem);
     const int lane = lane_id();
-    const int64_t p = blockIdx.x;
+    const int64_t p = a.p0 + blockIdx.x;
     const bool own = a.boff[p] != a.boff[p + 1];  // a pivot: its selection replaced what came before
     int nc = own ? a.sel_n[p] : 0;
     uint32_t id[SL], rank[SL];
@@ -894,8 +895,8 @@ __global__ __launch_bounds__(256) void k_place_events(const uint32_t *sel, const
 // Ascending order of the lists longer than 64 (shorter ones are sorted by the
 // wavefront that replays them): a bitonic network whose comparators all point
 // the same way, so that a length that is no power of two needs no padding.
-__global__ __launch_bounds__(256) void k_sort_events(const int64_t *off, uint32_t *src) {
-    const int64_t p = blockIdx.x;
+__global__ __launch_bounds__(256) void k_sort_events(const int64_t *off, uint32_t *src, int64_t p0) {
+    const int64_t p = p0 + blockIdx.x;
     const int64_t n = off[p + 1] - off[p];
     if (n <= 64) return;
     uint32_t *a = src + off[p];
@@ -946,6 +947,20 @@ struct Dev {
         return static_cast<T *>(p);
     }
 };
+
+// launch(first, count) over n workgroups, at most 2^18 at a time: a HIP grid
+// holds fewer than 2^32 threads, which one workgroup of 256 per node passes at
+// 2^24 nodes.  A launch of 2^18 is 32 rounds of workgroups or more, so its end
+// costs little.
+template <class F>
+int in_grids(int64_t n, F &&launch) {
+    constexpr int64_t most = 1 << 18;
+    for (int64_t p0 = 0; p0 < n; p0 += most) {
+        launch(p0, (unsigned)std::min(most, n - p0));
+        RG_HIP(hipGetLastError());
+    }
+    return RG_OK;
+}
 
 unsigned blocks_for(int64_t items) { return (unsigned)std::max<int64_t>(1, std::min<int64_t>(65536, (items + 255) / 256)); }
 
@@ -1039,8 +1054,11 @@ int selected_by(const SelectArgs &s, int64_t n, Dev &d_off, Dev &d_src, hipStrea
     RG_HIP(hipMemcpyAsync(d_off.p, off.data(), sizeof(int64_t) * (n + 1), hipMemcpyHostToDevice, st));
     hipLaunchKernelGGL(k_place_events, dim3(blocks_for(n)), dim3(256), 0, st, s.sel_ids, s.sel_n, n, s.m,
                        d_off.as<int64_t>(), d_cnt.as<uint32_t>(), d_src.as<uint32_t>());
-    hipLaunchKernelGGL(k_sort_events, dim3((unsigned)n), dim3(256), 0, st, d_off.as<int64_t>(), d_src.as<uint32_t>());
     RG_HIP(hipGetLastError());
+    const int rc = in_grids(n, [&](int64_t p0, unsigned cnt) {
+        hipLaunchKernelGGL(k_sort_events, dim3(cnt), dim3(256), 0, st, d_off.as<int64_t>(), d_src.as<uint32_t>(), p0);
+    });
+    if (rc) return rc;
     // before the counts and offsets go
     RG_HIP(hipStreamSynchronize(st));
     return RG_OK;
@@ -1141,7 +1159,7 @@ int canon_project(const GpuCtx &gpu, int64_t n, int32_t d, int64_t nt, int32_t N
         hipLaunchKernelGGL(k_select, dim3(cnt), dim3(64), lds, st, s);
         RG_HIP(hipGetLastError());
     }
-    const int rc = selected_by(s, n, d_off, d_src, st, [] {});
+    int rc = selected_by(s, n, d_off, d_src, st, [] {});
     if (rc) {
         if (rc == RG_ENOMEM) (void)hipGetLastError();
         return rc;
@@ -1161,8 +1179,11 @@ int canon_project(const GpuCtx &gpu, int64_t n, int32_t d, int64_t nt, int32_t N
     r.out_pitch = ell;
     r.boff = c.boff;
     auto k_fill = m < 64 ? k_replay_fill<1> : k_replay_fill<2>;
-    hipLaunchKernelGGL(k_fill, dim3((unsigned)n), dim3(64), (size_t)gpu.pitch * 4, st, r);
-    RG_HIP(hipGetLastError());
+    rc = in_grids(n, [&](int64_t p0, unsigned cnt) {
+        r.p0 = p0;
+        hipLaunchKernelGGL(k_fill, dim3(cnt), dim3(64), (size_t)gpu.pitch * 4, st, r);
+    });
+    if (rc) return rc;
     pj->resize((size_t)n * ell);
     pj_n->resize((size_t)n);
     RG_HIP(hipMemcpyAsync(pj->data(), d_out.p, sizeof(uint32_t) * n * ell, hipMemcpyDeviceToHost, st));
@@ -1253,8 +1274,11 @@ int canon_enhance(const GpuCtx &gpu, int64_t n, int32_t d, const std::vector<uin
     r.out = d_out.as<uint32_t>();
     r.out_n = d_on.as<int32_t>();
     r.out_pitch = m;
-    hipLaunchKernelGGL(k_replay, dim3((unsigned)n), dim3(64), (size_t)gpu.pitch * 4 + (size_t)(m + 1) * 12 + 8, st, r);
-    RG_HIP(hipGetLastError());
+    rc = in_grids(n, [&](int64_t p0, unsigned cnt) {
+        r.p0 = p0;
+        hipLaunchKernelGGL(k_replay, dim3(cnt), dim3(64), (size_t)gpu.pitch * 4 + (size_t)(m + 1) * 12 + 8, st, r);
+    });
+    if (rc) return rc;
     ce->resize((size_t)n * m);
     ce_n->resize((size_t)n);
     RG_HIP(hipMemcpyAsync(ce->data(), d_out.p, sizeof(uint32_t) * n * m, hipMemcpyDeviceToHost, st));

@@ -1,0 +1,71 @@
+"""What the library asks of the device, on the CPU: a runtime without a device (native/fake_hip.cpp) takes the place
+of HIP's, records launches instead of running them and keeps two of its rules, grids of fewer than 2^32 threads and an
+amount of memory.  Each case runs in a process of its own, which never loads the real runtime's calls."""
+import os
+import shutil
+import subprocess
+import sys
+import textwrap
+
+import pytest
+
+import paper_2408_08933_amd as rg
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CXX = shutil.which("g++")
+pytestmark = pytest.mark.skipif(not CXX, reason="needs g++")
+
+PRELUDE = """
+import ctypes as C, sys
+import numpy as np
+fake, lib = C.CDLL(sys.argv[1], C.RTLD_GLOBAL), C.CDLL(sys.argv[2])
+lib.rg_last_error.restype = C.c_char_p
+fake.fake_launch.restype = C.c_char_p
+fake.fake_launches.restype = C.c_int64
+fake.fake_most.restype = fake.fake_in_use.restype = C.c_uint64
+fake.fake_limit.argtypes, fake.fake_amax.argtypes = [C.c_uint64], [C.c_float]
+I64, P = C.c_int64, lambda a: C.c_void_p(a.ctypes.data)
+class Opts(C.Structure):
+    _fields_ = [(k, C.c_int32) for k in ("L_build", "m_pj", "m_ce", "threads", "knn_slack", "keep_stages")]
+def ok(rc):
+    assert rc == 0, (rc, lib.rg_last_error())
+def launches(*names):
+    g, b, out = C.c_uint64(), C.c_uint64(), []
+    for i in range(fake.fake_launches()):
+        name = fake.fake_launch(I64(i), C.byref(g), C.byref(b)).decode()
+        if any(n in name for n in names):
+            out.append((name, g.value, b.value))
+    return out
+def build(X, T, Nq, M, L, m_pj=0, m_ce=0, keep=0):
+    ix, o = C.c_void_p(), Opts(L, m_pj, m_ce, 8, 0, keep)
+    rc = lib.rg_build(P(X), I64(X.shape[0]), X.shape[1], P(T), I64(T.shape[0]), Nq, M, 0, C.byref(o), None, C.byref(ix))
+    if rc == 0:
+        lib.rg_free(ix)
+    return rc
+"""
+
+
+@pytest.fixture(scope="module")
+def fake(tmp_path_factory):
+    so = str(tmp_path_factory.mktemp("fake") / "fake_hip.so")
+    subprocess.run([CXX, "-std=c++17", "-O1", "-shared", "-fPIC", os.path.join(ROOT, "tests", "native", "fake_hip.cpp"),
+                    "-o", so], check=True, capture_output=True, text=True)
+    return so
+
+
+def run(fake, body, timeout=300):
+    r = subprocess.run([sys.executable, "-c", PRELUDE + textwrap.dedent(body), fake, rg.LIB_PATH], capture_output=True,
+                       text=True, timeout=timeout)
+    assert r.returncode == 0, r.stdout + r.stderr
+
+
+def test_build_past_2_to_24_rows(fake):
+    # the smallest n whose one workgroup of 256 per node is a grid of 2^32 threads, and one more
+    run(fake, """
+        n = (1 << 24) + 1
+        ok(build(np.zeros((n, 1), np.float32), np.zeros((8, 1), np.float32), 2, 3, 4, 1, 1))
+        for kernel, times in (("k_sort_events", 2), ("k_replay_fill", 1), ("k_replayE", 1)):
+            at = launches(kernel)
+            assert sum(g for _, g, _ in at) == times * n, (kernel, at)
+            assert max(g for _, g, _ in at) <= 1 << 22, (kernel, at)
+    """)
