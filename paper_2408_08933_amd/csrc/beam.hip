@@ -1031,8 +1031,19 @@ void (*persistent_kernel(int Leff))(SearchArgs) {
 template <int ST, int CLS, class VIS>
 int launch_table(const SearchArgs &a, hipStream_t stream) {
     const size_t lds = search_lds_bytes(a.Leff, a.qpad, a.hash_bits, a.cand);
-    hipLaunchKernelGGL((table_kernel<ST, CLS, VIS>(a.Leff)), dim3((unsigned)a.nq), dim3(64), lds, stream, a);
-    RG_HIP(hipGetLastError());
+    // one wavefront per query: a HIP grid holds fewer than 2^32 threads
+    constexpr int64_t most = 1 << 25;
+    for (int64_t q0 = 0; q0 < a.nq; q0 += most) {
+        SearchArgs b = a;
+        b.nq = std::min(most, a.nq - q0);
+        b.queries += q0 * a.d;
+        b.out_ids += q0 * a.k;
+        b.out_d += q0 * a.k;
+        if (a.out_hops) b.out_hops += q0;
+        if (a.out_evals) b.out_evals += q0;
+        hipLaunchKernelGGL((table_kernel<ST, CLS, VIS>(a.Leff)), dim3((unsigned)b.nq), dim3(64), lds, stream, b);
+        RG_HIP(hipGetLastError());
+    }
     return RG_OK;
 }
 

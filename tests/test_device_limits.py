@@ -69,3 +69,19 @@ def test_build_past_2_to_24_rows(fake):
             assert sum(g for _, g, _ in at) == times * n, (kernel, at)
             assert max(g for _, g, _ in at) <= 1 << 22, (kernel, at)
     """)
+
+
+@pytest.mark.parametrize("n", [300, 40_000])
+def test_search_of_2_to_26_queries(fake, n):
+    # n: a base whose visited bitmap lies in LDS, and one with a visited table.  No kernel runs, so neither queries nor
+    # results are touched
+    run(fake, f"""
+        n, nq = {n}, (1 << 26) + 1
+        X, off, idx = np.zeros((n, 64), np.float32), np.arange(n + 1), np.zeros(n, np.uint32)
+        ix = C.c_void_p()
+        ok(lib.rg_index_from_csr(P(X), I64(n), 64, P(off), P(idx), 0, 0, None, C.byref(ix)))
+        ok(lib.rg_search(ix, P(X), I64(nq), 1, 50, P(idx), P(X), None, None, None))
+        at = launches("k_search")
+        assert sum(g for _, g, _ in at) == nq and max(g for _, g, _ in at) <= 1 << 25, at
+        lib.rg_free(ix)
+    """)
