@@ -1159,6 +1159,7 @@ struct DevMem {
     int alloc(size_t bytes) {
         if (hipMalloc(&p, bytes) != hipSuccess) {
             p = nullptr;
+            (void)hipGetLastError();  // else the next launch's check would find it
             set_error("knn: out of device memory (" + std::to_string(bytes) + " bytes)");
             return RG_ENOMEM;
         }

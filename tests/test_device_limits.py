@@ -85,3 +85,16 @@ def test_search_of_2_to_26_queries(fake, n):
         assert sum(g for _, g, _ in at) == nq and max(g for _, g, _ in at) <= 1 << 25, at
         lib.rg_free(ix)
     """)
+
+
+def test_knn_without_room_for_the_sweep(fake):
+    # 131,072 queries: the sweep's buffers take 2.4 GB beside what the running top-K needs too, which fits
+    run(fake, """
+        n, nq, d, k = 8192, 1 << 17, 8, 16
+        X, Q = np.zeros((n, d), np.float32), np.zeros((nq, d), np.float32)
+        ids, ds = np.zeros((nq, k), np.uint32), np.zeros((nq, k), np.float32)
+        fake.fake_limit(1 << 30)
+        ok(lib.rg_knn(P(Q), I64(nq), P(X), I64(n), d, k, P(ids), P(ds), None))
+        assert launches("k_knn16") and not launches("k_scan16")
+        assert fake.fake_in_use() == 0
+    """)

@@ -1,0 +1,60 @@
+"""Calls on a device without room for their large buffers, on the GPU: the results are those of one with room.  Each
+case runs in a process of its own, where hipMalloc refuses requests above a limit (native/alloc_limit.cpp)."""
+import os
+import shutil
+import subprocess
+import sys
+import textwrap
+
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+PRELUDE = """
+import ctypes as C, sys
+limiter = C.CDLL(sys.argv[1], C.RTLD_GLOBAL)
+limiter.alloc_limit.argtypes, limiter.alloc_failed.restype = [C.c_uint64], C.c_int64
+import numpy as np, torch
+import paper_2408_08933_amd as rg
+g = torch.Generator().manual_seed(4)
+def with_room_and_without(call, limit):
+    a = call()
+    torch.cuda.synchronize()
+    print("with room", flush=True)
+    limiter.alloc_limit(limit)
+    b = call()
+    torch.cuda.synchronize()
+    limiter.alloc_limit(0)
+    assert limiter.alloc_failed() > 0
+    print("without", flush=True)
+    return a, b
+"""
+
+
+@pytest.fixture(scope="module")
+def limiter(tmp_path_factory):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    so = str(tmp_path_factory.mktemp("limit") / "alloc_limit.so")
+    subprocess.run([shutil.which("g++") or "c++", "-std=c++17", "-O1", "-shared", "-fPIC",
+                    os.path.join(ROOT, "tests", "native", "alloc_limit.cpp"), "-o", so, "-ldl"], check=True)
+    return so
+
+
+def run(limiter, body):
+    r = subprocess.run([sys.executable, "-u", "-c", PRELUDE + textwrap.dedent(body), limiter], cwd=ROOT,
+                       capture_output=True, text=True, timeout=100)
+    print(r.stdout, r.stderr, flush=True)
+    assert r.returncode == 0
+
+
+def test_knn_without_room_for_the_sweep(limiter):
+    # 40,000 queries: 655 MB of buffers for the sweep, none of the running top-K's above 300 MB
+    run(limiter, """
+        X, Q = torch.randn(9000, 24, generator=g).cuda(), torch.randn(40_000, 24, generator=g).cuda()
+        a, b = with_room_and_without(lambda: rg.rg_knn(Q, X, 20), 400 << 20)
+        assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1])
+    """)
