@@ -50,6 +50,7 @@ struct DevBuf {
     int alloc(size_t bytes) {
         if (hipMalloc(&p, bytes ? bytes : 1) != hipSuccess) {
             p = nullptr;
+            (void)hipGetLastError();  // callers may go on without it
             set_error("out of device memory (" + std::to_string(bytes) + " bytes)");
             return RG_ENOMEM;
         }
@@ -296,11 +297,8 @@ void knn_scan_row(const float *q, const float *X, int64_t n, int32_t d, int32_t 
 // only for the scan.  Before, both matrices were copied to the host for the
 // norms and the lists went through it: on 10k x 1M x 200 that was 215 of 270
 // ms.
-int knn_exact(const float *Qdev, int64_t nq, const float *Xdev, int64_t n, int32_t d, int32_t k, int32_t slack,
-              const float *Xhost, int threads, uint32_t *ids, float *dists, hipStream_t st) {
-    threads = hw_threads(threads);
-    if (slack <= 0) slack = std::max(16, k / 4);
-    g_knn_rows[0] = g_knn_rows[1] = g_knn_rows[2] = 0;
+int knn_rows(const float *Qdev, int64_t nq, const float *Xdev, int64_t n, int32_t d, int32_t k, int32_t slack,
+             const float *Xhost, int threads, uint32_t *ids, float *dists, int64_t (&done)[3], hipStream_t st) {
     const bool log = std::getenv("RG_LOG") != nullptr;
     const double u32 = std::ldexp(1.0, -24), u64 = std::ldexp(1.0, -53), u16 = std::ldexp(1.0, -11);
     const double g64 = (d + 1) * u64 / (1.0 - (d + 1) * u64);
@@ -330,7 +328,7 @@ int knn_exact(const float *Qdev, int64_t nq, const float *Xdev, int64_t n, int32
         uint32_t nf = 0;
         RG_HIP(hipMemcpyAsync(&nf, n_fail, 4, hipMemcpyDeviceToHost, st));
         RG_HIP(hipStreamSynchronize(st));
-        g_knn_rows[f16 ? 0 : 1] += m - (int64_t)nf;
+        done[f16 ? 0 : 1] += m - (int64_t)nf;
         if (log)
             std::fprintf(stderr, "[rg] knn %s candidates: %lld rows, K=%d, %lld not certified\n", f16 ? "FP16" : "FP32",
                          (long long)m, K, (long long)nf);
@@ -352,11 +350,14 @@ int knn_exact(const float *Qdev, int64_t nq, const float *Xdev, int64_t n, int32
         const size_t hq = 2 * (size_t)knn16_rows(nq) * dp, hx = 2 * (size_t)knn16_rows(n) * dp;
         const size_t hs = s16 > 0 ? 2 * (size_t)knn16_rows((n + s16 - 1) / s16) * dp : 0;
         DevBuf half, cand;
-        rc = half.alloc(hq + hx + hs);
-        if (rc) return rc;
-        char *q16 = half.as<char>(), *x16 = q16 + hq, *smp = s16 > 0 ? x16 + hx : nullptr;
+        // with no room for the sample the running top-K does without; with
+        // none for the copies only values out of FP16's range, which need
+        // none, can go on
+        int32_t s = s16;
+        if (half.alloc(hq + hx + hs) && (s == 0 || (s = 0, half.alloc(hq + hx)))) s = -1;
+        char *q16 = s < 0 ? nullptr : half.as<char>(), *x16 = s < 0 ? nullptr : q16 + hq, *smp = s > 0 ? x16 + hx : nullptr;
         rc = launch_pack16(Qdev, nq, d, d, q16, knn16_rows(nq), dp, nullptr, 0, st_q, st);
-        if (!rc) rc = launch_pack16(Xdev, n, d, d, x16, knn16_rows(n), dp, smp, s16, st_x, st);
+        if (!rc) rc = launch_pack16(Xdev, n, d, d, x16, knn16_rows(n), dp, smp, std::max(s, 0), st_x, st);
         if (rc) return rc;
         PackStats h[2];
         RG_HIP(hipMemcpyAsync(h, st_q, sizeof(h), hipMemcpyDeviceToHost, st));
@@ -369,6 +370,10 @@ int knn_exact(const float *Qdev, int64_t nq, const float *Xdev, int64_t n, int32
         // the sums of squares, in another order, may be off by d ulps
         xmax = h[1].nan0 ? NAN : std::sqrt(norm2) * (1.0 + 1e-12 + d * u64);
         if (std::max(aq, ax) < 32768.f) {
+            if (s < 0) {
+                set_error("knn: out of device memory for the FP16 rows");
+                return RG_ENOMEM;
+            }
             const double eta0 = std::ldexp(1.0, -25);
             const double gacc = 2.0 * dp * u32 / (1.0 - 2.0 * dp * u32);
             const double gsum = 2 * u16 + u16 * u16 + gacc * (1 + u16) * (1 + u16) + g64;
@@ -378,7 +383,7 @@ int knn_exact(const float *Qdev, int64_t nq, const float *Xdev, int64_t n, int32
             if (rc) return rc;
             uint32_t *cid = cand.as<uint32_t>();
             float *csc = reinterpret_cast<float *>(cid + (size_t)nq * K16);
-            rc = launch_knn16_candidates(q16, nq, x16, n, d, dp, smp, s16, K16, cid, csc, st);
+            rc = launch_knn16_candidates(q16, nq, x16, n, d, dp, smp, s, K16, cid, csc, st);
             if (!rc) rc = certify(Qdev, cid, csc, true, K16, gsum, eta, abs0);
             if (rc) return rc;
         }
@@ -433,7 +438,31 @@ int knn_exact(const float *Qdev, int64_t nq, const float *Xdev, int64_t n, int32
             RG_HIP(hipMemcpyAsync(dists + (int64_t)r * k, hd.data(), sizeof(float) * k, hipMemcpyHostToDevice, st));
         RG_HIP(hipStreamSynchronize(st));
     }
-    g_knn_rows[2] = m;
+    done[2] += m;
+    return RG_OK;
+}
+
+// The same for all rows, with half of them at a time where their lists do not
+// fit.
+int knn_exact(const float *Qdev, int64_t nq, const float *Xdev, int64_t n, int32_t d, int32_t k, int32_t slack,
+              const float *Xhost, int threads, uint32_t *ids, float *dists, hipStream_t st) {
+    threads = hw_threads(threads);
+    if (slack <= 0) slack = std::max(16, k / 4);
+    g_knn_rows[0] = g_knn_rows[1] = g_knn_rows[2] = 0;
+    int64_t part = nq;
+    for (int64_t q0 = 0; q0 < nq;) {
+        const int64_t cnt = std::min(part, nq - q0);
+        int64_t done[3] = {0, 0, 0};
+        const int rc = knn_rows(Qdev + q0 * d, cnt, Xdev, n, d, k, slack, Xhost, threads, ids + q0 * k,
+                                dists ? dists + q0 * k : nullptr, done, st);
+        if (rc == RG_ENOMEM && cnt >= 4096) {
+            part = (cnt + 1) / 2;
+            continue;
+        }
+        if (rc) return rc;
+        for (int i = 0; i < 3; ++i) g_knn_rows[i] += done[i];
+        q0 += cnt;
+    }
     return RG_OK;
 }
 
@@ -463,11 +492,12 @@ int rg_knn_candidates_f16(const float *queries, int64_t nq, const float *base, i
     }
     if (nq == 0) return RG_OK;
     hipStream_t st = (hipStream_t)stream;
-    const int32_t dp = knn16_width(d), s = knn16_sample(n, K);
+    const int32_t dp = knn16_width(d);
+    int32_t s = knn16_sample(n, K);
     DevBuf q16, x16, smp, stats;
     int rc = q16.alloc(2 * (size_t)knn16_rows(nq) * dp);
     if (!rc) rc = x16.alloc(2 * (size_t)knn16_rows(n) * dp);
-    if (!rc && s > 0) rc = smp.alloc(2 * (size_t)knn16_rows((n + s - 1) / s) * dp);
+    if (!rc && s > 0 && smp.alloc(2 * (size_t)knn16_rows((n + s - 1) / s) * dp)) s = 0;  // the running top-K
     if (!rc) rc = stats.alloc(2 * sizeof(PackStats));
     if (!rc)
         rc = launch_pack16(queries, nq, d, d, q16.p, knn16_rows(nq), dp, nullptr, 0, stats.as<PackStats>(), st);

@@ -935,10 +935,10 @@ __global__ void k_fill_words(uint32_t *p, int64_t n, uint32_t v) {
 }
 
 // FP32 rows -> packed FP16 (round to nearest even), zeros past (rows, d) up
-// to rows_pad x 32 nks, and in the same pass over the rows what the choice of
-// pass and the certificate need: the largest |element|, the largest squared
-// row norm (FP64), whether some element is not below 2^15 in magnitude (a NaN
-// included), and whether row 0's norm is a NaN.  Every s-th row is also
+// to rows_pad x 32 nks (dst; null: none), and in the same pass over the rows
+// what the choice of pass and the certificate need: the largest |element|, the
+// largest squared row norm (FP64), whether some element is not below 2^15 in
+// magnitude (a NaN included), and whether row 0's norm is a NaN.  Every s-th row is also
 // written to the sample, packed the same way (dst_s, when s > 0).  Sixteen
 // threads per row, each 8 coordinates at a time; bound by memory: 0.30 ms for
 // 1M x 200 (1.28 GB moved, 4.3 TB/s).
@@ -977,7 +977,8 @@ __global__ __launch_bounds__(256) void k_pack16(const float *src, int64_t rows, 
                 amax = fmaxf(amax, fabsf(v[i]));
                 bad |= !(fabsf(v[i]) < 32768.f);
             }
-            *reinterpret_cast<hx8 *>(dst + (b * nks + (c >> 2)) * BLK16 + (4 * j + ((c & 3) ^ ((j >> 2) & 3))) * 8) = h;
+            if (dst)
+                *reinterpret_cast<hx8 *>(dst + (b * nks + (c >> 2)) * BLK16 + (4 * j + ((c & 3) ^ ((j >> 2) & 3))) * 8) = h;
             if (samp) {
                 const int sj = (int)(rs & 15);
                 *reinterpret_cast<hx8 *>(dst_s + ((rs >> 4) * nks + (c >> 2)) * BLK16 +
@@ -1207,6 +1208,7 @@ int knn_range(const KnnKernel &kk, const void *Q, int64_t nq, int32_t ldq, const
     if (hipMalloc(&buf_sc, sizeof(float) * slots * kk.bq * CAP) != hipSuccess ||
         hipMalloc(&buf_id, sizeof(uint32_t) * slots * kk.bq * CAP) != hipSuccess) {
         cleanup();
+        (void)hipGetLastError();
         set_error("knn: out of device memory for candidate buffers");
         return RG_ENOMEM;
     }
@@ -1214,6 +1216,7 @@ int knn_range(const KnnKernel &kk, const void *Q, int64_t nq, int32_t ldq, const
         if (hipMalloc(&tmp_sc, sizeof(float) * splits * nq * K) != hipSuccess ||
             hipMalloc(&tmp_id, sizeof(uint32_t) * splits * nq * K) != hipSuccess) {
             cleanup();
+            (void)hipGetLastError();
             set_error("knn: out of device memory for split lists");
             return RG_ENOMEM;
         }

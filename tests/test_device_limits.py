@@ -98,3 +98,43 @@ def test_knn_without_room_for_the_sweep(fake):
         assert launches("k_knn16") and not launches("k_scan16")
         assert fake.fake_in_use() == 0
     """)
+
+
+def test_knn_out_of_fp16_range_needs_no_fp16_rows(fake):
+    # 4M x 64: FP16 rows of 537 MB, while the FP32 passes that such values take need 300 MB
+    run(fake, """
+        n, nq, d, k = 4 << 20, 1000, 64, 10
+        X, Q = np.zeros((n, d), np.float32), np.zeros((nq, d), np.float32)
+        ids, ds = np.zeros((nq, k), np.uint32), np.zeros((nq, k), np.float32)
+        fake.fake_amax(1e6)
+        fake.fake_limit(400 << 20)
+        ok(lib.rg_knn(P(Q), I64(nq), P(X), I64(n), d, k, P(ids), P(ds), None))
+        assert launches("k_knnE") and not launches("k_knn16", "k_scan16")
+        fake.fake_amax(1.0)
+        assert lib.rg_knn(P(Q), I64(nq), P(X), I64(n), d, k, P(ids), P(ds), None) == -2
+        assert fake.fake_in_use() == 0
+    """)
+
+
+def test_knn_without_room_for_the_sample(fake):
+    # 16M x 64: FP16 rows of 2.15 GB, a sample of 0.54 GB, 0.3 GB for the running top-K
+    run(fake, """
+        n, nq, d, k = 16 << 20, 1000, 64, 10
+        X, Q = np.zeros((n, d), np.float32), np.zeros((nq, d), np.float32)
+        ids, ds = np.zeros((nq, k), np.uint32), np.zeros((nq, k), np.float32)
+        fake.fake_limit(2500 << 20)
+        ok(lib.rg_knn(P(Q), I64(nq), P(X), I64(n), d, k, P(ids), P(ds), None))
+        ok(lib.rg_knn_candidates_f16(P(Q), I64(nq), P(X), I64(n), d, 58, P(ids), P(ds), None))
+        assert len(launches("k_knn16")) == 2 and not launches("k_scan16")
+    """)
+
+
+def test_build_knn_in_parts(fake):
+    # 1M lists of 100: 1.6 GB of candidates and 0.5 GB of buffers beside the lists themselves (0.4 GB), which stay
+    run(fake, """
+        n, nt, d = 8192, 1 << 20, 8
+        fake.fake_limit(2250 << 20)
+        ok(build(np.zeros((n, d), np.float32), np.zeros((nt, d), np.float32), 100, 16, 32))
+        assert sum(g for _, g, _ in launches("k_knn_certify")) == nt
+        assert fake.fake_in_use() == 0
+    """)

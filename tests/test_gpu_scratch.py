@@ -58,3 +58,22 @@ def test_knn_without_room_for_the_sweep(limiter):
         a, b = with_room_and_without(lambda: rg.rg_knn(Q, X, 20), 400 << 20)
         assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1])
     """)
+
+
+def test_knn_in_parts(limiter):
+    # 200,000 queries: 320 MB of candidates, none of the running top-K's buffers above 269 MB
+    run(limiter, """
+        X, Q = torch.randn(5000, 8, generator=g).cuda(), torch.randn(200_000, 8, generator=g).cuda()
+        a, b = with_room_and_without(lambda: rg.rg_knn(Q, X, 100), 300 << 20)
+        assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1])
+        assert sum(rg.rg_knn_last_stats().values()) == 200_000
+    """)
+
+
+def test_knn_out_of_fp16_range_without_room_for_fp16_rows(limiter):
+    # 1.25M x 128: FP16 rows of 320 MB
+    run(limiter, """
+        X, Q = 1e5 * torch.randn(1_250_000, 128, generator=g).cuda(), torch.randn(200, 128, generator=g).cuda()
+        a, b = with_room_and_without(lambda: rg.rg_knn(Q, X, 20), 300 << 20)
+        assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1])
+    """)
