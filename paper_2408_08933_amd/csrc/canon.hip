@@ -142,10 +142,11 @@ __device__ __forceinline__ void shared_sums(const CanonArgs &a, const float *q, 
 // lie within twice their error (2.5e-14 |q| |x| at d = 200) of each other; then
 // the queue is the canonical one, and its distances are computed at the end,
 // one lane per entry.  While the queue is full most candidates are far beyond
-// its last entry: FP32 sums with their own bound turn those away.  A search
-// that meets two closer keys (copies of a row, say) gives up, and a second
-// launch (redo) runs it with a canonical chain for every candidate, as all
-// searches did before.  60k rows of 200, L = 500 (about 550 expansions and
+// its last entry: FP32 sums with their own bound turn those away, unless |q|
+// times the longest row's norm is near FP32's largest value.  A search that
+// meets two closer keys (copies of a row, say) gives up, and a second launch
+// (redo) runs it with a canonical chain for every candidate, as all searches
+// did before.  60k rows of 200, L = 500 (about 550 expansions and
 // 16k rows scored each): 69.5 ms against 210; before the merge was short,
 // shared FP64 sums for every row took 117 (their conversions keep the VALU
 // busy), FP32 sums with chains for what they leave open 129, this form 83.
@@ -176,7 +177,8 @@ __global__ __launch_bounds__(64) void k_canon_search(CanonArgs a) {
         for (int o = 32; o > 0; o >>= 1) n2 += __shfl_xor(n2, o);
         const double nn = sqrt(n2 * *a.xmax2) * (1.0 + 1e-9);
         tol = 2.0 * a.gam * nn;
-        tol32 = (a.gam + a.gam32) * nn + 1e-30;  // and what underflow may lose
+        // and what underflow may lose; an FP32 sum that can overflow bounds nothing
+        tol32 = nn < 1e38 ? (a.gam + a.gam32) * nn + 1e-30 : __builtin_inf();
     }
     wave_sync();
     if (NEAR) {
@@ -222,7 +224,7 @@ __global__ __launch_bounds__(64) void k_canon_search(CanonArgs a) {
         wave_sync();
         if (nnew == 0) continue;
         if constexpr (NEAR) {
-            if (qn == L) {
+            if (qn == L && tol32 < __builtin_inf()) {
                 float *fd = reinterpret_cast<float *>(s.ql.sd);
                 shared_sums<float, 4>(a, qrow, ci, nnew, fd);
                 wave_sync();
