@@ -435,6 +435,12 @@ __device__ __forceinline__ void near_kept(const float *crow, KR kr, int nch, int
     }
 }
 
+// At least the norm of a row whose FP32 sum of squares is n2: squares below
+// FP32's smallest normal number may have counted as zero.
+__device__ __forceinline__ float norm_above(float n2, const SelectArgs &a) {
+    return sqrtf(n2 + (float)a.pitch * 1.2e-38f) * (1.0001f + a.gam);
+}
+
 template <bool KEPT_IN_LDS, bool FILL>
 __global__ __launch_bounds__(64) void k_canon_select(SelectArgs a) {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -479,11 +485,13 @@ __global__ __launch_bounds__(64) void k_canon_select(SelectArgs a) {
             if (alive) {
                 float n2;
                 near_kept(crow, [&](int t) { return kept_row(r0 + t); }, nch, nk, acc, n2);
-                cnorm = sqrtf(n2) * (1.0001f + a.gam);
+                cnorm = norm_above(n2, a);
 #pragma unroll
                 for (int t = 0; t < KG; ++t)
                     if (t < nk) {
-                        const double dcp = -(double)acc[t], tau = (double)fmaf(a.gam * cnorm, kn[r0 + t], 1e-30f);
+                        const float cp = cnorm * kn[r0 + t];
+                        // a sum that can overflow bounds nothing
+                        const double dcp = -(double)acc[t], tau = cp < 1e38f ? (double)fmaf(a.gam, cp, 1e-30f) : INFINITY;
                         if (dxc >= dcp + tau)
                             alive = false;
                         else if (!(dxc < dcp - tau))
@@ -522,7 +530,7 @@ __global__ __launch_bounds__(64) void k_canon_select(SelectArgs a) {
             for (int o = 32; o > 0; o >>= 1) n2 += __shfl_xor(n2, o);
             if (lane == 0) {
                 kid[nr] = cs;
-                kn[nr] = sqrtf(n2) * (1.0001f + a.gam);
+                kn[nr] = norm_above(n2, a);
                 sel_ids[nr] = cs;
                 sel_d[nr] = ds;
             }

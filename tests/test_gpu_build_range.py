@@ -56,3 +56,19 @@ def test_insertion_of_very_long_rows(dev, oracle_lib):
     off, idx, entry = ix.graph()
     o2, i2 = st.csr()
     assert np.array_equal(off, o2) and np.array_equal(idx, i2) and entry == st.entry
+
+
+# scale of the short rows: their squares are FP32 normal numbers, subnormal ones and zero
+@pytest.mark.parametrize("short", [1e-10, 1e-19, 1e-23, 1e-30])
+def test_build_of_short_rows_among_long_ones(dev, oracle_lib, short):
+    # Long rows in groups that differ by an FP32 rounding or two per coordinate: a short row is about as near to one of
+    # them as to another, so only the last bits of the sums decide which of them keep it out
+    print(f"build of rows of {short} among rows of 1e10", flush=True)
+    rng = np.random.default_rng(5)
+    d, groups, copies = 200, 24, 12
+    X = np.repeat(rng.standard_normal((groups, d)), copies, axis=0) * 1e10
+    X *= 1 + rng.integers(-3, 4, X.shape) * 2.0 ** -23
+    X = np.concatenate([X, rng.standard_normal((300, d)) * short]).astype(np.float32)
+    X = X[rng.permutation(len(X))]
+    T = rng.standard_normal((400, d)).astype(np.float32)
+    check(dev, oracle_lib, X, T, 100, 32, 500)
