@@ -397,9 +397,10 @@ struct SelectArgs {
     int32_t L, m, head_len;
     int64_t x0;
     const uint32_t *nodes;   // the nodes, or null: x0, x0 + 1, ...
-    uint32_t *sel_ids;       // n x m
+    uint32_t *sel_ids;       // rows of m, of nodes sel0, sel0 + 1, ...
     double *sel_d;
     int32_t *sel_n;
+    int64_t sel0;
     uint32_t *head;          // count x head_len: the first candidates
     int32_t *head_n;         // candidates per node (without the node), or null
     float gam;
@@ -451,8 +452,9 @@ __global__ __launch_bounds__(64) void k_canon_select(SelectArgs a) {
     const int lane = lane_id(), nch = a.pitch >> 2;
     const int64_t b = blockIdx.x;
     const uint32_t x = a.nodes ? a.nodes[b] : (uint32_t)(a.x0 + b);
-    uint32_t *sel_ids = a.sel_ids + (int64_t)x * a.m;
-    double *sel_d = a.sel_d + (int64_t)x * a.m;
+    const int64_t at = (int64_t)x - a.sel0;
+    uint32_t *sel_ids = a.sel_ids + at * a.m;
+    double *sel_d = a.sel_d + at * a.m;
     const uint32_t *cid = a.ids + b * a.L;
     const double *cdd = a.dists + b * a.L;
     const int qn = a.counts[b];
@@ -558,7 +560,7 @@ __global__ __launch_bounds__(64) void k_canon_select(SelectArgs a) {
         }
     }
     if (lane == 0) {
-        a.sel_n[x] = nr;
+        a.sel_n[at] = nr;
         if (a.head_n) a.head_n[b] = hn;
     }
 }
@@ -948,10 +950,18 @@ struct Dev {
     Dev() = default;
     Dev(const Dev &) = delete;
     Dev &operator=(const Dev &) = delete;
-    ~Dev() {
+    ~Dev() { release(); }
+    void release() {
         if (p) (void)hipFree(p);
+        p = nullptr;
     }
-    bool alloc(size_t bytes) { return hipMalloc(&p, bytes ? bytes : 1) == hipSuccess || (p = nullptr, false); }
+    bool alloc(size_t bytes) {
+        release();
+        if (hipMalloc(&p, bytes ? bytes : 1) == hipSuccess) return true;
+        p = nullptr;
+        (void)hipGetLastError();  // callers may go on without it
+        return false;
+    }
     template <class T>
     T *as() const {
         return static_cast<T *>(p);
@@ -1127,10 +1137,8 @@ int canon_project(const GpuCtx &gpu, int64_t n, int32_t d, int64_t nt, int32_t N
         !d_cd.alloc(sizeof(double) * B * L) || !d_cn.alloc(sizeof(int32_t) * B) ||
         !d_sid.alloc(sizeof(uint32_t) * n * m) || !d_sd.alloc(sizeof(double) * n * m) ||
         !d_sn.alloc(sizeof(int32_t) * n) || !d_out.alloc(sizeof(uint32_t) * n * ell) ||
-        !d_on.alloc(sizeof(int32_t) * n)) {
-        (void)hipGetLastError();
+        !d_on.alloc(sizeof(int32_t) * n))
         return RG_ENOMEM;
-    }
     RG_HIP(hipMemcpyAsync(d_piv.p, piv.data(), sizeof(uint32_t) * np, hipMemcpyHostToDevice, st));
     RG_HIP(hipMemcpyAsync(d_boff.p, boff.data(), sizeof(int64_t) * (n + 1), hipMemcpyHostToDevice, st));
     RG_HIP(hipMemcpyAsync(d_bidx.p, bidx.data(), sizeof(uint32_t) * nt, hipMemcpyHostToDevice, st));
@@ -1170,10 +1178,7 @@ int canon_project(const GpuCtx &gpu, int64_t n, int32_t d, int64_t nt, int32_t N
         RG_HIP(hipGetLastError());
     }
     int rc = selected_by(s, n, d_off, d_src, st, [] {});
-    if (rc) {
-        if (rc == RG_ENOMEM) (void)hipGetLastError();
-        return rc;
-    }
+    if (rc) return rc;
     ReplayArgs r{};
     r.X = gpu.X;
     r.d = d;
@@ -1204,9 +1209,11 @@ int canon_project(const GpuCtx &gpu, int64_t n, int32_t d, int64_t nt, int32_t N
 
 // The searches and selections run in batches (their queues are the large
 // buffers); selections, reverse updates and the lists stay on the device.
+// Where those of all nodes do not fit, the selections of each batch go to the
+// host.
 int canon_enhance(const GpuCtx &gpu, int64_t n, int32_t d, const std::vector<uint32_t> &adj, int32_t ell,
                   uint32_t entry, int32_t L, int32_t m, int32_t head_len, std::vector<uint32_t> *ce,
-                  std::vector<int32_t> *ce_n, uint32_t *head, int32_t *head_n, double *t_search) {
+                  std::vector<int32_t> *ce_n, Selections *sel, uint32_t *head, int32_t *head_n, double *t_search) {
     if (m < 1 || m >= kMaxEll || L < 1) {
         set_error("build: bad list bound");
         return RG_EINVAL;
@@ -1217,14 +1224,43 @@ int canon_enhance(const GpuCtx &gpu, int64_t n, int32_t d, const std::vector<uin
     hipStream_t st = gpu.stream;
     const int64_t B = std::min<int64_t>(n, 1 << 15);
     Dev d_adj, d_q, d_qd, d_qn, d_sid, d_sd, d_sn, d_hd, d_hn, d_max;
+    // the selections and first candidates of this many nodes
+    auto room_for = [&](int64_t rows) {
+        if (d_sid.alloc(sizeof(uint32_t) * rows * m) && d_sd.alloc(sizeof(double) * rows * m) &&
+            d_sn.alloc(sizeof(int32_t) * rows) && d_hd.alloc(sizeof(uint32_t) * rows * head_len) &&
+            d_hn.alloc(sizeof(int32_t) * rows))
+            return true;
+        for (Dev *b : {&d_sid, &d_sd, &d_sn, &d_hd, &d_hn}) b->release();
+        return false;
+    };
     if (!d_max.alloc(8) || !d_adj.alloc(sizeof(uint32_t) * adj.size()) || !d_q.alloc(sizeof(uint32_t) * B * L) ||
-        !d_qd.alloc(sizeof(double) * B * L) || !d_qn.alloc(sizeof(int32_t) * B) ||
-        !d_sid.alloc(sizeof(uint32_t) * n * m) || !d_sd.alloc(sizeof(double) * n * m) ||
-        !d_sn.alloc(sizeof(int32_t) * n) || !d_hd.alloc(sizeof(uint32_t) * n * head_len) ||
-        !d_hn.alloc(sizeof(int32_t) * n)) {
+        !d_qd.alloc(sizeof(double) * B * L) || !d_qn.alloc(sizeof(int32_t) * B)) {
         set_error("build: out of memory for enhancement searches");
         return RG_ENOMEM;
     }
+    const bool whole = room_for(n);
+    if (!whole && !room_for(B)) {
+        set_error("build: out of memory for enhancement searches");
+        return RG_ENOMEM;
+    }
+    // nodes x0 .. x0 + cnt of what room_for holds, to the host
+    auto selections_to_host = [&](int64_t x0, int64_t cnt) -> int {
+        if (sel->counts.empty()) {
+            sel->ids.resize((size_t)n * m);
+            sel->dists.resize((size_t)n * m);
+            sel->counts.resize((size_t)n);
+        }
+        RG_HIP(hipMemcpyAsync(sel->ids.data() + x0 * m, d_sid.p, sizeof(uint32_t) * cnt * m, hipMemcpyDeviceToHost, st));
+        RG_HIP(hipMemcpyAsync(sel->dists.data() + x0 * m, d_sd.p, sizeof(double) * cnt * m, hipMemcpyDeviceToHost, st));
+        RG_HIP(hipMemcpyAsync(sel->counts.data() + x0, d_sn.p, sizeof(int32_t) * cnt, hipMemcpyDeviceToHost, st));
+        RG_HIP(hipStreamSynchronize(st));
+        return RG_OK;
+    };
+    auto head_to_host = [&](int64_t x0, int64_t cnt) -> int {
+        RG_HIP(hipMemcpyAsync(head + x0 * head_len, d_hd.p, sizeof(uint32_t) * cnt * head_len, hipMemcpyDeviceToHost, st));
+        RG_HIP(hipMemcpyAsync(head_n + x0, d_hn.p, sizeof(int32_t) * cnt, hipMemcpyDeviceToHost, st));
+        return RG_OK;
+    };
     RG_HIP(hipMemcpyAsync(d_adj.p, adj.data(), sizeof(uint32_t) * adj.size(), hipMemcpyHostToDevice, st));
     int rc = launch_max_norm(gpu.X, n, gpu.pitch, d_max.as<double>(), st);
     if (rc) return rc;
@@ -1253,24 +1289,36 @@ int canon_enhance(const GpuCtx &gpu, int64_t n, int32_t d, const std::vector<uin
                                  d_max.as<double>(), d_q.as<uint32_t>(), d_qd.as<double>(), d_qn.as<int32_t>(), st);
         if (rc) return rc;
         s.x0 = x0;
-        s.head = d_hd.as<uint32_t>() + x0 * head_len;
-        s.head_n = d_hn.as<int32_t>() + x0;
+        s.sel0 = whole ? 0 : x0;
+        s.head = d_hd.as<uint32_t>() + (x0 - s.sel0) * head_len;
+        s.head_n = d_hn.as<int32_t>() + (x0 - s.sel0);
         hipLaunchKernelGGL(k_select, dim3((unsigned)cnt), dim3(64), lds, st, s);
         RG_HIP(hipGetLastError());
+        if (!whole) {
+            rc = head_to_host(x0, cnt);
+            if (!rc) rc = selections_to_host(x0, cnt);
+            if (rc) return rc;
+        }
         if (log && ((x0 + cnt) % step == 0 || x0 + cnt == n)) {  // progress (waits for the batches)
             RG_HIP(hipStreamSynchronize(st));
             std::fprintf(stderr, "[rg] enhancement searches %lld / %lld nodes\n", (long long)(x0 + cnt), (long long)n);
         }
     }
-    RG_HIP(hipMemcpyAsync(head, d_hd.p, sizeof(uint32_t) * n * head_len, hipMemcpyDeviceToHost, st));
-    RG_HIP(hipMemcpyAsync(head_n, d_hn.p, sizeof(int32_t) * n, hipMemcpyDeviceToHost, st));
+    if (!whole) {
+        *t_search = std::chrono::duration<double>(Clock::now() - t0).count();
+        return RG_OK;
+    }
+    rc = head_to_host(0, n);
+    if (rc) return rc;
     Dev d_off, d_src, d_out, d_on;
     rc = selected_by(s, n, d_off, d_src, st, [&] { *t_search = std::chrono::duration<double>(Clock::now() - t0).count(); });
-    if (rc) return rc;
-    if (!d_out.alloc(sizeof(uint32_t) * n * m) || !d_on.alloc(sizeof(int32_t) * n)) {
-        set_error("build: out of memory for reverse updates");
-        return RG_ENOMEM;
+    if (!rc && (!d_out.alloc(sizeof(uint32_t) * n * m) || !d_on.alloc(sizeof(int32_t) * n))) rc = RG_ENOMEM;
+    if (rc == RG_ENOMEM) {
+        rc = selections_to_host(0, n);
+        *t_search = std::chrono::duration<double>(Clock::now() - t0).count();
+        return rc;
     }
+    if (rc) return rc;
     ReplayArgs r{};
     r.X = gpu.X;
     r.d = d;

@@ -538,9 +538,18 @@ int host_construct(const float *X, int64_t n, int32_t d, const uint32_t *knn, in
     std::vector<uint32_t> dev_ce;
     std::vector<int32_t> dev_ce_n;
     if (gpu) {
-        const int rc = gpu->enhance(*gpu, n, d, pj, pj_ell, entry, L, std::max(1, m_ce), kHead, &dev_ce, &dev_ce_n,
-                                    head.data(), head_n.data(), &out->t_enhance_search);
+        const int32_t m = std::max(1, m_ce);
+        Selections sel;
+        const int rc = gpu->enhance(*gpu, n, d, pj, pj_ell, entry, L, m, kHead, &dev_ce, &dev_ce_n, &sel, head.data(),
+                                    head_n.data(), &out->t_enhance_search);
         if (rc) return rc;
+        if (dev_ce_n.empty()) {
+            E.init(n, capl);
+            parallel_for(n, threads, 4096, [&](int64_t x, int) {
+                E.deg[x] = sel.counts[x];
+                for (int j = 0; j < E.deg[x]; ++j) E.row(x)[j] = Cand{sel.dists[x * m + j], sel.ids[x * m + j]};
+            });
+        }
     } else {
         std::vector<Searcher> sr((size_t)threads);
         std::vector<std::vector<Cand>> cc((size_t)threads);
@@ -560,7 +569,8 @@ int host_construct(const float *X, int64_t n, int32_t d, const uint32_t *knn, in
     }
     const auto t1b = Clock::now();
     Lists CE;
-    if (!gpu) {
+    const bool on_host = dev_ce_n.empty();
+    if (on_host) {
         CE.init(n, capl);
         std::vector<int64_t> eoff;
         std::vector<uint32_t> esrc;
@@ -584,9 +594,9 @@ int host_construct(const float *X, int64_t n, int32_t d, const uint32_t *knn, in
         auto &r = fin[x];
         r.reserve((size_t)M);
         for (int j = 0; j < pj_n[x]; ++j) r.push_back(pj[x * pj_ell + j]);
-        const int nce = gpu ? dev_ce_n[x] : CE.deg[x];
+        const int nce = on_host ? CE.deg[x] : dev_ce_n[x];
         for (int j = 0; j < nce; ++j) {
-            const uint32_t u = gpu ? dev_ce[x * (int64_t)std::max(1, m_ce) + j] : CE.row(x)[j].id;
+            const uint32_t u = on_host ? CE.row(x)[j].id : dev_ce[x * (int64_t)std::max(1, m_ce) + j];
             if (std::find(r.begin(), r.end(), u) == r.end()) r.push_back(u);
         }
         std::sort(r.begin(), r.end());  // the repair's BFS visits neighbours in ascending id

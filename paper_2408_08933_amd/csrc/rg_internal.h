@@ -265,6 +265,12 @@ struct HostGraph {
     double t_knn = 0, t_project = 0, t_enhance = 0, t_total = 0;
     double t_enhance_search = 0;
 };
+// A list of at most m neighbours per node, in (delta, id) order.
+struct Selections {
+    std::vector<uint32_t> ids;  // n x m
+    std::vector<double> dists;
+    std::vector<int32_t> counts;
+};
 // Device resources construction may use: the padded FP32 base and the kNN
 // lists on the device, and the work done there (canon.hip; pointers, so that
 // the host half links without the device half).
@@ -284,10 +290,12 @@ struct GpuCtx {
                    std::vector<int32_t> *pj_n);
     // the enhancement, from the projected graph to the lists after the reverse
     // updates (n x m ids in ce, ce_n per node), the first head_len search
-    // results of each node (itself left out) and their number
+    // results of each node (itself left out) and their number.  Where the
+    // reverse updates find no room, ce and ce_n stay empty and sel holds what
+    // they start from, each node's own selection.
     int (*enhance)(const GpuCtx &gpu, int64_t n, int32_t d, const std::vector<uint32_t> &adj, int32_t ell,
                    uint32_t entry, int32_t L, int32_t m, int32_t head_len, std::vector<uint32_t> *ce,
-                   std::vector<int32_t> *ce_n, uint32_t *head, int32_t *head_n, double *t_search);
+                   std::vector<int32_t> *ce_n, Selections *sel, uint32_t *head, int32_t *head_n, double *t_search);
     std::function<void()> drop_lists;  // called after the projection
 };
 // knn lists: nt x Nq canonical ids (null: on the device only, without kept
@@ -324,7 +332,7 @@ int canon_project(const GpuCtx &gpu, int64_t n, int32_t d, int64_t nt, int32_t N
                   std::vector<int32_t> *pj_n);
 int canon_enhance(const GpuCtx &gpu, int64_t n, int32_t d, const std::vector<uint32_t> &adj, int32_t ell,
                   uint32_t entry, int32_t L, int32_t m, int32_t head_len, std::vector<uint32_t> *ce,
-                  std::vector<int32_t> *ce_n, uint32_t *head, int32_t *head_n, double *t_search);
+                  std::vector<int32_t> *ce_n, Selections *sel, uint32_t *head, int32_t *head_n, double *t_search);
 
 // canonical FP64 distance helpers (host)
 double canon_dist(const float *a, const float *b, int32_t d);

@@ -1,7 +1,8 @@
-// A device that has no room for large buffers, for tests: loaded with
+// A device that has no room for some buffers, for tests: loaded with
 // RTLD_GLOBAL ahead of the HIP runtime, hipMalloc passes every request on to
-// it, but one of more than the limit as one that no device can grant, so that
-// the runtime itself reports (and remembers) the failure.
+// it, but one of more than the limit (or of the one size refused) as one that
+// no device can grant, so that the runtime itself reports (and remembers) the
+// failure.
 #include <dlfcn.h>
 
 #include <cstddef>
@@ -9,13 +10,14 @@
 #include <initializer_list>
 
 namespace {
-size_t limit = 0;  // bytes; 0: none
+size_t limit = 0, refused = 0;  // bytes; 0: none
 int64_t failed = 0;
 }  // namespace
 
 extern "C" {
 
 void alloc_limit(uint64_t bytes) { limit = bytes; }
+void alloc_refuse(uint64_t bytes) { refused = bytes; }
 int64_t alloc_failed() { return failed; }
 
 int hipMalloc(void **p, size_t bytes) {
@@ -27,7 +29,7 @@ int hipMalloc(void **p, size_t bytes) {
         return h ? reinterpret_cast<Fn>(dlsym(h, "hipMalloc")) : nullptr;
     }();
     if (!real) return 3;  // not initialized
-    if (!limit || bytes <= limit) return real(p, bytes);
+    if ((!limit || bytes <= limit) && (!refused || bytes != refused)) return real(p, bytes);
     ++failed;
     const int rc = real(p, (size_t)1 << 60);
     if (rc == 0) *p = nullptr;

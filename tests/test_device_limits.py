@@ -138,3 +138,17 @@ def test_build_knn_in_parts(fake):
         assert sum(g for _, g, _ in launches("k_knn_certify")) == nt
         assert fake.fake_in_use() == 0
     """)
+
+
+# MB: the selections of all nodes do not fit, or the lists after the reverse updates do not
+@pytest.mark.parametrize("limit", [180, 345])
+def test_build_without_room_for_all_selections(fake, limit):
+    # 400,000 rows of 16: the base takes 26 MB, the projected graph 51 MB and a batch of searches and selections 56 MB;
+    # the selections of all nodes take 150 MB and their first candidates 51 MB, their reverse updates 54 MB
+    run(fake, f"""
+        n, d = 400_000, 16
+        fake.fake_limit({limit} * 1000 * 1000)
+        ok(build(np.zeros((n, d), np.float32), np.zeros((1000, d), np.float32), 16, 64, 100))
+        assert not launches("k_replayE") and sum(g for _, g, _ in launches("k_sort_events")) == ({limit} > 300) * 2 * n
+        assert fake.fake_in_use() == 0
+    """)

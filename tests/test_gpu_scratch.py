@@ -16,18 +16,21 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 PRELUDE = """
 import ctypes as C, sys
 limiter = C.CDLL(sys.argv[1], C.RTLD_GLOBAL)
-limiter.alloc_limit.argtypes, limiter.alloc_failed.restype = [C.c_uint64], C.c_int64
+limiter.alloc_limit.argtypes = limiter.alloc_refuse.argtypes = [C.c_uint64]
+limiter.alloc_failed.restype = C.c_int64
 import numpy as np, torch
 import paper_2408_08933_amd as rg
 g = torch.Generator().manual_seed(4)
-def with_room_and_without(call, limit):
+def with_room_and_without(call, limit=0, refuse=0):
     a = call()
     torch.cuda.synchronize()
     print("with room", flush=True)
     limiter.alloc_limit(limit)
+    limiter.alloc_refuse(refuse)
     b = call()
     torch.cuda.synchronize()
     limiter.alloc_limit(0)
+    limiter.alloc_refuse(0)
     assert limiter.alloc_failed() > 0
     print("without", flush=True)
     return a, b
@@ -76,4 +79,15 @@ def test_knn_out_of_fp16_range_without_room_for_fp16_rows(limiter):
         X, Q = 1e5 * torch.randn(1_250_000, 128, generator=g).cuda(), torch.randn(200, 128, generator=g).cuda()
         a, b = with_room_and_without(lambda: rg.rg_knn(Q, X, 20), 300 << 20)
         assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1])
+    """)
+
+
+# 150,000 rows, lists of 31: no room for the selected distances of all nodes, or for the offsets of the reverse updates
+# (8 bytes a row), where the projection goes to the host too
+@pytest.mark.parametrize("refuse", [8 * 31 * 150_000, 8 * 150_001])
+def test_build_without_room_for_all_selections(limiter, refuse):
+    run(limiter, f"""
+        X, T = torch.randn(150_000, 16, generator=g).cuda(), torch.randn(20_000, 16, generator=g).cuda()
+        a, b = with_room_and_without(lambda: rg.rg_build(X, T, 16, 64, L_build=48).graph(), refuse={refuse})
+        assert a[2] == b[2] and np.array_equal(a[0], b[0]) and np.array_equal(a[1], b[1])
     """)
