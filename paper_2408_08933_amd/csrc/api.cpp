@@ -586,6 +586,18 @@ int rg_build(const float *base, int64_t n, int32_t d, const float *train, int64_
     ix->m_ce = m_ce;
     (void)hipGetDevice(&ix->device);
     rc = upload_base(ix, base, st);
+    if (rc == RG_ENOMEM && lists.p) {
+        // no room for the rows beside the lists: these go to the host, and the
+        // projection with them
+        (void)hipGetLastError();
+        knn.resize((size_t)nt * Nq);
+        rc = hipMemcpyAsync(knn.data(), lists.p, sizeof(uint32_t) * knn.size(), hipMemcpyDeviceToHost, st) == hipSuccess &&
+                     hipStreamSynchronize(st) == hipSuccess
+                 ? RG_OK
+                 : RG_EDEVICE;
+        lists.release();
+        if (!rc) rc = upload_base(ix, base, st);
+    }
     HostGraph g;
     if (!rc) {
         GpuCtx gpu{ix->d_base,  ix->pitch,     st,            lists.as<uint32_t>(),     canon_pivots,

@@ -1119,6 +1119,7 @@ int canon_project(const GpuCtx &gpu, int64_t n, int32_t d, int64_t nt, int32_t N
                   const std::vector<uint32_t> &bidx, int32_t L, int32_t m, int32_t ell, std::vector<uint32_t> *pj,
                   std::vector<int32_t> *pj_n) {
     hipStream_t st = gpu.stream;
+    if (!gpu.lists) return RG_ENOMEM;
     if (L > kMaxL || m < 1 || m >= kMaxEll || Nq > 512 || ell < m) return RG_ENOMEM;  // no room in the kernels
     std::vector<uint32_t> piv;
     for (int64_t x = 0; x < n; ++x)

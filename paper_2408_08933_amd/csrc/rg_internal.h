@@ -278,7 +278,7 @@ struct GpuCtx {
     const float *X;      // n x pitch
     int32_t pitch;
     hipStream_t stream;
-    const uint32_t *lists;  // nt x Nq; not used after the projection
+    const uint32_t *lists;  // nt x Nq, or null (host_construct has them then); not used after the projection
     // the first entry of each list
     int (*pivots)(const GpuCtx &gpu, int64_t nt, int32_t Nq, uint32_t *out);
     // the lists themselves

@@ -11,13 +11,17 @@
 
 namespace {
 size_t limit = 0, refused = 0;  // bytes; 0: none
+int64_t times = -1;              // how often the one size is refused; below 0: always
 int64_t failed = 0;
 }  // namespace
 
 extern "C" {
 
 void alloc_limit(uint64_t bytes) { limit = bytes; }
-void alloc_refuse(uint64_t bytes) { refused = bytes; }
+void alloc_refuse(uint64_t bytes, int64_t often) {
+    refused = bytes;
+    times = often;
+}
 int64_t alloc_failed() { return failed; }
 
 int hipMalloc(void **p, size_t bytes) {
@@ -29,7 +33,9 @@ int hipMalloc(void **p, size_t bytes) {
         return h ? reinterpret_cast<Fn>(dlsym(h, "hipMalloc")) : nullptr;
     }();
     if (!real) return 3;  // not initialized
-    if ((!limit || bytes <= limit) && (!refused || bytes != refused)) return real(p, bytes);
+    const bool one = refused && bytes == refused && times != 0;
+    if ((!limit || bytes <= limit) && !one) return real(p, bytes);
+    if (one) --times;
     ++failed;
     const int rc = real(p, (size_t)1 << 60);
     if (rc == 0) *p = nullptr;

@@ -152,3 +152,14 @@ def test_build_without_room_for_all_selections(fake, limit):
         assert not launches("k_replayE") and sum(g for _, g, _ in launches("k_sort_events")) == ({limit} > 300) * 2 * n
         assert fake.fake_in_use() == 0
     """)
+
+
+def test_build_without_room_for_rows_beside_the_lists(fake):
+    # 3M rows of 128 (1.57 GB, 0.8 GB as FP16) and 4M lists of 32 (0.54 GB): rows and graph fit, rows and lists do not
+    run(fake, """
+        n, nt, d = 3 << 20, 4 << 20, 128
+        X, T = np.zeros((n, d), np.float32), np.zeros((nt, d), np.float32)
+        fake.fake_limit(2050 * 1000 * 1000)
+        ok(build(X, T, 32, 8, 16))
+        assert fake.fake_in_use() == 0
+    """)

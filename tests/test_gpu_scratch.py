@@ -16,21 +16,21 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 PRELUDE = """
 import ctypes as C, sys
 limiter = C.CDLL(sys.argv[1], C.RTLD_GLOBAL)
-limiter.alloc_limit.argtypes = limiter.alloc_refuse.argtypes = [C.c_uint64]
+limiter.alloc_limit.argtypes, limiter.alloc_refuse.argtypes = [C.c_uint64], [C.c_uint64, C.c_int64]
 limiter.alloc_failed.restype = C.c_int64
 import numpy as np, torch
 import paper_2408_08933_amd as rg
 g = torch.Generator().manual_seed(4)
-def with_room_and_without(call, limit=0, refuse=0):
+def with_room_and_without(call, limit=0, refuse=0, times=-1):
     a = call()
     torch.cuda.synchronize()
     print("with room", flush=True)
     limiter.alloc_limit(limit)
-    limiter.alloc_refuse(refuse)
+    limiter.alloc_refuse(refuse, times)
     b = call()
     torch.cuda.synchronize()
     limiter.alloc_limit(0)
-    limiter.alloc_refuse(0)
+    limiter.alloc_refuse(0, 0)
     assert limiter.alloc_failed() > 0
     print("without", flush=True)
     return a, b
@@ -89,5 +89,15 @@ def test_build_without_room_for_all_selections(limiter, refuse):
     run(limiter, f"""
         X, T = torch.randn(150_000, 16, generator=g).cuda(), torch.randn(20_000, 16, generator=g).cuda()
         a, b = with_room_and_without(lambda: rg.rg_build(X, T, 16, 64, L_build=48).graph(), refuse={refuse})
+        assert a[2] == b[2] and np.array_equal(a[0], b[0]) and np.array_equal(a[1], b[1])
+    """)
+
+
+def test_build_without_room_for_rows_beside_the_lists(limiter):
+    # the padded rows are refused while the lists are on the device: 48 coordinates are not padded, so that no other
+    # buffer has their size
+    run(limiter, """
+        X, T = torch.randn(20_000, 48, generator=g).cuda(), torch.randn(20_000, 48, generator=g).cuda()
+        a, b = with_room_and_without(lambda: rg.rg_build(X, T, 16, 24, L_build=64).graph(), refuse=4 * 48 * 20_000, times=1)
         assert a[2] == b[2] and np.array_equal(a[0], b[0]) and np.array_equal(a[1], b[1])
     """)
