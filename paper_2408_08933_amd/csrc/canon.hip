@@ -172,13 +172,15 @@ __global__ __launch_bounds__(64) void k_canon_search(CanonArgs a) {
     }
     vis.clear();
     double tol = 0.0, tol32 = 0.0;
+    int when = -1;  // the queue length at which FP32 sums turn candidates away
     if constexpr (NEAR) {
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) n2 += __shfl_xor(n2, o);
         const double nn = sqrt(n2 * *a.xmax2) * (1.0 + 1e-9);
         tol = 2.0 * a.gam * nn;
         // and what underflow may lose; an FP32 sum that can overflow bounds nothing
-        tol32 = nn < 1e38 ? (a.gam + a.gam32) * nn + 1e-30 : __builtin_inf();
+        tol32 = (a.gam + a.gam32) * nn + 1e-30;
+        when = __builtin_amdgcn_readfirstlane(nn < 1e38 ? L : -1);
     }
     wave_sync();
     if (NEAR) {
@@ -224,7 +226,7 @@ __global__ __launch_bounds__(64) void k_canon_search(CanonArgs a) {
         wave_sync();
         if (nnew == 0) continue;
         if constexpr (NEAR) {
-            if (qn == L && tol32 < __builtin_inf()) {
+            if (qn == when) {
                 float *fd = reinterpret_cast<float *>(s.ql.sd);
                 shared_sums<float, 4>(a, qrow, ci, nnew, fd);
                 wave_sync();
@@ -404,6 +406,7 @@ struct SelectArgs {
     uint32_t *head;          // count x head_len: the first candidates
     int32_t *head_n;         // candidates per node (without the node), or null
     float gam;
+    float floor2;            // what squares that underflow can add up to
 };
 
 constexpr int KG = 16;
@@ -436,10 +439,12 @@ __device__ __forceinline__ void near_kept(const float *crow, KR kr, int nch, int
     }
 }
 
-// At least the norm of a row whose FP32 sum of squares is n2: squares below
-// FP32's smallest normal number may have counted as zero.
+// At least the norm of a row whose FP32 sum of squares is n2.  Squares below
+// FP32's smallest normal number may have counted as zero: floor2 is what they
+// can add up to.  The 1.01 makes it infinite, and with it the bound, before
+// the product of two norms, and so a sum of two rows, can overflow.
 __device__ __forceinline__ float norm_above(float n2, const SelectArgs &a) {
-    return sqrtf(n2 + (float)a.pitch * 1.2e-38f) * (1.0001f + a.gam);
+    return sqrtf(fmaf(n2, 1.01f, a.floor2)) * (1.0001f + a.gam);
 }
 
 template <bool KEPT_IN_LDS, bool FILL>
@@ -491,9 +496,7 @@ __global__ __launch_bounds__(64) void k_canon_select(SelectArgs a) {
 #pragma unroll
                 for (int t = 0; t < KG; ++t)
                     if (t < nk) {
-                        const float cp = cnorm * kn[r0 + t];
-                        // a sum that can overflow bounds nothing
-                        const double dcp = -(double)acc[t], tau = cp < 1e38f ? (double)fmaf(a.gam, cp, 1e-30f) : INFINITY;
+                        const double dcp = -(double)acc[t], tau = (double)fmaf(a.gam * cnorm, kn[r0 + t], 1e-30f);
                         if (dxc >= dcp + tau)
                             alive = false;
                         else if (!(dxc < dcp - tau))
@@ -1168,6 +1171,7 @@ int canon_project(const GpuCtx &gpu, int64_t n, int32_t d, int64_t nt, int32_t N
     s.sel_d = d_sd.as<double>();
     s.sel_n = d_sn.as<int32_t>();
     s.gam = sum_bound(d, gpu.pitch + 8);
+    s.floor2 = (float)gpu.pitch * 1.2e-38f;
     bool rows;
     const size_t lds = select_lds(gpu, m, &rows);
     auto k_select = rows ? k_canon_select<true, true> : k_canon_select<false, true>;
@@ -1280,6 +1284,7 @@ int canon_enhance(const GpuCtx &gpu, int64_t n, int32_t d, const std::vector<uin
     s.sel_n = d_sn.as<int32_t>();
     // a lane's chain over the whole row, and the norms' own rounding
     s.gam = sum_bound(d, gpu.pitch + 8);
+    s.floor2 = (float)gpu.pitch * 1.2e-38f;
     bool kept_in_lds;
     const size_t lds = select_lds(gpu, m, &kept_in_lds);
     auto k_select = kept_in_lds ? k_canon_select<true, false> : k_canon_select<false, false>;
