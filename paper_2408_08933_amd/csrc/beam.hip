@@ -226,11 +226,13 @@ __device__ __forceinline__ void dot_rows(const SearchArgs &a, const uint32_t (&u
 }
 
 // delta of this group's row from its group-summed dot product (and, for
-// E4M3, the row's power-of-two scale: the product is exact)
+// E4M3, the row's power-of-two scale: the product is exact).  A NaN would have
+// no place in the queue's order (every merge would put it elsewhere): it counts
+// as +inf, behind all that are nearer, and restore_nans returns it.
 template <int ST>
 __device__ __forceinline__ float finish_delta(float sum, float scale) {
-    if constexpr (ST == RG_STORE_FP8E4M3) return -(scale * sum);
-    return -sum;
+    // one instruction with the sign: v_min_f32 returns the operand that is a number
+    return __builtin_fminf(ST == RG_STORE_FP8E4M3 ? -(scale * sum) : -sum, __builtin_inff());
 }
 
 // Score ids[0..cnt) (LDS) into dout[0..cnt) (LDS); R rows per group in flight.
@@ -252,12 +254,13 @@ __device__ __forceinline__ void score_batch(const SearchArgs &a, const float *qs
         for (int r = 0; r < R; ++r) {
             acc[r] = group_sum<G>(acc[r]);
             if constexpr (ST == RG_STORE_FP8E4M3) sc[r] = group_sum<G>(sc[r]);
+            acc[r] = finish_delta<ST>(acc[r], sc[r]);
         }
         if (j == 0) {
 #pragma unroll
             for (int r = 0; r < R; ++r) {
                 const int sl = p + r * NG + g;
-                if (sl < cnt) dout[sl] = finish_delta<ST>(acc[r], sc[r]);
+                if (sl < cnt) dout[sl] = acc[r];
             }
         }
     }
@@ -428,11 +431,26 @@ __device__ __forceinline__ void rerank_queue(const SearchArgs &a, const Lds &s, 
     wave_sync();
 }
 
+// Where a key of +inf stands for a NaN: the NaN again.
+__device__ __forceinline__ void restore_nans(const SearchArgs &a, const Lds &s, int qn) {
+    // the last entry has the largest key
+    if (!(s.qd[qn - 1] == __builtin_inff())) return;
+    for (int i = lane_id(); i < qn; i += 64) {
+        if (!(s.qd[i] == __builtin_inff())) continue;
+        const float *row = a.base + (size_t)(s.qi[i] & ~kExpanded) * a.pitch;
+        float sum = 0.f;
+        for (int j = 0; j < a.d; ++j) sum = fmaf(s.qs[j], row[j], sum);
+        if (sum != sum) s.qd[i] = sum;
+    }
+    wave_sync();
+}
+
 // The k results: the first k entries of the final queue that are not
 // deleted (a tombstoned node still routes the search but is never
 // returned), padded with kNone / +inf.
 __device__ __forceinline__ void emit_topk(const SearchArgs &a, const Lds &s, int qn, uint32_t *ids, float *ds) {
     const int lane = lane_id();
+    restore_nans(a, s, qn);
     if (!a.tomb) {
         for (int i = lane; i < a.k; i += 64) {
             ids[i] = i < qn ? (s.qi[i] & ~kExpanded) : kNone;
@@ -1012,6 +1030,7 @@ __global__ __launch_bounds__(64 * kWide) __attribute__((amdgpu_waves_per_eu(2)))
     }
     if (w == 0) {
         Lds out{};
+        out.qs = qs;
         out.qd = qd;
         out.qi = qi;
         write_result(a, out, q, n, s.hops, s.evals);
