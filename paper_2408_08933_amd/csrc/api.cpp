@@ -170,6 +170,16 @@ int choose_table(SearchArgs &a, int cus) {
     const int width = a.adj_off ? kMaxEll : a.ell;  // ids inserted per batch
     const int64_t want = (a.nq + cus - 1) / std::max(1, cus);
     int best = 10, occ = -1;
+    // A table of ids is cleared at half load, so short queues lose more to a
+    // smaller one than a fifth wavefront gives back: 4 KB for up to 128 entries
+    // on graphs of 65 to 112 ids a row and CSR, 64 < d <= 256.  4 / 2 KB, ms for
+    // 10,000 queries: E4M3 100k x 200, 100 ids, L = 50 4.2 / 4.5, 200 ids (CSR)
+    // 7.2 / 7.8, BF16 100k x 96, 100 ids, L = 100 1.19 times as fast; but 128 ids
+    // 0.96 times, and d = 64, 100 ids, L = 100 6.4 / 5.9.
+    set_table(a, best);
+    if (!a.sets && (a.adj_off || a.ell <= 112) && a.d > 64 && a.d <= 256 && a.Leff <= 128 &&
+        !(a.storage == RG_STORE_FP32 && a.d > 128))
+        return RG_OK;
     for (int hb = a.storage == RG_STORE_FP32 && a.d > 128 ? 11 : 10; hb >= 8; --hb) {
         if ((1 << hb) < 2 * width + 2) break;
         int o = 0;

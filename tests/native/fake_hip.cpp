@@ -6,6 +6,7 @@
 // error of a failed call stays the thread's last error until it is asked for.
 #include <sys/mman.h>
 
+#include <algorithm>
 #include <cstdint>
 #include <cstdlib>
 #include <cstring>
@@ -23,6 +24,7 @@ struct Dim {
 struct Launch {
     std::string name;
     Dim grid, block;
+    size_t shared;
 };
 
 std::recursive_mutex mu;
@@ -87,6 +89,7 @@ const char *fake_launch(int64_t i, uint64_t *grid, uint64_t *block) {
     *block = (uint64_t)l.block.x * l.block.y * l.block.z;
     return l.name.c_str();
 }
+uint64_t fake_shared(int64_t i) { return launches[(size_t)i].shared; }
 
 // for the library
 void **__hipRegisterFatBinary(const void *) {
@@ -111,10 +114,10 @@ int __hipPopCallConfiguration(Dim *grid, Dim *block, size_t *shared, void **stre
     *stream = call.stream;
     return kOk;
 }
-int hipLaunchKernel(const void *f, Dim grid, Dim block, void **args, size_t, void *) {
+int hipLaunchKernel(const void *f, Dim grid, Dim block, void **args, size_t shared, void *) {
     std::lock_guard<std::recursive_mutex> lk(mu);
     if ((uint64_t)grid.x * block.x >= 1ull << 32 || grid.x == 0 || block.x == 0) return fail(kInvalidConfiguration);
-    launches.push_back({names[f], grid, block});
+    launches.push_back({names[f], grid, block, shared});
     if (pack_amax && names[f].find("k_pack16") != std::string::npos)
         // its last argument, a PackStats: the largest |element| is the third word
         (*static_cast<uint32_t **>(args[10]))[2] = pack_amax;
@@ -150,8 +153,9 @@ int hipDeviceGetAttribute(int *v, int, int) {
     return kOk;
 }
 int hipFuncSetAttribute(const void *, int, int) { return kOk; }
-int hipOccupancyMaxActiveBlocksPerMultiprocessor(int *v, const void *, int, size_t) {
-    *v = 2;
+int hipOccupancyMaxActiveBlocksPerMultiprocessor(int *v, const void *, int, size_t shared) {
+    // one wavefront each, five on a SIMD, 160 KB
+    *v = (int)std::min<size_t>(20, (160u << 10) / std::max<size_t>(shared, 1));
     return kOk;
 }
 int hipGetDevice(int *d) {

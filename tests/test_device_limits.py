@@ -22,7 +22,7 @@ fake, lib = C.CDLL(sys.argv[1], C.RTLD_GLOBAL), C.CDLL(sys.argv[2])
 lib.rg_last_error.restype = C.c_char_p
 fake.fake_launch.restype = C.c_char_p
 fake.fake_launches.restype = C.c_int64
-fake.fake_most.restype = fake.fake_in_use.restype = C.c_uint64
+fake.fake_most.restype = fake.fake_in_use.restype = fake.fake_shared.restype = C.c_uint64
 fake.fake_limit.argtypes, fake.fake_amax.argtypes = [C.c_uint64], [C.c_float]
 I64, P = C.c_int64, lambda a: C.c_void_p(a.ctypes.data)
 class Opts(C.Structure):
@@ -162,4 +162,24 @@ def test_build_without_room_for_rows_beside_the_lists(fake):
         fake.fake_limit(2050 * 1000 * 1000)
         ok(build(X, T, 32, 8, 16))
         assert fake.fake_in_use() == 0
+    """)
+
+
+# rows of ids, d, L, KB of the table: short queues on wide rows keep 4 KB where one of 2 KB lets more workgroups share a
+# CU; longer queues, other rows and narrow coordinates do not
+@pytest.mark.parametrize("deg,d,L,kb", [(100, 200, 50, 4), (100, 96, 128, 4), (200, 200, 60, 4), (112, 256, 128, 4),
+                                        (100, 200, 129, 2), (128, 200, 50, 2), (100, 64, 100, 2), (56, 200, 200, 2)])
+def test_visited_table_of_wide_rows(fake, deg, d, L, kb):
+    run(fake, f"""
+        n, deg, d, L = 5000, {deg}, {d}, {L}
+        X, idx = np.zeros((n, d), np.float32), np.zeros(n * deg, np.uint32)
+        off, ix = np.arange(n + 1, dtype=np.int64) * deg, C.c_void_p()
+        ok(lib.rg_index_from_csr(P(X), I64(n), d, P(off), P(idx), 0, 0, None, C.byref(ix)))
+        ok(lib.rg_index_set_storage(ix, 1, None))
+        fake.fake_reset()
+        ok(lib.rg_search(ix, P(X), I64(10_000), 10, L, P(idx), P(X), None, None, None))
+        assert len(launches("k_search")) == fake.fake_launches() == 1
+        cand, pad = 64 if deg <= 64 else 128, (d + 15) // 16 * 16
+        assert fake.fake_shared(I64(0)) - (4 * pad + 8 * L + 20 * cand) == {kb} << 10
+        lib.rg_free(ix)
     """)
