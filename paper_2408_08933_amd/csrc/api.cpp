@@ -1090,7 +1090,6 @@ int rg_search(const rg_index *ix, const float *queries, int64_t nq, int32_t k, i
     const bool bits = exact && !a.adj_off && ix->n <= 32 << 10;
     if (!a.adj_off && a.ell <= 64 && nq <= most && ((exact && nq <= 2 * (int64_t)cus) || (a.sets && !bits))) {
         a.grid = nq <= cus ? 8 : nq <= 2 * (int64_t)cus ? 4 : 2;
-        a.prep = 2;
         void *ws = nullptr;
         if (exact && nq <= 2 * (int64_t)cus) {
             // room for twice the expected nodes, as LDS allows

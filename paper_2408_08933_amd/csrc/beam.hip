@@ -801,7 +801,8 @@ __global__ __launch_bounds__(64 * kWide) __attribute__((amdgpu_waves_per_eu(2)))
     extern __shared__ __align__(16) unsigned char smem[];
     const int tid = threadIdx.x, nthr = blockDim.x, w = tid >> 6, lane = lane_id();
     // P wavefronts per preparation, W preparations at a time
-    const int P = a.prep, W = (nthr >> 6) / P, slot_w = w / P, part = w % P;
+    constexpr int P = kPrep;
+    const int W = (nthr >> 6) / P, slot_w = w / P, part = w % P;
     const int64_t q = blockIdx.x;
     const int Leff = a.Leff, nch = row_chunk_count<ST>(a.d);
     WideLds &s = *reinterpret_cast<WideLds *>(smem);
@@ -1279,7 +1280,7 @@ int launch_search_bits(const SearchArgs &a, hipStream_t stream) {
 int launch_search_wide(const SearchArgs &a, hipStream_t stream) {
     if (a.nq == 0) return RG_OK;
     if (a.adj_off || a.ell > 64 || a.Leff > kMaxSearchL || a.grid < 2 || a.grid > kMaxWide ||
-        a.prep < 1 || a.grid % a.prep != 0 ||
+        a.grid % kPrep != 0 ||
         (!a.sets && (a.storage != RG_STORE_FP32 || (!a.bitmap && a.n_rows + 64 * (kMaxWide + 1) > (3ll << a.hash_bits) / 4)))) {
         set_error("search: bad arguments for several wavefronts per query");
         return RG_EINTERNAL;

@@ -1374,8 +1374,8 @@ int64_t choose_splits(int64_t qtiles, int64_t units, int64_t resident) {
     return best;
 }
 
-int old_series(const void *Q16, int64_t nq, const void *X16, int64_t n, int32_t dp, int32_t K, uint32_t *ids,
-               float *scores, hipStream_t stream) {
+int running_topk(const void *Q16, int64_t nq, const void *X16, int64_t n, int32_t dp, int32_t K, uint32_t *ids,
+                 float *scores, hipStream_t stream) {
     const KnnKernel kk{k_knn16, BQ16, BX16, 256, sizeof(_Float16)};
     return knn_series(kk, Q16, nq, dp, X16, n, dp, dp, K, ids, scores, true, true, stream);
 }
@@ -1390,7 +1390,7 @@ int launch_knn16_candidates(const void *Q16, int64_t nq, const void *X16, int64_
         return RG_EINVAL;
     }
     if (nq == 0) return RG_OK;
-    if (s <= 0) return old_series(Q16, nq, X16, n, dp, K, ids, scores, stream);
+    if (s <= 0) return running_topk(Q16, nq, X16, n, dp, K, ids, scores, stream);
     const int nks = dp / KS16;
     const int64_t ns = (n + s - 1) / s;
     const int64_t xtiles = (n + BX16 - 1) / BX16, stiles = (ns + BX16 - 1) / BX16;
@@ -1417,7 +1417,7 @@ int launch_knn16_candidates(const void *Q16, int64_t nq, const void *X16, int64_
     const size_t bytes = sizeof(float) * chunk * (size_t)G + 8 * (size_t)chunk * SCAP + 8 * (size_t)chunk +
                          4 * (size_t)nq + 8 * 256;
     // no room for the buffers: the running top-K needs less
-    if (mem.alloc(bytes)) return old_series(Q16, nq, X16, n, dp, K, ids, scores, stream);
+    if (mem.alloc(bytes)) return running_topk(Q16, nq, X16, n, dp, K, ids, scores, stream);
     gm = mem.take<float>(chunk * (size_t)G);
     thr = mem.take<float>(chunk);
     buf_sc = mem.take<float>(chunk * (size_t)SCAP);
@@ -1479,7 +1479,7 @@ int launch_knn16_candidates(const void *Q16, int64_t nq, const void *X16, int64_
     hipLaunchKernelGGL(k_gather16, dim3((unsigned)(fp / 16)), dim3(256), 0, stream,
                        static_cast<const _Float16 *>(Q16), fail, (int64_t)nf, nks, qs);
     RG_HIP(hipGetLastError());
-    rc = old_series(qs, nf, X16, n, dp, K, fid, fsc, stream);
+    rc = running_topk(qs, nf, X16, n, dp, K, fid, fsc, stream);
     if (rc) return rc;
     hipLaunchKernelGGL(k_scatter_lists, dim3(nf), dim3(64), 0, stream, fail, K, fsc, fid, scores, ids);
     RG_HIP(hipGetLastError());

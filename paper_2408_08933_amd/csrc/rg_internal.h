@@ -59,7 +59,6 @@ struct SearchArgs {
     int64_t bm_words;
     uint32_t *work;
     int32_t grid;
-    int32_t prep;               // wavefronts per preparation (launch_search_wide)
     int *occ_out;
 };
 
@@ -75,11 +74,12 @@ int launch_search_persistent(const SearchArgs &a, hipStream_t stream);
 // FP32 rows, one query per workgroup, an exact visited bitmap of 4 <<
 // a.hash_bits bytes in LDS
 int launch_search_bits(const SearchArgs &a, hipStream_t stream);
-// a.grid wavefronts (2 .. kMaxWide) per query; ELL rows of at most 64 ids.
+// a.grid wavefronts (2 .. kMaxWide, kPrep to a preparation) per query; ELL
+// rows of at most 64 ids.
 // a.sets: the visited table of set_table; else an exact one of 2^hash_bits
 // ids that overflows into the bitmaps (one per query; null where
 // n nodes and kMaxWide + 1 rows of 64 fill less than 3/4 of the table)
-constexpr int kMaxWide = 8;
+constexpr int kMaxWide = 8, kPrep = 2;
 int launch_search_wide(const SearchArgs &a, hipStream_t stream);
 int search_occupancy(const SearchArgs &a, int *blocks_per_cu);
 // workgroups of the LDS-table search (k_search) one CU holds with a.hash_bits and a.sets
@@ -109,12 +109,8 @@ struct SlotArgs {
     int32_t *slot_k, *slot_L;
     float *slot_qd;             // slots x kMaxL queue distances
     uint32_t *slot_qi;          // slots x kMaxL queue ids (+flag)
-    int32_t *slot_state;        // slots x 4: qn, ptr, hops, evals
+    int32_t *slot_state;        // slots x 8: qn, ptr, the table's count, hops, evals
     uint32_t *slot_hash;        // slots x (1 << hash_bits)
-    int32_t *slot_hcount;       // slots
-    uint32_t *slot_out_ids;     // unused
-    float *slot_out_d;          // unused
-    int32_t *slot_done;         // unused
     int32_t hops_budget;
     // finished requests are appended here: out_count (atomic) and records
     uint32_t *out_count;
