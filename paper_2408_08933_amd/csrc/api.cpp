@@ -19,6 +19,12 @@ static thread_local int64_t g_knn_rows[3];
 
 void set_error(const std::string &msg) { g_err = msg; }
 
+int no_memory(const std::string &msg) {
+    (void)hipGetLastError();
+    set_error(msg);
+    return RG_ENOMEM;
+}
+
 namespace {
 
 int32_t round_up(int32_t v, int32_t m) { return (v + m - 1) / m * m; }
@@ -50,9 +56,7 @@ struct DevBuf {
     int alloc(size_t bytes) {
         if (hipMalloc(&p, bytes ? bytes : 1) != hipSuccess) {
             p = nullptr;
-            (void)hipGetLastError();  // callers may go on without it
-            set_error("out of device memory (" + std::to_string(bytes) + " bytes)");
-            return RG_ENOMEM;
+            return no_memory("out of device memory (" + std::to_string(bytes) + " bytes)");
         }
         return RG_OK;
     }
@@ -84,8 +88,7 @@ int upload_base(rg_index *ix, const float *base_dev, hipStream_t st) {
     ix->pitch = round_up(ix->d, 16);
     if (hipMalloc(&ix->d_base, sizeof(float) * (size_t)ix->n * ix->pitch) != hipSuccess) {
         ix->d_base = nullptr;
-        set_error("index: out of device memory for the base rows");
-        return RG_ENOMEM;
+        return no_memory("index: out of device memory for the base rows");
     }
     return launch_pad_rows(base_dev, ix->n, ix->d, ix->d_base, ix->pitch, st);
 }
@@ -105,13 +108,11 @@ int upload_adj(rg_index *ix, hipStream_t st) {
         ix->ell = 0;
         if (hipMalloc(&ix->d_adj, sizeof(uint32_t) * (size_t)std::max<int64_t>(nnz, 1)) != hipSuccess) {
             ix->d_adj = nullptr;
-            set_error("index: out of device memory for the adjacency");
-            return RG_ENOMEM;
+            return no_memory("index: out of device memory for the adjacency");
         }
         if (hipMalloc(&ix->d_adj_off, sizeof(int64_t) * (size_t)(n + 1)) != hipSuccess) {
             ix->d_adj_off = nullptr;
-            set_error("index: out of device memory for the adjacency");
-            return RG_ENOMEM;
+            return no_memory("index: out of device memory for the adjacency");
         }
         RG_HIP(hipMemcpyAsync(ix->d_adj, ix->indices.data(), sizeof(uint32_t) * (size_t)nnz, hipMemcpyHostToDevice,
                               st));
@@ -123,8 +124,7 @@ int upload_adj(rg_index *ix, hipStream_t st) {
     ix->ell = round_up((int32_t)maxdeg, 8);
     if (hipMalloc(&ix->d_adj, sizeof(uint32_t) * (size_t)n * ix->ell) != hipSuccess) {
         ix->d_adj = nullptr;
-        set_error("index: out of device memory for the adjacency");
-        return RG_ENOMEM;
+        return no_memory("index: out of device memory for the adjacency");
     }
     std::vector<uint32_t> ell((size_t)n * ix->ell, kNone);
     for (int64_t x = 0; x < n; ++x)
@@ -599,7 +599,6 @@ int rg_build(const float *base, int64_t n, int32_t d, const float *train, int64_
     if (rc == RG_ENOMEM && lists.p) {
         // no room for the rows beside the lists: these go to the host, and the
         // projection with them
-        (void)hipGetLastError();
         knn.resize((size_t)nt * Nq);
         rc = hipMemcpyAsync(knn.data(), lists.p, sizeof(uint32_t) * knn.size(), hipMemcpyDeviceToHost, st) == hipSuccess &&
                      hipStreamSynchronize(st) == hipSuccess
@@ -793,8 +792,7 @@ int grow_device_base(rg_index *ix, const float *rows_host, int64_t nv, hipStream
     RG_HIP(hipMemcpyAsync(tmp.p, rows_host, sizeof(float) * (size_t)nv * ix->d, hipMemcpyHostToDevice, st));
     float *nb = nullptr;
     if (hipMalloc(&nb, sizeof(float) * (size_t)(ix->n + nv) * ix->pitch) != hipSuccess) {
-        set_error("insert: out of device memory for the base rows");
-        return RG_ENOMEM;
+        return no_memory("insert: out of device memory for the base rows");
     }
     if (hipMemcpyAsync(nb, ix->d_base, sizeof(float) * (size_t)ix->n * ix->pitch, hipMemcpyDeviceToDevice, st) !=
             hipSuccess ||
@@ -820,8 +818,7 @@ int upload_tomb(rg_index *ix, hipStream_t st) {
     if (ix->n_deleted == 0 || !ix->d_base) return RG_OK;
     if (hipMalloc(&ix->d_tomb, sizeof(uint32_t) * ix->tomb.size()) != hipSuccess) {
         ix->d_tomb = nullptr;
-        set_error("delete: out of device memory for the tombstones");
-        return RG_ENOMEM;
+        return no_memory("delete: out of device memory for the tombstones");
     }
     RG_HIP(hipMemcpyAsync(ix->d_tomb, ix->tomb.data(), sizeof(uint32_t) * ix->tomb.size(), hipMemcpyHostToDevice, st));
     RG_HIP(hipStreamSynchronize(st));
@@ -1003,8 +1000,7 @@ int rg_index_set_storage(rg_index *ix, int32_t storage, void *stream) {
     if (storage == RG_STORE_BF16 && !ix->d_bf16) {
         if (hipMalloc(&ix->d_bf16, sizeof(uint16_t) * (size_t)ix->n * ix->pitch) != hipSuccess) {
             ix->d_bf16 = nullptr;
-            set_error("set_storage: out of device memory");
-            return RG_ENOMEM;
+            return no_memory("set_storage: out of device memory");
         }
         const int rc = launch_quant_bf16(ix->d_base, ix->n, ix->pitch, ix->d_bf16, st);
         if (rc) return rc;
@@ -1016,8 +1012,7 @@ int rg_index_set_storage(rg_index *ix, int32_t storage, void *stream) {
             if (ix->d_fp8) (void)hipFree(ix->d_fp8);
             ix->d_fp8 = nullptr;
             ix->d_scale = nullptr;
-            set_error("set_storage: out of device memory");
-            return RG_ENOMEM;
+            return no_memory("set_storage: out of device memory");
         }
         const int rc = launch_quant_fp8(ix->d_base, ix->n, ix->d, ix->pitch, ix->d_fp8, ix->pitch8, ix->d_scale, st);
         if (rc) return rc;
@@ -1098,8 +1093,7 @@ int rg_search(const rg_index *ix, const float *queries, int64_t nq, int32_t k, i
             while (a.hash_bits < (a.grid == 8 ? 15 : 14) && (1 << a.hash_bits) < 80 * a.Leff) ++a.hash_bits;
             if (ix->n + 64 * (kMaxWide + 1) > (3ll << a.hash_bits) / 4) {
                 if (hipMallocAsync(&ws, (size_t)nq * a.bm_words * 4, st) != hipSuccess) {
-                    set_error("rg_search: out of device memory for visited bitmaps");
-                    return RG_ENOMEM;
+                    return no_memory("rg_search: out of device memory for visited bitmaps");
                 }
                 a.bitmap = static_cast<uint32_t *>(ws);
             }
@@ -1138,8 +1132,7 @@ int rg_search(const rg_index *ix, const float *queries, int64_t nq, int32_t k, i
     void *ws = nullptr;
     const size_t bytes = (size_t)grid * a.bm_words * 4 + 256;
     if (hipMallocAsync(&ws, bytes, st) != hipSuccess) {
-        set_error("rg_search: out of device memory for visited bitmaps");
-        return RG_ENOMEM;
+        return no_memory("rg_search: out of device memory for visited bitmaps");
     }
     a.work = static_cast<uint32_t *>(ws);
     a.bitmap = reinterpret_cast<uint32_t *>(static_cast<char *>(ws) + 256);

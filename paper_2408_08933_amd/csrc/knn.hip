@@ -1160,9 +1160,7 @@ struct DevMem {
     int alloc(size_t bytes) {
         if (hipMalloc(&p, bytes) != hipSuccess) {
             p = nullptr;
-            (void)hipGetLastError();  // else the next launch's check would find it
-            set_error("knn: out of device memory (" + std::to_string(bytes) + " bytes)");
-            return RG_ENOMEM;
+            return no_memory("knn: out of device memory (" + std::to_string(bytes) + " bytes)");
         }
         return RG_OK;
     }
@@ -1208,17 +1206,13 @@ int knn_range(const KnnKernel &kk, const void *Q, int64_t nq, int32_t ldq, const
     if (hipMalloc(&buf_sc, sizeof(float) * slots * kk.bq * CAP) != hipSuccess ||
         hipMalloc(&buf_id, sizeof(uint32_t) * slots * kk.bq * CAP) != hipSuccess) {
         cleanup();
-        (void)hipGetLastError();
-        set_error("knn: out of device memory for candidate buffers");
-        return RG_ENOMEM;
+        return no_memory("knn: out of device memory for candidate buffers");
     }
     if (splits > 1) {
         if (hipMalloc(&tmp_sc, sizeof(float) * splits * nq * K) != hipSuccess ||
             hipMalloc(&tmp_id, sizeof(uint32_t) * splits * nq * K) != hipSuccess) {
             cleanup();
-            (void)hipGetLastError();
-            set_error("knn: out of device memory for split lists");
-            return RG_ENOMEM;
+            return no_memory("knn: out of device memory for split lists");
         }
     }
     KnnArgs a{};

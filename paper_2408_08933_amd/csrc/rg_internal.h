@@ -20,6 +20,9 @@ constexpr int kMaxSearchL = 1024;            // largest queue of rg_search (L_ef
 constexpr int kMaxEll = 128;                  // widest ELL row; wider graphs are searched as CSR
 
 void set_error(const std::string &msg);
+// RG_ENOMEM for a failed allocation.  The runtime keeps the failure as the
+// thread's last error, where the check after some later launch would find it.
+int no_memory(const std::string &msg);
 
 // status helpers
 #define RG_HIP(call)                                                                  \

@@ -358,8 +358,7 @@ int rg_server_create(const rg_index *ix, const rg_server_limits *lim, rg_server 
     if (!ok) {
         s->release();
         delete s;
-        set_error("rg_server_create: out of memory");
-        return RG_ENOMEM;
+        return no_memory("rg_server_create: out of memory");
     }
     s->t0 = std::chrono::steady_clock::now();
     s->th = std::thread([s]() { s->loop(); });

@@ -183,3 +183,28 @@ def test_visited_table_of_wide_rows(fake, deg, d, L, kb):
         assert fake.fake_shared(I64(0)) - (4 * pad + 8 * L + 20 * cand) == {kb} << 10
         lib.rg_free(ix)
     """)
+
+
+def test_calls_after_one_without_room(fake):
+    # each call that finds no room says so, and leaves nothing behind for the next one
+    run(fake, """
+        n, d = 50_000, 64
+        X, off, idx = np.zeros((n, d), np.float32), np.arange(n + 1), np.zeros(n, np.uint32)
+        def index():
+            ix = C.c_void_p()
+            rc = lib.rg_index_from_csr(P(X), I64(n), d, P(off), P(idx), 0, 0, None, C.byref(ix))
+            return rc, ix
+        def search(nq, evals):
+            return lib.rg_search(ix, P(X), I64(nq), 10, 100, P(idx), P(X), None, P(idx) if evals else None, None)
+        rc, ix = index()
+        ok(rc)
+        calls = [lambda: search(1, False), lambda: search(2000, True), lambda: lib.rg_index_set_storage(ix, 1, None),
+                 lambda: lib.rg_index_set_storage(ix, 2, None), lambda: index()[0],
+                 lambda: lib.rg_knn(P(X), I64(10), P(X), I64(n), d, 5, P(idx), P(X), None)]
+        for call in calls:
+            fake.fake_limit(fake.fake_in_use() + 5000)
+            assert call() == -2, lib.rg_last_error()
+            fake.fake_limit(0)
+            ok(search(2000, False))
+        lib.rg_free(ix)
+    """)
