@@ -85,10 +85,13 @@ enum { RG_STAGE_PROJECTED = 1, RG_STAGE_BIPARTITE = 2 };
  *          enhancement use m_pj + m_ce <= M - 1 and one slot per node is left
  *          for the reachability repair.
  * The Nq-NN lists come from the GPU kNN (rg_knn semantics: FP16 or FP32 MFMA
- * candidates, exact FP64 rerank with a certified margin); the graph steps run
- * on host threads with the canonical FP64 distance (sum of exact products in
- * increasing coordinate order).  The result is deterministic and independent
- * of the thread count.  On success *out owns a device copy of the base, the
+ * candidates, exact FP64 rerank with a certified margin).  Projection and
+ * enhancement run on the device and the rest (bipartite graph, medoid, merge,
+ * repair) on host threads, every decision by the canonical FP64 distance (sum
+ * of exact products in increasing coordinate order); where the device has no
+ * room for the projection or the reverse updates, host threads run those too.
+ * The result is deterministic and independent of the thread count and of
+ * where a step ran.  On success *out owns a device copy of the base, the
  * adjacency, and a host CSR view (rg_index_graph).
  * Errors: RG_EINVAL (n < 1, n >= 2^31, d < 1, nt < 1, Nq < 2, Nq > n, M < 3,
  * M > 128, metric != RG_METRIC_IP, null pointers), RG_ENOMEM, RG_EDEVICE,
@@ -238,14 +241,16 @@ int rg_index_info(const rg_index *idx, int64_t *n, int32_t *d, int32_t *pitch,
 int rg_index_set_storage(rg_index *idx, int32_t storage, void *stream);
 
 /*
- * rg_search -- batched beam search (Sec. 4.3), one query per wavefront.
+ * rg_search -- batched beam search (Sec. 4.3), one wavefront per query, or
+ *   several where there are few queries.
  *   queries device, nq x d float32.
  *   k       results per query (1..1024); L queue length (1..1024); the
  *           queue actually kept is L_eff = max(L, k).  Queues of up to 512
  *           entries and longer ones run in separate kernels (the longer
  *           holding twice the queue entries per lane), with the same rules.
  *   ids     device, nq x k uint32; dists device, nq x k float32 holding
- *           -<q, x_id> in FP32, ascending; when fewer than k nodes are
+ *           -<q, x_id> in FP32, ascending (a distance that is NaN ranks as
+ *           +inf and is returned as NaN); when fewer than k nodes are
  *           reachable the tail is 0xFFFFFFFF / +inf.
  *   hops    device, nq uint32 or NULL: nodes expanded per query.
  *   evals   device, nq uint32 or NULL: distances computed per query
@@ -265,7 +270,8 @@ int rg_index_set_storage(rg_index *idx, int32_t storage, void *stream);
  * row batch is at most 256 ids), or 8 KB for FP32 rows of d > 128.  For n up
  * to 2^24 (4 KB: 2^25; 1 KB: 2^23) and rows of at most 64 ids it holds 16-bit
  * entries in sets of four that drop their oldest; otherwise node ids, cleared
- * at half load.
+ * at half load (and then 4 KB for L_eff <= 128, 64 < d <= 256 and rows of at
+ * most 112 ids or CSR).
  * Asynchronous on stream.
  * Errors: RG_EINVAL, RG_EDEVICE.
  */
@@ -285,7 +291,8 @@ int rg_search(const rg_index *idx, const float *queries, int64_t nq, int32_t k, 
  * canonical score, so no other base row can be among the k nearest.  Rows
  * not certified are redone from FP32 MFMA scores (k + slack candidates,
  * doubling to 256) and, failing that (more than 256 rows tied), by a full
- * canonical scan on the host.  ids are in (delta, id) order and dists hold
+ * canonical scan on the host.  Where the lists of all queries do not fit the
+ * device, the queries are taken in parts.  ids are in (delta, id) order and dists hold
  * the FP64 delta rounded to float.  Synchronous.
  * Errors: RG_EINVAL (k < 1, k > n, k > 224, n >= 2^31), RG_ENOMEM,
  * RG_EDEVICE.
