@@ -177,7 +177,7 @@ int choose_table(SearchArgs &a, int cus) {
     // 7.2 / 7.8, BF16 100k x 96, 100 ids, L = 100 1.19 times as fast; but 128 ids
     // 0.96 times, and d = 64, 100 ids, L = 100 6.4 / 5.9.
     set_table(a, best);
-    if (!a.sets && (a.adj_off || a.ell <= 112) && a.d > 64 && a.d <= 256 && a.Leff <= 128 &&
+    if (!a.sets && (a.adj_off || (a.ell > 64 && a.ell <= 112)) && a.d > 64 && a.d <= 256 && a.Leff <= 128 &&
         !(a.storage == RG_STORE_FP32 && a.d > 128))
         return RG_OK;
     for (int hb = a.storage == RG_STORE_FP32 && a.d > 128 ? 11 : 10; hb >= 8; --hb) {
