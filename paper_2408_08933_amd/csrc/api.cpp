@@ -576,11 +576,18 @@ int rg_build(const float *base, int64_t n, int32_t d, const float *train, int64_
         rc = knn_exact(train, nt, base, n, d, Nq, o.knn_slack, xh.data(), threads, lists.as<uint32_t>(), nullptr, st);
     if (rc) return rc;
     std::vector<uint32_t> knn;
-    if (o.keep_stages) {
+    if (o.keep_stages || n <= 256) {
         knn.resize((size_t)nt * Nq);
         RG_HIP(hipMemcpyAsync(knn.data(), lists.p, sizeof(uint32_t) * knn.size(), hipMemcpyDeviceToHost, st));
     }
     RG_HIP(hipStreamSynchronize(st));
+    // a list of the whole base is certified as it is, and lacks the rows whose
+    // scores are NaN
+    if (n <= 256 && std::find(knn.begin(), knn.end(), kNone) != knn.end()) {
+        set_error("rg_build: a training query has fewer than Nq base rows at a distance that is a number");
+        return RG_EINVAL;
+    }
+    if (!o.keep_stages) std::vector<uint32_t>().swap(knn);
     if (std::getenv("RG_LOG"))
         std::fprintf(stderr, "[rg] kNN preprocessing done in %.2f s\n",
                      std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count());

@@ -60,6 +60,12 @@ __device__ __forceinline__ double canon_sum(const float *q, const float *row, in
     return s;
 }
 
+// delta(q, row).  A NaN counts as +inf: without a place in the order it would
+// leave holes in a queue and gaps among ranks.
+__device__ __forceinline__ double canon_delta(const float *q, const float *row, int d) {
+    return __builtin_fmin(-canon_sum(q, row, d), __builtin_inf());
+}
+
 struct CanonArgs {
     const float *X;         // n x pitch (zero padded)
     const uint32_t *adj;    // n x ell
@@ -188,7 +194,7 @@ __global__ __launch_bounds__(64) void k_canon_search(CanonArgs a) {
         wave_sync();
         shared_sums<double, 1>(a, qrow, ci, 1, qd);
     } else if (lane == 0) {
-        qd[0] = -canon_sum(qrow, a.X + (size_t)a.entry * a.pitch, d);
+        qd[0] = canon_delta(qrow, a.X + (size_t)a.entry * a.pitch, d);
     }
     if (lane == 0) {
         qi[0] = a.entry;
@@ -250,7 +256,7 @@ __global__ __launch_bounds__(64) void k_canon_search(CanonArgs a) {
                 return;
             }
         } else {
-            for (int j = lane; j < nnew; j += 64) cd[j] = -canon_sum(qrow, a.X + (size_t)ci[j] * a.pitch, d);
+            for (int j = lane; j < nnew; j += 64) cd[j] = canon_delta(qrow, a.X + (size_t)ci[j] * a.pitch, d);
             wave_sync();
             if (nnew <= 64)
                 merge_batch<1, double>(s.ql, nnew, L, qn, ptr);
@@ -262,7 +268,7 @@ __global__ __launch_bounds__(64) void k_canon_search(CanonArgs a) {
     for (int i = lane; i < qn; i += 64) {
         const uint32_t u = qi[i] & ~kExpanded;
         a.out_ids[b * L + i] = u;
-        a.out_d[b * L + i] = NEAR ? -canon_sum(qrow, a.X + (size_t)u * a.pitch, d) : qd[i];
+        a.out_d[b * L + i] = NEAR ? canon_delta(qrow, a.X + (size_t)u * a.pitch, d) : qd[i];
     }
     if (lane == 0) a.out_n[b] = qn;
 }
@@ -319,8 +325,7 @@ __device__ __forceinline__ void rank_candidates(const CandArgs &a, const float *
     for (int e = 0; e < E; ++e) {
         const int j = e * 64 + lane;  // any assignment of candidates to lanes will do
         id[e] = j < cnt ? cid[j] : kNone;
-        key[e] = j < cnt ? -canon_sum(xrow, a.X + (size_t)id[e] * a.pitch, a.d) : INFINITY;
-        if (!(key[e] < INFINITY)) key[e] = INFINITY;  // a NaN has no place in the order
+        key[e] = j < cnt ? canon_delta(xrow, a.X + (size_t)id[e] * a.pitch, a.d) : INFINITY;
     }
     wave_sort<E, double>(key, id);
     const int nk = min(cnt, a.L);
@@ -508,7 +513,7 @@ __global__ __launch_bounds__(64) void k_canon_select(SelectArgs a) {
                 if (open) {
                     const int t = __builtin_ctz(open);
                     open &= open - 1;
-                    if (!(dxc < -canon_sum(crow, kept_row(r0 + t), a.d))) {
+                    if (!(dxc < canon_delta(crow, kept_row(r0 + t), a.d))) {
                         alive = false;
                         open = 0;
                     }
@@ -632,7 +637,7 @@ __global__ __launch_bounds__(64) void k_replay(ReplayArgs a) {
                 } else {
                     c[s] = (uint32_t)p;
                 }
-                dj[s] = -canon_sum(xrow, a.X + (size_t)c[s] * a.pitch, a.d);
+                dj[s] = canon_delta(xrow, a.X + (size_t)c[s] * a.pitch, a.d);
             }
         }
         const double d0 = __shfl(dj[0], nc & 63), d1 = __shfl(dj[1], nc & 63);
@@ -750,7 +755,7 @@ __global__ __launch_bounds__(64) void k_replay_fill(ReplayArgs a) {
             load_row((uint32_t)p);
 #pragma unroll
             for (int s = 0; s < SL; ++s)
-                if (id[s] != kNone) key[s] = -canon_sum(xrow, a.X + (size_t)id[s] * a.pitch, a.d);
+                if (id[s] != kNone) key[s] = canon_delta(xrow, a.X + (size_t)id[s] * a.pitch, a.d);
             for (int r = 0; r < a.m; ++r) {
                 const uint32_t ir = id_of(r);
                 const double kr = key_of(r);
@@ -759,7 +764,7 @@ __global__ __launch_bounds__(64) void k_replay_fill(ReplayArgs a) {
                 for (int s = 0; s < SL; ++s)
                     if (id[s] != kNone && kless(kr, ir, key[s], id[s])) {
                         ++rank[s];
-                        const double dj = -canon_sum(xrow, a.X + (size_t)id[s] * a.pitch, a.d);
+                        const double dj = canon_delta(xrow, a.X + (size_t)id[s] * a.pitch, a.d);
                         if (!(key[s] < dj)) {
 #pragma unroll
                             for (int t = 0; t < SL; ++t)
@@ -775,7 +780,7 @@ __global__ __launch_bounds__(64) void k_replay_fill(ReplayArgs a) {
         for (int s = 0; s < SL; ++s) {
             const bool here = lane + 64 * s == open;
             dj[s] = here || id[s] != kNone
-                        ? -canon_sum(xrow, a.X + (size_t)(here ? (uint32_t)p : id[s]) * a.pitch, a.d)
+                        ? canon_delta(xrow, a.X + (size_t)(here ? (uint32_t)p : id[s]) * a.pitch, a.d)
                         : 0.0;
         }
         double dx = __shfl(dj[0], open & 63);
@@ -840,8 +845,7 @@ __global__ __launch_bounds__(64) void k_replay_fill(ReplayArgs a) {
                 settled |= km | om;
                 any |= undecided[s];
             }
-            // a round settles none only where NaNs leave no order
-            if (ballot64(any) == 0 || settled == 0) break;
+            if (ballot64(any) == 0 || settled == 0) break;  // (every round settles the lowest rank still open)
         }
         // the highest rank of those out, or of all
         bool none_out = true;

@@ -39,6 +39,9 @@ namespace {
 using Clock = std::chrono::steady_clock;
 double secs(Clock::time_point a, Clock::time_point b) { return std::chrono::duration<double>(b - a).count(); }
 
+// A distance that is NaN counts as +inf, so that every order has a place for it.
+inline double ordered(double v) { return v == v ? v : INFINITY; }
+
 constexpr int kHead = 16;  // leading enhancement candidates kept per node for the repair
 
 template <class F>
@@ -145,14 +148,14 @@ void dist8(const float *q, const float *const r[8], int d, double out[8]) {
         s6 += qi * (double)r[6][i];
         s7 += qi * (double)r[7][i];
     }
-    out[0] = -s0;
-    out[1] = -s1;
-    out[2] = -s2;
-    out[3] = -s3;
-    out[4] = -s4;
-    out[5] = -s5;
-    out[6] = -s6;
-    out[7] = -s7;
+    out[0] = ordered(-s0);
+    out[1] = ordered(-s1);
+    out[2] = ordered(-s2);
+    out[3] = ordered(-s3);
+    out[4] = ordered(-s4);
+    out[5] = ordered(-s5);
+    out[6] = ordered(-s6);
+    out[7] = ordered(-s7);
 }
 
 // out[j] = delta(q, X[ids[j]]) for j < cnt
@@ -366,7 +369,7 @@ struct Searcher {
 double canon_dist(const float *a, const float *b, int32_t d) {
     double s = 0.0;
     for (int32_t i = 0; i < d; ++i) s += (double)a[i] * (double)b[i];
-    return -s;
+    return ordered(-s);
 }
 
 int hw_threads(int requested) {

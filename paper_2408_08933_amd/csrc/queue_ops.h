@@ -264,8 +264,7 @@ __device__ __forceinline__ bool merge_held(K *qd, uint32_t *qi, uint32_t *bits, 
         const uint64_t w = ((uint64_t)lane_value(word, 2 * r + 1) << 32) | lane_value(word, 2 * r);
         before -= (int)__popcll(w);
         const int p = 64 * r + lane;
-        // (FP64 keys may be NaN; without an order places could coincide: still an entry)
-        const int i = max(0, min(p - before - lanes_below(w), qn - 1));
+        const int i = max(0, min(p - before - lanes_below(w), qn - 1));  // (a lane past the queue reads an entry)
         const K md = qd[i];
         const uint32_t mi = qi[i];
         wave_sync();
